@@ -223,6 +223,7 @@ struct Level {
   DBuf gs_coef;    // double, wave-tiled by slot: ncoef() values per slot
   DBuf gs_dinv;    // double [slots * ndof]
   DBuf gs_d;       // double [slots * ndof]: the sweep's corrections by slot
+  int64_t gs_records = 0;  // > 0: 2D levels swept by rows (gs_pbase, gs_coef hold k_gs_sweep2d's records)
   double lambda = 0.0;
   std::vector<double> cheb_c1, cheb_c2;  // per Chebyshev step: direction and residual factors
   // work vectors (regional): b (rhs), u / u2 (ping-pong), d (Chebyshev direction), r (residual)
