@@ -148,9 +148,8 @@ typedef struct {
                          after each coarse correction, and a dense inverse on the first AMG level
                          with at most amg_coarse_size rows */
   int amg_coarse_size; /* rows of the directly solved AMG level, in [1, 20000] (default 2000) */
-  int region_table;   /* 1 (default): on symmetric 27-point FP64 levels of the FP64 V-cycle (scalar
-                         levels on 768-thread 2.5D tiles or node blocks, 3-dof levels on node
-                         blocks; the FP32 V-cycle always streams), setup sorts every region's nodes
+  int region_table;   /* 1 (default): on symmetric 27-point levels (scalar or 3-dof, FP64 and
+                         low-precision V-cycles), setup sorts every region's nodes
                          into 125 classes (per axis: the two low layers, the inside, the two high
                          layers) and compares each node's 27 couplings (its stored upper ones and
                          its neighbours' mirrored ones; 3 x 3 blocks on 3-dof levels) with those of
@@ -158,7 +157,8 @@ typedef struct {
                          operator is the same everywhere inside, as the structured regions of the
                          Q1 Laplacian, the per-region diffusion and elasticity problems give), the
                          region's couplings come from its 125 x 27 class table (whole-row tiles on
-                         tiled levels, each node's class row on node blocks) instead of being
+                         scalar levels of 2.5D tiles or at least 150,000 nodes, each node's class row
+                         on node blocks; the low-precision V-cycle has a table of its own values) instead of being
                          streamed from memory.  Results are bit for bit those of 0, which always
                          streams them */
   int tile_planes;    /* planes per 2.5D tile: 0 (default) chooses (41 on FP64 levels that keep at
@@ -376,8 +376,9 @@ rmg_status rmg_level_tiles(rmg_handle* h, int level, int* ntiles, int* threads, 
  * restriction's and the prolongation's blocks, 0 where they run one thread per node (and on the
  * coarsest level).  Any output may be NULL. */
 rmg_status rmg_level_transfer_tiles(rmg_handle* h, int level, int* restriction_tiles, int* prolongation_tiles);
-/* Regions of `level` whose couplings the 2.5D kernels take from the region's class table
- * (rmg_options.region_table); 0 where no table was built.  Output may be NULL. */
+/* Regions of `level` whose couplings the FP64 V-cycle takes from the region's class table
+ * (rmg_options.region_table); 0 where no table was built and with a low-precision V-cycle.
+ * Output may be NULL. */
 rmg_status rmg_level_table_regions(rmg_handle* h, int level, int* nregions);
 /* Copy region `region`'s stencil on `level` to host memory in the layout of
  * rmg_set_region_stencil (npts 27 in 3D, 9 in 2D, all levels). */

@@ -257,6 +257,8 @@ static void begin_operator_change(rmg_handle* h, Level& L) {
   L.coef_lo_sym.release();
   L.class_table.release();
   L.class_table_ok.release();
+  L.class_table_lo.release();
+  L.class_table_lo_ok.release();
   clear_split(L);
 }
 
@@ -764,7 +766,7 @@ rmg_status rmg_level_table_regions(rmg_handle* h, int level, int* nregions) {
   Level& L = level_of(h, level);
   const DBuf& ok = L.class_table_ok;
   int count = 0;
-  if (ok.p) {
+  if (ok.p && h->opt.precision == RMG_PREC_FP64) {
     std::vector<int> flags(L.nreg);
     RMG_HIP(hipStreamSynchronize(h->stream));
     RMG_HIP(hipMemcpy(flags.data(), ok.p, sizeof(int) * L.nreg, hipMemcpyDeviceToHost));

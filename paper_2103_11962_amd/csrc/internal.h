@@ -96,13 +96,12 @@ constexpr size_t kDeepTileMin = 1024;  // 41-plane FP64 tiles needed before they
 constexpr int kTileThreadsF64 = 768;
 constexpr int kTileThreadsF32 = 256;
 // Threads per whole-region tile of a table region (k_stencil_table): the inner x-nodes of a few rows
-// padded to whole wavefronts plus their rows' four x-face nodes; planes and rows per tile at most.
+// padded to whole wavefronts plus their rows' four x-face nodes; planes per tile at most.
 // Five rows of 82 nodes fill 468 of 512 lanes; at six waves per SIMD three 8-wave blocks run per CU
 // (on C2: 284 us per Chebyshev step, against 307 us for four rows in 384 threads, 288 us for eight
 // rows in 768, 312 us for seven in 640).
 constexpr int kTableThreads = 512;
 constexpr int kTablePlanes = 41;
-constexpr int kTableRows = 5;
 // Largest (tx + 2)(ty + 2) over tiles of at most nt nodes (tx * ty <= nt): the single row, ty = 1.
 constexpr int tile_plane_cap(int nt) { return 3 * (nt + 2); }
 // Region tables: a node's class along an axis of extent e >= 5 is its coordinate on the two low
@@ -192,14 +191,24 @@ struct Level {
   // operator (FP64, wave-tiled, ncoef() values per node: npts blocks of ndof x ndof)
   DBuf coef;
   DBuf coef_sym;     // symmetric scalar 27-point levels: the upper half (kSymPts per node), else empty
-  // Region tables (FP64 levels run by 768-thread 2.5D tiles, else empty): per region the
+  // Region tables (symmetric 27-point levels, else empty): per region the
   // kClasses x kClassPts couplings of its node classes, and a flag that every node of the region
   // has its class's couplings bit for bit (the couplings the streaming kernel reads: its own upper
   // ones and its neighbours' mirrored ones, 0 towards neighbours outside the region).
   DBuf class_table, class_table_ok;
+  // The same couplings as the low-precision copy stores them, in FP32 (ndof x ndof blocks), and the
+  // regions all of whose nodes have them; empty without class_table or a low-precision copy.
+  DBuf class_table_lo, class_table_lo_ok;
   // With the tables: the served regions run whole-row tiles that take every coupling from the
   // tables (k_stencil_table), the other regions the level's streaming 2.5D tiles.  Built with the
   // tables (make_split), refreshed when the tiles change.
+  bool use_split = false;            // run the split (an autotuned level may prefer node blocks)
+  bool split_auto = false;           // a level without 2.5D tiles may run table tiles when they serve all of it
+  // the split also runs the CG product, whose (p, q) sums follow the launch's tiles: not with an FP32
+  // V-cycle on a forced tile kernel, where a rounding of alpha flips FP32 roundings of the next cycle
+  // and the solve would no longer repeat the streamed one to FP64 accuracy
+  bool split_dot = true;
+  bool deep_table = false;           // table tiles kTablePlanes deep, however few (rmg_options.tile_planes)
   std::vector<int> table_served;     // per region: 1 when the tables serve it
   std::vector<Tile3> table_tiles;    // whole-row tiles of the served regions (k_stencil_table)
   std::vector<Tile3> other_tiles;    // the level's 2.5D tiles of the regions not served
@@ -334,6 +343,8 @@ void make_tiles(Level& L, int depth);
 // Region-table split of a level whose table flags are `served` (per region): whole-row tiles of the
 // served regions and the remaining regions' tiles (also rebuilt by make_tiles while a split exists).
 void make_split(Level& L, const std::vector<int>& served);
+// Whether every served region's rows fit a table tile.
+bool split_fits(const Level& L, const std::vector<int>& served);
 // Row-and-plane tiles of the transfers between F and the next level C (F.rtiles, F.ptiles), or
 // none when `rows` is false or a region's rows are too long for them.
 void make_transfer_tiles(Level& F, const Level& C, bool rows);

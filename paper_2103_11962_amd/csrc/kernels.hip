@@ -1990,26 +1990,31 @@ __global__ __launch_bounds__(kBlock) void k_make_sym(LevelView L, const C* __res
 __device__ __forceinline__ bool same_bits(double a, double b) { return __double_as_longlong(a) == __double_as_longlong(b); }
 
 
-// Coupling s of node (x, y, z) of region R, A(i, i + offset(s)), as the symmetric kernels read it.
-template <int NDOF>
-__device__ __forceinline__ double read_coupling(const RegionGeo& R, const double* __restrict__ sym, int x, int y,
-                                                int z, int s, int a, int b) {
+// Coupling s of node (x, y, z) of region R, A(i, i + offset(s)), as the symmetric kernels read it
+// (from bfloat16 storage the centre block in FP32).
+template <int NDOF, class C>
+__device__ __forceinline__ double read_coupling(const RegionGeo& R, const C* __restrict__ sym,
+                                                const float* __restrict__ centre, int x, int y, int z, int s, int a,
+                                                int b) {
   constexpr int NB = NDOF * NDOF, NC = kSymPts * NB;
   const int64_t gi = R.off + ((int64_t)z * R.ey + y) * R.ex + x;
-  if (s >= 13) return sym[coef_index(gi, (s - 13) * NB + a * NDOF + b, NC)];
+  if (sizeof(C) == 2 && s == 13) return (double)centre[gi * NB + a * NDOF + b];
+  if (s >= 13) return (double)CoefLoad<C>::get(sym + coef_index(gi, (s - 13) * NB + a * NDOF + b, NC));
   int dx, dy, dz;
   stencil_offset<27>(s, dx, dy, dz);
   if ((unsigned)(x + dx) >= (unsigned)R.ex || (unsigned)(y + dy) >= (unsigned)R.ey || (unsigned)(z + dz) >= (unsigned)R.ez)
     return 0.0;
   // a lower block is the transpose of the neighbour's upper block
-  return sym[coef_index(gi + dx + (int64_t)dy * R.ex + (int64_t)dz * R.ex * R.ey, (13 - s) * NB + b * NDOF + a, NC)];
+  return (double)CoefLoad<C>::get(
+      sym + coef_index(gi + dx + (int64_t)dy * R.ex + (int64_t)dz * R.ex * R.ey, (13 - s) * NB + b * NDOF + a, NC));
 }
 
 // One block per region, one thread per class; a class's row holds its 27 (blocks of) couplings in
-// stencil order, each block row-major.
-template <int NDOF>
-__global__ __launch_bounds__(128) void k_class_table_ref(LevelView L, const double* __restrict__ sym,
-                                                         double* __restrict__ table, int* __restrict__ ok) {
+// stencil order, each block row-major, in the arithmetic's type V.
+template <int NDOF, class V, class C>
+__global__ __launch_bounds__(128) void k_class_table_ref(LevelView L, const C* __restrict__ sym,
+                                                         const float* __restrict__ centre, V* __restrict__ table,
+                                                         int* __restrict__ ok) {
   constexpr int NB = NDOF * NDOF;
   const int k = blockIdx.x, c = threadIdx.x;
   const RegionGeo R = L.regs[k];
@@ -2017,15 +2022,17 @@ __global__ __launch_bounds__(128) void k_class_table_ref(LevelView L, const doub
   if (c == 0) ok[k] = big ? 1 : 0;
   if (c >= kClasses) return;
   const int x = class_node(c % 5, R.ex), y = class_node(c / 5 % 5, R.ey), z = class_node(c / 25, R.ez);
-  double* out = table + ((int64_t)k * kClasses + c) * kClassPts * NB;
+  V* out = table + ((int64_t)k * kClasses + c) * kClassPts * NB;
   for (int s = 0; s < kClassPts; ++s)
-    for (int e = 0; e < NB; ++e) out[s * NB + e] = big ? read_coupling<NDOF>(R, sym, x, y, z, s, e / NDOF, e % NDOF) : 0.0;
+    for (int e = 0; e < NB; ++e)
+      out[s * NB + e] = big ? (V)read_coupling<NDOF, C>(R, sym, centre, x, y, z, s, e / NDOF, e % NDOF) : (V)0;
 }
 
 // One thread per node: a coupling that differs from its class's clears the region's flag.
-template <int NDOF>
-__global__ __launch_bounds__(kBlock) void k_class_table_check(LevelView L, const double* __restrict__ sym,
-                                                              const double* __restrict__ table, int* __restrict__ ok) {
+template <int NDOF, class V, class C>
+__global__ __launch_bounds__(kBlock) void k_class_table_check(LevelView L, const C* __restrict__ sym,
+                                                              const float* __restrict__ centre,
+                                                              const V* __restrict__ table, int* __restrict__ ok) {
   constexpr int NB = NDOF * NDOF;
   const BlockDesc bd = L.blocks[blockIdx.x];
   const RegionGeo R = L.regs[bd.region];
@@ -2034,13 +2041,27 @@ __global__ __launch_bounds__(kBlock) void k_class_table_check(LevelView L, const
   int x, y, z;
   decompose(R, li, x, y, z);
   const int c = (axis_class(z, R.ez) * 5 + axis_class(y, R.ey)) * 5 + axis_class(x, R.ex);
-  const double* ref = table + ((int64_t)bd.region * kClasses + c) * kClassPts * NB;
+  const V* ref = table + ((int64_t)bd.region * kClasses + c) * kClassPts * NB;
   bool same = true;
   for (int s = 0; s < kClassPts; ++s)
     for (int e = 0; e < NB; ++e)
-      same = same && same_bits(read_coupling<NDOF>(R, sym, x, y, z, s, e / NDOF, e % NDOF), ref[s * NB + e]);
+      same = same && same_bits(read_coupling<NDOF, C>(R, sym, centre, x, y, z, s, e / NDOF, e % NDOF), (double)ref[s * NB + e]);
   if (!same) ok[bd.region] = 0;
 }
+
+template <int NDOF, class V, class C>
+static void class_table_launch(const Level& L, const C* sym, const float* centre, V* tab, int* ok, hipStream_t st) {
+  RMG_LAUNCH((k_class_table_ref<NDOF, V, C>), dim3(L.nreg), dim3(128), 0, st, L.view(), sym, centre, tab, ok);
+  RMG_LAUNCH((k_class_table_check<NDOF, V, C>), dim3(L.blocks.size()), dim3(kBlock), 0, st, L.view(), sym, centre,
+             static_cast<const V*>(tab), ok);
+  LAUNCH_CHECK();
+}
+
+// Scalar levels below the 2.5D tiles' size take table tiles instead of node blocks from this many
+// nodes on.  A Chebyshev step on node blocks and on table tiles: 8 regions of 28^3 (176k nodes) 12 us
+// each, 12 ragged regions of 1.9M nodes 50 and 24 us, 8 regions of 82^3 (4.4M) 125 and 40 us; below,
+// a step is a few microseconds of latency either way and the tiles are too few for the chip.
+constexpr int64_t kTableMinNodes = 150000;
 
 static void make_class_table(Level& L, hipStream_t st) {
   DBuf& tab = L.class_table;
@@ -2049,29 +2070,42 @@ static void make_class_table(Level& L, hipStream_t st) {
   const int nb = L.ndof * L.ndof;
   tab.alloc(sizeof(double) * kClasses * kClassPts * nb * L.nreg);
   ok.alloc(sizeof(int) * L.nreg);
-  if (L.ndof == 3) {
-    RMG_LAUNCH(k_class_table_ref<3>, dim3(L.nreg), dim3(128), 0, st, L.view(), sym, tab.as<double>(), ok.as<int>());
-    RMG_LAUNCH(k_class_table_check<3>, dim3(L.blocks.size()), dim3(kBlock), 0, st, L.view(), sym,
-               static_cast<const double*>(tab.p), ok.as<int>());
-  } else {
-    RMG_LAUNCH(k_class_table_ref<1>, dim3(L.nreg), dim3(128), 0, st, L.view(), sym, tab.as<double>(), ok.as<int>());
-    RMG_LAUNCH(k_class_table_check<1>, dim3(L.blocks.size()), dim3(kBlock), 0, st, L.view(), sym,
-               static_cast<const double*>(tab.p), ok.as<int>());
-  }
-  LAUNCH_CHECK();
+  if (L.ndof == 3) class_table_launch<3, double, double>(L, sym, nullptr, tab.as<double>(), ok.as<int>(), st);
+  else class_table_launch<1, double, double>(L, sym, nullptr, tab.as<double>(), ok.as<int>(), st);
   std::vector<int> flags(L.nreg);
   RMG_HIP(hipMemcpyAsync(flags.data(), ok.p, sizeof(int) * L.nreg, hipMemcpyDeviceToHost, st));
   RMG_HIP(hipStreamSynchronize(st));
   int served = 0;
   for (int f : flags) served += f != 0;
+  clear_split(L);
   if (served == 0) {  // no region served: drop the tables, so the streaming kernel runs
     tab.release();
     ok.release();
-    clear_split(L);
-  } else if (L.use_tiles && L.tile_threads == kTileThreadsF64) {
+  } else if (L.ndof == 1 && L.use_tiles) {
     make_split(L, flags);
+  } else if (L.ndof == 1 && L.split_auto && served == L.nreg && L.n >= kTableMinNodes && split_fits(L, flags)) {
+    make_split(L, flags);
+    if (L.table_tiles.size() > L.blocks.size()) clear_split(L);  // (the partial sums' space)
+  }  // else node blocks: each block of a served region reads the tables
+}
+
+// The tables in the low-precision copy's values.  Its couplings are the FP64 ones rounded one by one,
+// so the FP32 copy is served where the FP64 operator is; the centre blocks beside BF16 storage carry
+// a row-sum correction, and the check clears regions where those differ within a class.
+static void make_class_table_lo(Level& L, hipStream_t st) {
+  L.class_table_lo.alloc(sizeof(float) * kClasses * kClassPts * L.ndof * L.ndof * L.nreg);
+  L.class_table_lo_ok.alloc(sizeof(int) * L.nreg);
+  float* tab = L.class_table_lo.as<float>();
+  int* ok = L.class_table_lo_ok.as<int>();
+  const float* centre = L.center_lo.as<float>();
+  if (L.ct_lo == kCoefBF16) {
+    const uint16_t* sym = L.coef_lo_sym.as<uint16_t>();
+    if (L.ndof == 3) class_table_launch<3, float, uint16_t>(L, sym, centre, tab, ok, st);
+    else class_table_launch<1, float, uint16_t>(L, sym, centre, tab, ok, st);
   } else {
-    clear_split(L);  // node blocks: each block of a served region reads the tables
+    const int64_t ne = (int64_t)kClasses * kClassPts * L.ndof * L.ndof * L.nreg;
+    launch_f64_to_f32(ne, L.class_table.as<double>(), tab, st);
+    RMG_HIP(hipMemcpyAsync(ok, L.class_table_ok.p, sizeof(int) * L.nreg, hipMemcpyDeviceToDevice, st));
   }
 }
 
@@ -2098,6 +2132,8 @@ static void make_sym_t(Level& L, bool lowp, int* flag, hipStream_t st) {
 bool launch_make_sym(Level& L, bool lowp, hipStream_t st, bool table) {
   DBuf& out = lowp ? L.coef_lo_sym : L.coef_sym;
   out.release();
+  L.class_table_lo.release();
+  L.class_table_lo_ok.release();
   if (!lowp) {
     L.class_table.release();
     L.class_table_ok.release();
@@ -2109,6 +2145,7 @@ bool launch_make_sym(Level& L, bool lowp, hipStream_t st, bool table) {
     if (!L.coef_sym.p || L.ct_lo == kCoefF64) return false;
     if (L.ndof == 3) make_sym_t<3>(L, true, nullptr, st);
     else make_sym_t<1>(L, true, nullptr, st);
+    if (L.class_table.p) make_class_table_lo(L, st);
     return true;
   }
   DBuf flag;

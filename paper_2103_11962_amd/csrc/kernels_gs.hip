@@ -176,7 +176,7 @@ struct Gs2d {
   static constexpr int NV = NLOW + 1;             // with D~^-1
   // steps stored per wavefront: the last lane's last node, and one more so that the next wavefront
   // finds a (zero) correction right of the row's end
-  __host__ __device__ static int steps(int ex) { return (ex + 63 * WY + 1 + 15) / 16 * 16; }
+  __host__ __device__ static int steps(int ex, int ey) { return (ex + WY * ((ey < 64 ? ey : 64) - 1) + 1 + 15) / 16 * 16; }
   // stencil offset index of visited neighbour v, in summation order
   __host__ __device__ static constexpr int low(int v, bool backward) {
     return backward ? center_index<NPTS>() + 1 + v : v;
@@ -212,7 +212,7 @@ __global__ __launch_bounds__(kBlock) void k_gs_fill2d(LevelView L, const int64_t
                                                       const double* __restrict__ dinv, double* __restrict__ out) {
   using G = Gs2d<NPTS>;
   const RegionGeo R = L.regs[blockIdx.y];
-  const int ts = G::steps(R.ex);
+  const int ts = G::steps(R.ex, R.ey);
   const int64_t recs = rec0[blockIdx.y + 1] - rec0[blockIdx.y];
   const int lane = threadIdx.x & 63;
   for (int64_t k = (int64_t)blockIdx.x * (kBlock / 64) + (threadIdx.x >> 6); k < recs;
@@ -244,7 +244,7 @@ __global__ __launch_bounds__(B == 16 ? 256 : (B == 8 ? 512 : 1024)) void k_gs_sw
   const int lane = threadIdx.x & 63;
   const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int nwb = (int)blockDim.x >> 6, nw = (R.ey + 63) / 64;
-  const int ts = G::steps(R.ex), nch = ts / B;
+  const int ts = G::steps(R.ex, R.ey), nch = ts / B;
   double* rows = lds + w * 64 * (B + 1);
   double* ring = lds + nwb * 64 * (B + 1);
   ring[w * kGsRing + lane] = 0.0;
@@ -341,12 +341,19 @@ __global__ __launch_bounds__(B == 16 ? 256 : (B == 8 ? 512 : 1024)) void k_gs_sw
   }
 }
 
-// The rows of every region fit sixteen wavefronts (one block); taller regions take k_gs_sweep.
+// The rows of every region fit sixteen wavefronts (one block; taller regions take k_gs_sweep), and
+// the records, whose lanes outside the region hold zeros, stay small: below 256 MiB, or at most
+// eight lanes a node (82 x 82: 3, 28 x 28: 8, 10 x 10: 20, so only a mesh of many tiny regions
+// keeps k_gs_sweep for its memory).
+template <int NPTS>
 static bool gs2d_ok(const Level& L) {
-  if (L.dim != 2 || L.ndof != 1) return false;
-  for (const RegionGeo& R : L.regs)
+  if (L.dim != 2 || L.ndof != 1 || L.nreg > 65535) return false;
+  int64_t lanes = 0;
+  for (const RegionGeo& R : L.regs) {
     if (R.ey > 1024) return false;
-  return true;
+    lanes += (int64_t)((R.ey + 63) / 64) * Gs2d<NPTS>::steps(R.ex, R.ey) * 64;
+  }
+  return lanes <= 8 * L.n || lanes * 2 * Gs2d<NPTS>::NV * (int64_t)sizeof(double) <= (int64_t)256 << 20;
 }
 
 template <int NPTS>
@@ -355,7 +362,7 @@ static void gs2d_prepare(Level& L, hipStream_t st) {
   std::vector<int64_t> rec0(L.nreg + 1, 0);
   int64_t most = 0;
   for (int k = 0; k < L.nreg; ++k) {
-    const int64_t n = (int64_t)((L.regs[k].ey + 63) / 64) * G::steps(L.regs[k].ex);
+    const int64_t n = (int64_t)((L.regs[k].ey + 63) / 64) * G::steps(L.regs[k].ex, L.regs[k].ey);
     rec0[k + 1] = rec0[k] + n;
     most = std::max(most, n);
   }
@@ -401,9 +408,12 @@ static void gs_fill_launch(const Level& L, hipStream_t st) {
 void launch_gs_prepare(Level& L, hipStream_t st) {
   RMG_REQUIRE(L.ndof == 1 || L.npts == 27, RMG_ERR_ARG, "internal: Gauss-Seidel blocks need 27-point levels");
   L.gs_records = 0;
-  if (gs2d_ok(L)) {
-    if (L.npts == 9) gs2d_prepare<9>(L, st);
-    else gs2d_prepare<5>(L, st);
+  if (L.npts == 9 && gs2d_ok<9>(L)) {
+    gs2d_prepare<9>(L, st);
+    return;
+  }
+  if (L.npts == 5 && gs2d_ok<5>(L)) {
+    gs2d_prepare<5>(L, st);
     return;
   }
   const int wy = L.npts == 5 ? 1 : 2;

@@ -152,18 +152,18 @@ __device__ __forceinline__ auto coefv(const C* __restrict__ cf, const float* __r
 // kSymPts blocks per node; the block of a lower offset s is the transpose of the neighbour's
 // upper block at offset 26 - s, read from the neighbour's record (consecutive lanes read
 // consecutive records, and the record was streamed moments before by a nearby block).
-// table (FP64 27-point symmetric levels, else null): the regions' class tables, used for the
+// table (27-point symmetric levels, else null): the regions' class tables, used for the
 // regions whose flag in table_ok is set: a node's 27 couplings (3 x 3 blocks on 3-dof levels) are
 // its class's (the values the half stencil applies, bit for bit), read from the small table
 // instead of from its own and its neighbours' records.
 template <int NPTS, int NDOF, class V, class C, StencilOp OP, bool DOT, bool SYM>
 __global__ __launch_bounds__(kBlock) void k_stencil(LevelView L, const C* __restrict__ coef,
                                                     const float* __restrict__ centre, OpP<V> p,
-                                                    double* __restrict__ partials, const double* __restrict__ table,
+                                                    double* __restrict__ partials, const V* __restrict__ table,
                                                     const int* __restrict__ table_ok) {
   constexpr int NB = NDOF * NDOF;
   constexpr int NCOEF = SYM ? kSymPts * NB : NPTS * NB;
-  constexpr bool kTab = NPTS == 27 && SYM && std::is_same<V, double>::value && std::is_same<C, double>::value;
+  constexpr bool kTab = NPTS == 27 && SYM;
   // every XCD runs a contiguous run of node blocks, so a block finds the records of the plane below
   // (its lower couplings on symmetric levels) in its own XCD's L2; its partial sum goes to the
   // node block's slot, as without the mapping
@@ -181,7 +181,7 @@ __global__ __launch_bounds__(kBlock) void k_stencil(LevelView L, const C* __rest
     const int sy = R.ex, sz = R.ex * R.ey;
     const bool inner = x > 0 && x < R.ex - 1 && y > 0 && y < R.ey - 1 && (NPTS != 27 || (z > 0 && z < R.ez - 1));
     const bool tabbed = kTab && table && table_ok[bd.region];  // uniform over the block (one region)
-    const double* __restrict__ tc =
+    const V* __restrict__ tc =
         tabbed ? table + ((int64_t)bd.region * kClasses +
                           (axis_class(z, R.ez) * 5 + axis_class(y, R.ey)) * 5 + axis_class(x, R.ex)) * kClassPts * NB
                : nullptr;
@@ -201,7 +201,7 @@ __global__ __launch_bounds__(kBlock) void k_stencil(LevelView L, const C* __rest
 #pragma unroll
             for (int a = 0; a < NDOF; ++a)
 #pragma unroll
-              for (int b = 0; b < NDOF; ++b) acc[a] += (V)tc[(s * NDOF + a) * NDOF + b] * xr[nb * NDOF + b];
+              for (int b = 0; b < NDOF; ++b) acc[a] += tc[(s * NDOF + a) * NDOF + b] * xr[nb * NDOF + b];
           } else if (s >= 13) {
 #pragma unroll
             for (int a = 0; a < NDOF; ++a)
@@ -483,27 +483,29 @@ __global__ __launch_bounds__(NT) void k_stencil3d(LevelView L, const Tile3* __re
 // loads are in flight while one is computed, and each plane read adds its products to the running
 // sums of the three nodes it neighbours in z.  The kernel is held to 80 VGPRs (six waves per SIMD,
 // three 8-wave blocks per CU), at the cost of one spilled register in the Chebyshev step; the
-// variant that also sums (b, u_out) keeps five waves, where it needs no spill.  Blocks
+// variant that also sums (b, u_out) keeps five waves, where it needs no spill.  FP32 vectors (the
+// low-precision cycle, with its own tables) fit eight waves: on 113M rows in 256 uneven regions a
+// Chebyshev step takes 546 us, 3.3 TB/s on its 16 B a row, where streaming 14 couplings a row took
+// 2081 us, and the FP64 CG product of that solve 575 instead of 3649 us.  Blocks
 // are mapped to tiles so that every XCD runs a contiguous run of tiles (xcd_item) and neighbouring
 // tiles share their halo rows through its L2.  Every node sums its 27 products in stencil order with
 // one rounding each, as k_stencil3d does, so the results are those of streaming every coupling bit
 // for bit.
-template <StencilOp OP, bool DOT>
-__global__ __launch_bounds__(kTableThreads) __attribute__((amdgpu_waves_per_eu(DOT ? 5 : 6))) void k_stencil_table(LevelView L, const Tile3* __restrict__ tiles,
-                                                                 const double* __restrict__ table, OpP<double> p,
-                                                                 double* __restrict__ partials) {
+template <class V, StencilOp OP, bool DOT>
+__global__ __launch_bounds__(kTableThreads) __attribute__((amdgpu_waves_per_eu(sizeof(V) == 4 ? 8 : (DOT ? 5 : 6)))) void k_stencil_table(
+    LevelView L, const Tile3* __restrict__ tiles, const V* __restrict__ table, OpP<V> p, double* __restrict__ partials) {
   constexpr int NT = kTableThreads;
   constexpr int kPlane = 2 * NT;  // a tile's rows with their halo: two loads per lane (make_split)
   constexpr int kFetch = 2;
   constexpr bool kPreB = OP == StencilOp::Residual || OP == StencilOp::ResidualScaled || OP == StencilOp::Cheb ||
                          OP == StencilOp::ChebFirst;
   constexpr bool kPreD = OP == StencilOp::Cheb;
-  constexpr int kXRows = 4 * kTableRows;  // x-face lanes: four a row
-  __shared__ double pl[2][kPlane];
-  __shared__ double xt[5][kClassPts][kXRows];  // the x-face lanes' couplings by z class
+  constexpr int kXCols = 20;  // classes of the x-face nodes in a plane: five y classes, four x classes
+  __shared__ V pl[2][kPlane];
+  __shared__ V xt[5][kClassPts][kXCols];  // the x-face lanes' couplings by z class
   const Tile3 T = tiles[xcd_item((int)blockIdx.x, (int)gridDim.x)];
   const RegionGeo R = L.regs[T.region];
-  const double* __restrict__ tab = table + (int64_t)T.region * kClasses * kClassPts;
+  const V* __restrict__ tab = table + (int64_t)T.region * kClasses * kClassPts;
   const int t = threadIdx.x;
   // lane -> (row, x): inner-x lanes, padded to a wavefront boundary, then x-face lanes
   const int dxw = R.ex - 4, ndl = T.ty * dxw, pad = (ndl + 63) & ~63;
@@ -523,11 +525,11 @@ __global__ __launch_bounds__(kTableThreads) __attribute__((amdgpu_waves_per_eu(D
   const int cxy = axis_class(y, R.ey) * 5 + axis_class(x, R.ex);
   const int W = R.ex + 2, PL = (T.ty + 2) * W;
   const int sy = R.ex, sz = R.ex * R.ey;
-  const double* __restrict__ xr = p.x + R.off;
+  const V* __restrict__ xr = p.x + R.off;
   // Loads are issued unconditionally (out-of-range positions read a valid element and are zeroed
   // when stored), so that the compiler counts the loads in flight exactly and waits only for the
   // plane it needs.
-  auto fetch = [&](int zz, double(&pre)[kFetch]) {
+  auto fetch = [&](int zz, V(&pre)[kFetch]) {
     const int zc = min(max(zz, 0), R.ez - 1);
 #pragma unroll
     for (int k = 0; k < kFetch; ++k) {
@@ -537,7 +539,7 @@ __global__ __launch_bounds__(kTableThreads) __attribute__((amdgpu_waves_per_eu(D
       pre[k] = xr[(int64_t)zc * sz + (int64_t)yy * sy + xx];
     }
   };
-  auto store = [&](int slot, int zz, const double(&pre)[kFetch]) {
+  auto store = [&](int slot, int zz, const V(&pre)[kFetch]) {
 #pragma unroll
     for (int k = 0; k < kFetch; ++k) {
       const int idx = t + k * NT;
@@ -545,42 +547,42 @@ __global__ __launch_bounds__(kTableThreads) __attribute__((amdgpu_waves_per_eu(D
         const int r = idx / W;
         const int xx = idx - r * W - 1, yy = T.y0 - 1 + r;
         const bool in = (unsigned)zz < (unsigned)R.ez && (unsigned)yy < (unsigned)R.ey && (unsigned)xx < (unsigned)R.ex;
-        pl[slot][idx] = in ? pre[k] : 0.0;
+        pl[slot][idx] = in ? pre[k] : (V)0;
       }
     }
   };
-  double v9[9];  // this lane's 3 x 3 neighbourhood on the plane read last
+  V v9[9];  // this lane's 3 x 3 neighbourhood on the plane read last
   auto readn = [&](int slot) {
 #pragma unroll
     for (int j = 0; j < 9; ++j) v9[j] = pl[slot][(row + j / 3) * W + x + j % 3];
   };
   const int z0 = T.z0, z1 = T.z0 + T.nz;
-  auto load_bd = [&](int z2, double& b2, double& d2) {  // inactive lanes and planes past the tile: a valid node
+  auto load_bd = [&](int z2, V& b2, V& d2) {  // inactive lanes and planes past the tile: a valid node
     const int64_t g = R.off + (int64_t)min(z2, z1 - 1) * sz + (int64_t)y * sy + x;
     if constexpr (kPreB) b2 = p.b[g];
     if constexpr (kPreD) d2 = p.out[g];  // u_(k-2), see finish_value
   };
-  for (int e = t; e < 5 * kClassPts * kXRows; e += NT) {  // couplings of the x-face lanes' classes
-    const int u = e % kXRows, s2 = e / kXRows % kClassPts, cz = e / (kXRows * kClassPts);
-    const int yu = min(T.y0 + (u >> 2), R.ey - 1), xu = (u & 3) < 2 ? (u & 3) : R.ex - 4 + (u & 3);
-    xt[cz][s2][u] = tab[((cz * 5 + axis_class(yu, R.ey)) * 5 + axis_class(xu, R.ex)) * kClassPts + s2];
+  for (int e = t; e < 5 * kClassPts * kXCols; e += NT) {  // couplings of the x-face classes
+    const int u = e % kXCols, s2 = e / kXCols % kClassPts, cz = e / (kXCols * kClassPts);
+    const int cx = (u & 3) < 2 ? (u & 3) : (u & 3) + 1;
+    xt[cz][s2][u] = tab[((cz * 5 + (u >> 2)) * 5 + cx) * kClassPts + s2];
   }
   // Running sums: once plane q has been added, a0 is node q - 1's sum, a1 node q's and a2 node
   // q + 1's.  A plane adds its nine values to the three nodes it neighbours in z (as their plane
   // z + 1, z and z - 1), so each node adds its 27 products in stencil order with one rounding each,
   // and only the plane read last is held in registers.
-  double a0 = 0.0, a1 = 0.0, a2 = 0.0, ctr = 0.0, xprev = 0.0;
+  V a0 = (V)0, a1 = (V)0, a2 = (V)0, ctr = (V)0, xprev = (V)0;
   auto czc = [&](int z) { return min(max(axis_class(z, R.ez), 0), 4); };
   auto add_plane = [&](int q) {
-    a2 = 0.0;
+    a2 = (V)0;
     if (t >= pad) {
-      // the x-face wavefront (four classes a row): each lane reads its class's couplings from
+      // the x-face wavefronts (four classes a row): each lane reads its class's couplings from
       // the block's copy in LDS, nine at a time (the empty asm keeps the chunks' reads apart)
-      const int u = t - pad;
-      auto chunk = [&](const double* __restrict__ xc, double& acc) {
-        double cf[9];
+      const int u = axis_class(y, R.ey) * 4 + ((t - pad) & 3);
+      auto chunk = [&](const V* __restrict__ xc, V& acc) {
+        V cf[9];
 #pragma unroll
-        for (int j = 0; j < 9; ++j) cf[j] = xc[j * kXRows];
+        for (int j = 0; j < 9; ++j) cf[j] = xc[j * kXCols];
 #pragma unroll
         for (int j = 0; j < 9; ++j) acc = fma(cf[j], v9[j], acc);
         __asm__ volatile("" ::: "memory");
@@ -603,9 +605,9 @@ __global__ __launch_bounds__(kTableThreads) __attribute__((amdgpu_waves_per_eu(D
         __asm__ volatile("" : "+s"(o0), "+s"(o1), "+s"(o2));
         const bool mine = cxy == c;
         if (mine) {
-          const double* __restrict__ t0 = tab + o0;
-          const double* __restrict__ t1 = tab + o1;
-          const double* __restrict__ t2 = tab + o2;
+          const V* __restrict__ t0 = tab + o0;
+          const V* __restrict__ t1 = tab + o1;
+          const V* __restrict__ t2 = tab + o2;
 #pragma unroll
           for (int j = 0; j < 9; ++j) a0 = fma(t0[18 + j], v9[j], a0);
 #pragma unroll
@@ -623,8 +625,8 @@ __global__ __launch_bounds__(kTableThreads) __attribute__((amdgpu_waves_per_eu(D
     a1 = a2;
     xprev = v9[4];
   };
-  double preA[kFetch], preB[kFetch];
-  double nbA = 0.0, ndA = 0.0, nbB = 0.0, ndB = 0.0;
+  V preA[kFetch], preB[kFetch];
+  V nbA = (V)0, ndA = (V)0, nbB = (V)0, ndB = (V)0;
   load_bd(z0, nbA, ndA);
   load_bd(z0 + 1, nbB, ndB);
   fetch(z0 - 1, preA);
@@ -650,21 +652,21 @@ __global__ __launch_bounds__(kTableThreads) __attribute__((amdgpu_waves_per_eu(D
   // one plane: plane zz + 1 from LDS completes node zz; plane zz + 2 goes to LDS from the
   // registers that fetched it two planes ago, which then fetch plane zz + 4 (past the tile's last
   // plane it only keeps the loads in step: see the loop below)
-  auto plane = [&](int zz, double(&pre)[kFetch], double& b2, double& d2) {
+  auto plane = [&](int zz, V(&pre)[kFetch], V& b2, V& d2) {
     const int sp = (zz - z0) & 1;  // slot holding plane zz + 1
     const bool work = active && zz < z1;
     if (work) readn(sp);
     if (zz + 2 <= z1) store(sp ^ 1, zz + 2, pre);  // plane zz + 2 replaces plane zz
     fetch(zz + 4, pre);
-    const double cb = b2, cd = d2;
+    const V cb = b2, cd = d2;
     load_bd(zz + 2, b2, d2);
     if (work) {
       add_plane(zz + 1);
       const int64_t gi = R.off + (int64_t)zz * sz + (int64_t)y * sy + x;
       const bool edge = x == 0 || x == R.ex - 1 || y == 0 || y == R.ey - 1 || zz == 0 || zz == R.ez - 1;
-      if (edge && is_shared(L, R, x, y, zz)) write_partial<OP, double>(p, gi, a0, xprev, cd);  // finished by k_iface
-      else if constexpr (kPreB) contrib += finish_pre<OP, DOT, double, true>(p, gi, a0, 1, xprev, ctr, cb, cd);
-      else contrib += finish<OP, DOT, double, true>(p, gi, a0, 1, xprev, ctr);
+      if (edge && is_shared(L, R, x, y, zz)) write_partial<OP, V>(p, gi, a0, xprev, cd);  // finished by k_iface
+      else if constexpr (kPreB) contrib += finish_pre<OP, DOT, V, true>(p, gi, a0, 1, xprev, ctr, cb, cd);
+      else contrib += finish<OP, DOT, V, true>(p, gi, a0, 1, xprev, ctr);
       shift();
     }
     __syncthreads();
@@ -754,7 +756,14 @@ static int64_t run(const Level& L, const StencilArgs& a, hipStream_t st) {
   const C* coef = a.lowp ? L.coef_lo.as<C>() : L.coef.as<C>();
   const float* centre = L.center_lo.as<float>();
   const LevelView v = L.view();
-  const bool tiled = NPTS == 27 && NDOF == 1 && L.use_tiles;
+  constexpr bool kSameType = std::is_same<V, C>::value;
+  // the regions' class tables in this arithmetic's type
+  const V* table = static_cast<const V*>(a.lowp ? L.class_table_lo.p : L.class_table.p);
+  const int* table_ok = a.lowp ? L.class_table_lo_ok.as<int>() : L.class_table_ok.as<int>();
+  // region-table split: the served regions' whole-row tiles, then the other regions' 2.5D tiles
+  const bool split = NPTS == 27 && NDOF == 1 && kSameType && L.use_split && table &&
+                     (L.use_tiles || L.other_tiles.empty()) && (OP != StencilOp::CgQ || L.split_dot);
+  const bool tiled = NPTS == 27 && NDOF == 1 && (L.use_tiles || split);
   const int ntiles = (int)L.tiles.size();
   const int grid3 = (L.tile_grid > 0 && L.tile_grid < ntiles) ? L.tile_grid : ntiles;
   int64_t nparts = grid3;  // partial sums written by the tiled launches
@@ -762,68 +771,54 @@ static int64_t run(const Level& L, const StencilArgs& a, hipStream_t st) {
   if constexpr (NPTS == 27 && NDOF == 1) {
     if (tiled) {
       const C* sym = nullptr;
-      const C* table = nullptr;
-      if constexpr (std::is_same<V, C>::value) {
-        sym = static_cast<const C*>(a.lowp ? L.coef_lo_sym.p : L.coef_sym.p);
-        // the class tables serve the FP64 operator on 768-thread tiles
-        if (!a.lowp && L.tile_threads == kTileThreadsF64 && L.class_table.p && L.class_table_ok.p)
-          table = static_cast<const C*>(L.class_table.p);
-      }
-      bool split = false;
-      if constexpr (std::is_same<V, double>::value && std::is_same<C, double>::value) {
-        if (table && sym && L.tile_threads == kTileThreadsF64 && !L.table_tiles.empty()) {
-          // region-table split: the served regions' whole-region tiles, then the other regions'
-          // tiles, each with its own run of partial sums
-          const int64_t nd = (int64_t)L.table_tiles.size(), no = (int64_t)L.other_tiles.size();
-          RMG_REQUIRE(L.table_served.size() == (size_t)L.nreg, RMG_ERR_ARG, "internal: class tables without their split");
-          RMG_LAUNCH((k_stencil_table<OP, DOT>), dim3(nd), dim3(kTableThreads), 0, st, v, L.d_table_tiles.as<Tile3>(),
-                     table, p, a.partials);
-          if (no > 0)
-            RMG_LAUNCH((k_stencil3d<kTileThreadsF64, V, C, OP, DOT, true>), dim3(no), dim3(kTileThreadsF64), 0, st,
-                       v, L.d_other_tiles.as<Tile3>(), (int)no, sym, centre, p,
-                       a.partials ? a.partials + nd : nullptr);
-          nparts = nd + no;
-          split = true;
-        }
-      }
-      auto launch3d = [&](auto nt) {
+      if constexpr (kSameType) sym = static_cast<const C*>(a.lowp ? L.coef_lo_sym.p : L.coef_sym.p);
+      // tiles by the streaming kernel: n of them at d, partial sums from part on
+      auto launch3d = [&](auto nt, int grid, const Tile3* d, int n, double* part) {
         constexpr int NT = decltype(nt)::value;
         if (sym) {
-          if constexpr (std::is_same<V, C>::value) {
-            RMG_LAUNCH((k_stencil3d<NT, V, C, OP, DOT, true>), dim3(grid3), dim3(NT), 0, st, v,
-                               L.d_tiles.as<Tile3>(), ntiles, sym, centre, p, a.partials);
+          if constexpr (kSameType) {
+            RMG_LAUNCH((k_stencil3d<NT, V, C, OP, DOT, true>), dim3(grid), dim3(NT), 0, st, v, d, n, sym, centre, p,
+                       part);
           }
         } else {
-          RMG_LAUNCH((k_stencil3d<NT, V, C, OP, DOT, false>), dim3(grid3), dim3(NT), 0, st, v,
-                             L.d_tiles.as<Tile3>(), ntiles, coef, centre, p, a.partials);
+          RMG_LAUNCH((k_stencil3d<NT, V, C, OP, DOT, false>), dim3(grid), dim3(NT), 0, st, v, d, n, coef, centre, p,
+                     part);
+        }
+      };
+      auto stream = [&](int grid, const Tile3* d, int n, double* part) {
+        if constexpr (sizeof(V) == 8) {
+          if (L.tile_threads == kTileThreadsF64) launch3d(std::integral_constant<int, kTileThreadsF64>(), grid, d, n, part);
+          else launch3d(std::integral_constant<int, kTileThreadsF32>(), grid, d, n, part);
+        } else {
+          RMG_REQUIRE(L.tile_threads == kTileThreadsF32, RMG_ERR_ARG, "internal: FP32 tiles must be narrow");
+          launch3d(std::integral_constant<int, kTileThreadsF32>(), grid, d, n, part);
         }
       };
       if (split) {
-      } else if constexpr (sizeof(V) == 8) {
-        if (L.tile_threads == kTileThreadsF64) launch3d(std::integral_constant<int, kTileThreadsF64>());
-        else launch3d(std::integral_constant<int, kTileThreadsF32>());
+        const int64_t nd = (int64_t)L.table_tiles.size(), no = (int64_t)L.other_tiles.size();
+        RMG_REQUIRE(L.table_served.size() == (size_t)L.nreg, RMG_ERR_ARG, "internal: class tables without their split");
+        if constexpr (kSameType)
+          RMG_LAUNCH((k_stencil_table<V, OP, DOT>), dim3(nd), dim3(kTableThreads), 0, st, v,
+                     L.d_table_tiles.as<Tile3>(), table, p, a.partials);
+        if (no > 0) stream((int)no, L.d_other_tiles.as<Tile3>(), (int)no, a.partials ? a.partials + nd : nullptr);
+        nparts = nd + no;
       } else {
-        RMG_REQUIRE(L.tile_threads == kTileThreadsF32, RMG_ERR_ARG, "internal: FP32 tiles must be narrow");
-        launch3d(std::integral_constant<int, kTileThreadsF32>());
+        stream(grid3, L.d_tiles.as<Tile3>(), ntiles, a.partials);
       }
     }
   }
   if (!tiled) {
     const C* symc = static_cast<const C*>(a.lowp ? L.coef_lo_sym.p : L.coef_sym.p);
-    // the class tables of an FP64 level run by node blocks
-    const bool ntab = !a.lowp && NPTS == 27 && L.class_table.p && L.class_table_ok.p;
-    const double* ntable = ntab ? L.class_table.as<double>() : nullptr;
-    const int* ntable_ok = ntab ? L.class_table_ok.as<int>() : nullptr;
     auto node = [&](const LevelView& vk, int nblocks, double* part) {
       if constexpr (NPTS == 27) {
         if (symc) {
           RMG_LAUNCH((k_stencil<NPTS, NDOF, V, C, OP, DOT, true>), dim3(nblocks), dim3(kBlock), 0, st, vk,
-                             symc, centre, p, part, ntable, ntable_ok);
+                             symc, centre, p, part, table, table_ok);
           return;
         }
       }
       RMG_LAUNCH((k_stencil<NPTS, NDOF, V, C, OP, DOT, false>), dim3(nblocks), dim3(kBlock), 0, st, vk, coef,
-                         centre, p, part, nullptr, nullptr);
+                         centre, p, part, (const V*)nullptr, (const int*)nullptr);
     };
     if (L.per_region) {
       // unbatched: one launch per region over its slice of the block table (partials keep their slots)

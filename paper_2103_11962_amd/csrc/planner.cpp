@@ -116,6 +116,7 @@ void make_tiles(Level& L, int depth) {
 }
 
 void clear_split(Level& L) {
+  L.use_split = false;
   L.table_served.clear();
   L.table_tiles.clear();
   L.other_tiles.clear();
@@ -127,25 +128,64 @@ void clear_split(Level& L) {
 // to whole wavefronts, then four x-face nodes per row.
 static int table_lanes(int ex, int ty) { return ((ty * (ex - 4) + 63) & ~63) + 4 * ty; }
 
-// Served regions (at least 5 nodes a side): whole-row tiles of ty rows, ty the most (at most
-// kTableRows) whose lanes fit kTableThreads and whose plane with its halo takes two loads per lane,
-// rows shared out evenly, and
-// at most kTablePlanes planes (planes shared out evenly), largest first.
+// Rows of a table tile of row length ex: as many as the block's lanes and two loads per lane for a
+// plane with its halo allow.
+static int table_rows(const RegionGeo& R) {
+  int ty = 0;
+  while (ty < R.ey && table_lanes(R.ex, ty + 1) <= kTableThreads && (R.ex + 2) * (ty + 3) <= 2 * kTableThreads) ++ty;
+  return ty;
+}
+
+// Planes per table tile.  A block marches its planes one after the other at about the same pace
+// whatever else runs, after a start-up of about kTableStart planes' time, and kTableSlots blocks run
+// at once: of all depths, the one that makes (rounds of blocks) x (planes + start-up) least; beyond
+// a few rounds the blocks' ends even out and the rounds are no longer whole.
+static int table_planes(const Level& L, const std::vector<int>& served) {
+  constexpr int kTableSlots = 768, kTableStart = 4;
+  if (L.deep_table) return kTablePlanes;
+  double best = 1e300;
+  int planes = kTablePlanes;
+  for (int p = kTablePlanes; p >= 4; --p) {
+    int64_t tiles = 0;
+    int deepest = 1;
+    for (int k = 0; k < L.nreg; ++k) {
+      if (!served[k]) continue;
+      const RegionGeo& R = L.regs[k];
+      const int ty = table_rows(R), nz = (R.ez + p - 1) / p;
+      tiles += (int64_t)((R.ey + ty - 1) / ty) * nz;
+      deepest = std::max(deepest, (R.ez + nz - 1) / nz);
+    }
+    const double r = (double)tiles / kTableSlots;
+    const double cost = (r < 4.0 ? std::ceil(r) : r) * (deepest + kTableStart);
+    if (cost < best) {
+      best = cost;
+      planes = p;
+    }
+  }
+  return planes;
+}
+
+bool split_fits(const Level& L, const std::vector<int>& served) {
+  for (int k = 0; k < L.nreg; ++k)
+    if (served[k] && table_rows(L.regs[k]) < 1) return false;
+  return true;
+}
+
+// Served regions (at least 5 nodes a side): whole-row tiles, rows and planes shared out evenly.
 void make_split(Level& L, const std::vector<int>& served) {
   std::vector<int> keep = served;
   clear_split(L);
   L.table_served = keep;
+  L.use_split = true;
+  const int planes = table_planes(L, keep);
   for (int k = 0; k < L.nreg; ++k) {
     if (!keep[k]) continue;
     const RegionGeo& R = L.regs[k];
     RMG_REQUIRE(R.ex >= 5 && R.ey >= 5 && R.ez >= 5, RMG_ERR_ARG, "internal: table region under 5 nodes a side");
-    int tymax = 0;
-    while (tymax < std::min(R.ey, kTableRows) && table_lanes(R.ex, tymax + 1) <= kTableThreads &&
-           (R.ex + 2) * (tymax + 3) <= 2 * kTableThreads)
-      ++tymax;
+    const int tymax = table_rows(R);
     RMG_REQUIRE(tymax >= 1, RMG_ERR_ARG, "internal: region row wider than a table tile");
     const int nty = (R.ey + tymax - 1) / tymax;
-    const int ntz = (R.ez + kTablePlanes - 1) / kTablePlanes;
+    const int ntz = (R.ez + planes - 1) / planes;
     for (int iz = 0, z0 = 0; iz < ntz; ++iz) {
       const int nz = R.ez / ntz + (iz < R.ez % ntz ? 1 : 0);
       for (int j = 0, y0 = 0; j < nty; ++j) {
@@ -158,7 +198,7 @@ void make_split(Level& L, const std::vector<int>& served) {
   }
   for (const Tile3& T : L.table_tiles) {
     const RegionGeo& R = L.regs[T.region];
-    RMG_REQUIRE(table_lanes(T.tx, T.ty) <= kTableThreads && T.ty <= kTableRows && (T.tx + 2) * (T.ty + 2) <= 2 * kTableThreads &&
+    RMG_REQUIRE(table_lanes(T.tx, T.ty) <= kTableThreads && (T.tx + 2) * (T.ty + 2) <= 2 * kTableThreads &&
                     T.x0 == 0 && T.tx == R.ex && T.y0 + T.ty <= R.ey && T.z0 + T.nz <= R.ez && T.nz >= 1,
                 RMG_ERR_ARG, "internal: table tile does not fit its block");
   }

@@ -142,6 +142,7 @@ static std::string tune_key(const Level& L, int level, int precision) {
 }
 
 static void apply_choice(Level& L, const TuneChoice& c) {
+  L.use_split = c.mode != 0 && !L.table_tiles.empty();
   if (c.mode == 0) {
     L.use_tiles = false;
     L.tile_grid = 0;
@@ -248,14 +249,18 @@ static void configure_level(rmg_handle* h, Level& L, bool with_b, bool sym) {
   L.center_lo.release();
   L.coef_lo_sym.release();
   if (sym) {
-    // class tables for the FP64 2.5D tiles and, on FP64 levels run by node blocks, for those blocks
-    const bool tables = o.region_table != 0 && fp64 && L.npts == 27 &&
-                        ((L.use_tiles && L.tile_threads == kTileThreadsF64) || (!L.use_tiles && !L.per_region));
+    // class tables for the 2.5D tiles and for the levels run by node blocks
+    const bool tables = o.region_table != 0 && L.npts == 27 && !L.per_region;
+    L.split_auto = o.stencil_kernel == 0;
+    L.split_dot = fp64 || L.split_auto;
+    L.deep_table = o.tile_planes != 0;
     launch_make_sym(L, false, h->stream, tables);
   } else {
     L.coef_sym.release();
     L.class_table.release();
     L.class_table_ok.release();
+    L.class_table_lo.release();
+    L.class_table_lo_ok.release();
     clear_split(L);
   }
 }
@@ -265,8 +270,8 @@ void prepare_finest(rmg_handle* h) {
   for (size_t i = 1; i < h->levels.size(); ++i) delete h->levels[i];
   h->levels.resize(1);
   h->tune_report.clear();
-  h->partials.alloc(sizeof(double) * partial_capacity(*L0));
   configure_level(h, *L0, false, h->opt.symmetric != 0);
+  h->partials.alloc(sizeof(double) * partial_capacity(*L0));
   L0->pw.release();
   L0->rw.release();
   RMG_HIP(hipStreamSynchronize(h->stream));
@@ -283,13 +288,13 @@ static int build_levels(rmg_handle* h, bool stored) {
   h->levels.resize(1);
   const bool lowp = o.precision != RMG_PREC_FP64;
   h->tune_report.clear();
-  h->partials.alloc(sizeof(double) * partial_capacity(*L0));
   int pflags = 0;
   DBuf flag;
   flag.alloc(sizeof(int));
   for (int l = 0; l < o.nlevels; ++l) {
     Level& L = *h->levels[l];
     configure_level(h, L, l > 0, o.symmetric && l < o.nlevels - 1);  // (the coarsest is solved directly)
+    if (l == 0) h->partials.alloc(sizeof(double) * partial_capacity(L));
     if (lowp) alloc_vectors_lowp(L, true);  // level 0's b32 holds the FP32 copy of the CG residual
     if (l == o.nlevels - 1) {
       if (o.coarse_amg) amg_setup(h, L);  // Section 3.5: an AMG V-cycle instead of the direct solver
