@@ -159,8 +159,10 @@ typedef struct {
                          region's couplings come from its 125 x 27 class table (whole-row tiles on
                          scalar levels of 2.5D tiles or at least 150,000 nodes, each node's class row
                          on node blocks; the low-precision V-cycle has a table of its own values) instead of being
-                         streamed from memory.  Results are bit for bit those of 0, which always
-                         streams them */
+                         streamed from memory.  The regions of an RMG_PDE_DIFFUSION finest level
+                         that no table serves assemble their couplings on the fly in FP64 (levels
+                         of 2.5D tiles or at least 150,000 nodes).  Results are bit for bit those
+                         of 0, which always streams the couplings */
   int tile_planes;    /* planes per 2.5D tile: 0 (default) chooses (41 on FP64 levels that keep at
                          least 1024 such tiles, else 21); 21 or 41 forces that depth on every
                          tiled level, so that a problem small enough for the oracle runs the launch

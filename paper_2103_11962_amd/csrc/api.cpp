@@ -259,6 +259,7 @@ static void begin_operator_change(rmg_handle* h, Level& L) {
   L.class_table_ok.release();
   L.class_table_lo.release();
   L.class_table_lo_ok.release();
+  L.elem.release();
   clear_split(L);
 }
 
@@ -459,6 +460,12 @@ rmg_status rmg_assemble_q1(rmg_handle* h, int pde, double hsize, const double* e
     double K[64];
     q1_laplace_element(hsize, K);
     launch_assemble_q1_scalar(L, K, pde == RMG_PDE_DIFFUSION ? elem_coef : nullptr, h->stream);
+    if (pde == RMG_PDE_DIFFUSION) {  // kept for the kernels that assemble couplings on the fly
+      const size_t bytes = sizeof(double) * (size_t)(L.comp[0] - 1) * (L.comp[1] - 1) * (L.comp[2] - 1);
+      L.elem.alloc(bytes);
+      RMG_HIP(hipMemcpyAsync(L.elem.p, elem_coef, bytes, hipMemcpyDeviceToDevice, h->stream));
+      std::copy(K, K + 64, L.elem_k.k);
+    }
   }
   // features of the learned interpolation: log of the element coefficients
   if (pde == RMG_PDE_DIFFUSION) {

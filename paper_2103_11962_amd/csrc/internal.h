@@ -126,6 +126,11 @@ __host__ __device__ __forceinline__ int64_t coef_index(int64_t gi, int s, int np
 inline size_t coef_elems(int64_t n, int npts) { return (size_t)((n + kTile - 1) / kTile) * kTile * npts; }
 constexpr int kSymPts = 14;  // upper half of a symmetric 27-point stencil: offsets 13..26
 
+// Element matrix of the scalar Q1 operator, passed by value.
+struct Kmat {
+  double k[64];
+};
+
 // Everything a kernel needs to know about a level, passed by value.
 struct LevelView {
   const RegionGeo* regs;
@@ -213,6 +218,13 @@ struct Level {
   std::vector<Tile3> table_tiles;    // whole-row tiles of the served regions (k_stencil_table)
   std::vector<Tile3> other_tiles;    // the level's 2.5D tiles of the regions not served
   DBuf d_table_tiles, d_other_tiles;
+  // Finest level assembled from element-wise diffusion coefficients: the coefficients (composite
+  // element grid) and the element matrix.  In FP64 the regions that the tables do not serve then run
+  // elem_tiles (k_stencil_elem), which assemble each node's couplings from its eight elements.
+  DBuf elem;
+  Kmat elem_k;
+  std::vector<Tile3> elem_tiles;
+  DBuf d_elem_tiles;
   // Transfers to the next level by rows and planes (make_transfer_tiles; empty: one thread per
   // node).  Restriction tiles hold coarse rows y0 .. y0+ty-1 and planes z0 .. z0+nz-1 of a region
   // (tx = the coarse row length), prolongation tiles fine rows and planes; rtile_vals is the most
@@ -342,7 +354,10 @@ void build_tables(Level& L);
 void make_tiles(Level& L, int depth);
 // Region-table split of a level whose table flags are `served` (per region): whole-row tiles of the
 // served regions and the remaining regions' tiles (also rebuilt by make_tiles while a split exists).
-void make_split(Level& L, const std::vector<int>& served);
+// elem: the others run tiles of k_stencil_elem in FP64.
+void make_split(Level& L, const std::vector<int>& served, bool elem);
+// Whether the rows of every region not served fit an element tile.
+bool elem_fits(const Level& L, const std::vector<int>& served);
 // Whether every served region's rows fit a table tile.
 bool split_fits(const Level& L, const std::vector<int>& served);
 // Row-and-plane tiles of the transfers between F and the next level C (F.rtiles, F.ptiles), or

@@ -1562,10 +1562,6 @@ void launch_check_inverse(const double* A, int n, int* flag, hipStream_t st) {
 }
 
 // --------------------------------------------------------- Q1 assembly
-struct Kmat {
-  double k[64];
-};
-
 // One thread per node: sums the element matrices of the (up to 8) elements of its region
 // that contain it; Dirichlet rows become identity rows and couplings to Dirichlet nodes are
 // removed (symmetric elimination).  Element e's coefficient is elem_coef[e] or 1.
@@ -2081,11 +2077,15 @@ static void make_class_table(Level& L, hipStream_t st) {
   if (served == 0) {  // no region served: drop the tables, so the streaming kernel runs
     tab.release();
     ok.release();
-  } else if (L.ndof == 1 && L.use_tiles) {
-    make_split(L, flags);
-  } else if (L.ndof == 1 && L.split_auto && served == L.nreg && L.n >= kTableMinNodes && split_fits(L, flags)) {
-    make_split(L, flags);
-    if (L.table_tiles.size() > L.blocks.size()) clear_split(L);  // (the partial sums' space)
+  }
+  if (L.ndof != 1) return;
+  // regions that the tables do not serve: assembled on the fly where the level has its elements
+  const bool elem = L.elem.p && served < L.nreg && elem_fits(L, flags);
+  if (served == 0 && !elem) return;
+  if (L.use_tiles) {
+    make_split(L, flags, elem);
+  } else if (L.split_auto && (served == L.nreg || elem) && L.n >= kTableMinNodes && split_fits(L, flags)) {
+    make_split(L, flags, elem);
   }  // else node blocks: each block of a served region reads the tables
 }
 

@@ -691,6 +691,212 @@ __global__ __launch_bounds__(kTableThreads) __attribute__((amdgpu_waves_per_eu(s
   }
 }
 
+// ------------------------------------------------------- element tiles
+
+// Whole-row tiles of regions of the finest level whose operator was assembled from element-wise
+// diffusion coefficients (FP64).  A node's 27 couplings are sums over its eight elements of element
+// matrix entry times coefficient: they are assembled in registers, in the order and with the roundings
+// of k_assemble_q1, from one coefficient an element (8 B a node) instead of being streamed (112 B a
+// node); a mirrored coupling is the same sum seen from the neighbour, element for element (the element
+// matrix is symmetric bit for bit), so every coupling is the one k_stencil3d reads, bit for bit.  On 64
+// regions of 82^3 a Chebyshev step takes 430 us, 3.3 TB/s on its 40 B a row, where k_stencil3d takes
+// 1170 us.  What bounds it now is the 91 FMAs a node and their uniform operands: with the element
+// matrix's 64 entries read again for every plane by scalar loads a step took 540 us, with the 36
+// entries on and above the diagonal, which nearly fit the scalar registers, 430.  The layout follows
+// k_stencil_table: node planes and element layers pass through two LDS slots each, fetched four ahead,
+// and each plane adds its products to the running sums of the three nodes it neighbours in z.
+// Elements outside the region count 0.  Couplings to Dirichlet nodes are dropped by taking those nodes'
+// values as 0; a Dirichlet row is its stored centre coupling times its own value.
+template <StencilOp OP, bool DOT>
+__global__ __launch_bounds__(kTableThreads) __attribute__((amdgpu_waves_per_eu(4))) void k_stencil_elem(
+    LevelView L, const Tile3* __restrict__ tiles, const double* __restrict__ elem, Kmat K,
+    const double* __restrict__ sym, OpP<double> p, double* __restrict__ partials) {
+  constexpr int NT = kTableThreads;
+  constexpr int kPlane = 2 * NT;  // a tile's nodes with their halo, and its elements: two loads per lane
+  constexpr bool kPreB = OP == StencilOp::Residual || OP == StencilOp::ResidualScaled || OP == StencilOp::Cheb ||
+                         OP == StencilOp::ChebFirst;
+  constexpr bool kPreD = OP == StencilOp::Cheb;
+  __shared__ double pl[2][kPlane], el[2][kPlane];
+  const Tile3 T = tiles[xcd_item((int)blockIdx.x, (int)gridDim.x)];
+  const RegionGeo R = L.regs[T.region];
+  const int t = threadIdx.x;
+  const int row = t / T.tx, x = t - row * T.tx, y = T.y0 + row;
+  const bool active = row < T.ty;
+  const int W = R.ex + 2, PL = (T.ty + 2) * W, WE = R.ex + 1, PE = (T.ty + 1) * WE;
+  const int sy = R.ex, sz = R.ex * R.ey;
+  const double* __restrict__ xr = p.x + R.off;
+  const int64_t esy = L.cx - 1, esz = (int64_t)(L.cx - 1) * (L.cy - 1);
+  const double* __restrict__ er = elem + R.oz * esz + R.oy * esy + R.ox;
+  // this lane's two node and two element positions of a plane: offset of a valid one, and whether it counts
+  int noff[2], eoff[2];
+  bool nin[2], ein[2];
+#pragma unroll
+  for (int k = 0; k < 2; ++k) {
+    int idx = min(t + k * NT, PL - 1), r = idx / W;
+    int xx = idx - r * W - 1, yy = T.y0 - 1 + r;
+    nin[k] = (unsigned)yy < (unsigned)R.ey && (unsigned)xx < (unsigned)R.ex;
+    if (nin[k])  // Dirichlet nodes on the x and y faces
+      nin[k] = !(((L.mask & 1u) && R.ox + xx == 0) || ((L.mask & 2u) && R.ox + xx == L.cx - 1) ||
+                 ((L.mask & 4u) && R.oy + yy == 0) || ((L.mask & 8u) && R.oy + yy == L.cy - 1));
+    noff[k] = min(max(yy, 0), R.ey - 1) * sy + min(max(xx, 0), R.ex - 1);
+    idx = min(t + k * NT, PE - 1), r = idx / WE;
+    xx = idx - r * WE - 1, yy = T.y0 - 1 + r;
+    ein[k] = (unsigned)yy < (unsigned)(R.ey - 1) && (unsigned)xx < (unsigned)(R.ex - 1);
+    eoff[k] = min(max(yy, 0), R.ey - 2) * (int)esy + min(max(xx, 0), R.ex - 2);
+  }
+  auto fetch = [&](int zz, double(&pre)[4]) {  // nodes of plane zz, elements between planes zz and zz + 1
+    const double* __restrict__ xz = xr + (int64_t)min(max(zz, 0), R.ez - 1) * sz;
+    const double* __restrict__ ez = er + (int64_t)min(max(zz, 0), R.ez - 2) * esz;
+#pragma unroll
+    for (int k = 0; k < 2; ++k) {
+      pre[k] = xz[noff[k]];
+      pre[2 + k] = ez[eoff[k]];
+    }
+  };
+  auto store = [&](int slot, int zz, const double(&pre)[4]) {
+    const int gz = R.oz + zz;
+    const bool zn = (unsigned)zz < (unsigned)R.ez && !(((L.mask & 16u) && gz == 0) || ((L.mask & 32u) && gz == L.cz - 1));
+    const bool ze = (unsigned)zz < (unsigned)(R.ez - 1);
+#pragma unroll
+    for (int k = 0; k < 2; ++k) {
+      const int idx = t + k * NT;
+      if (idx < PL) pl[slot][idx] = nin[k] && zn ? pre[k] : 0.0;
+      if (idx < PE) el[slot][idx] = ein[k] && ze ? pre[2 + k] : 0.0;
+    }
+  };
+  double v9[9], cm[4], cp[4];  // plane q's 3 x 3 nodes; elements (x - ax, y - ay) below and above it, ax + 2 ay
+  auto readn = [&](int slot) {
+#pragma unroll
+    for (int j = 0; j < 9; ++j) v9[j] = pl[slot][(row + j / 3) * W + x + j % 3];
+#pragma unroll
+    for (int a = 0; a < 4; ++a) {
+      cm[a] = cp[a];
+      cp[a] = el[slot][(row + 1 - (a >> 1)) * WE + x + 1 - (a & 1)];
+    }
+  };
+  const int z0 = T.z0, z1 = T.z0 + T.nz;
+  auto load_bd = [&](int z2, double& b2, double& d2) {  // inactive lanes and planes past the tile: a valid node
+    const int64_t g = R.off + (int64_t)min(z2, z1 - 1) * sz + (int64_t)(active ? y * sy + x : 0);
+    if constexpr (kPreB) b2 = p.b[g];
+    if constexpr (kPreD) d2 = p.out[g];  // u_(k-2), see finish_value
+  };
+  // running sums as in k_stencil_table: once plane q has been added, a0 is node q - 1's sum, a1 node
+  // q's, a2 node q + 1's; c0 and c1 the centre couplings of nodes q - 1 and q
+  double a0 = 0.0, a1 = 0.0, a2 = 0.0, c0 = 0.0, c1 = 0.0, xprev = 0.0;
+  double w[9];
+  // the element matrix is symmetric bit for bit: its 36 entries on and above the diagonal
+  auto ks = [&](int a, int b) { return K.k[min(a, b) * 8 + max(a, b)]; };
+  // w[j] += sum over corner roles a of the node (its element c[a & 3]) and b of the neighbour, both
+  // four corners of a z layer: the couplings of one stencil plane
+  auto couple = [&](const double(&c)[4], int a0c, int b0c) {
+#pragma unroll
+    for (int a = 0; a < 4; ++a)
+#pragma unroll
+      for (int b = 0; b < 4; ++b) {
+        const int j = ((b >> 1) - (a >> 1) + 1) * 3 + (b & 1) - (a & 1) + 1;
+        w[j] = fma(ks(a0c + a, b0c + b), c[a], w[j]);
+      }
+  };
+  auto clear = [&]() {
+#pragma unroll
+    for (int j = 0; j < 9; ++j) w[j] = 0.0;
+  };
+  auto add_plane = [&]() {
+    clear();
+    couple(cm, 0, 4);  // node q - 1 (bottom corners), plane above it
+#pragma unroll
+    for (int j = 0; j < 9; ++j) a0 = fma(w[j], v9[j], a0);
+    clear();
+    couple(cp, 0, 0);  // node q: its elements above, then below
+    couple(cm, 4, 4);
+    c1 = w[4];
+#pragma unroll
+    for (int j = 0; j < 9; ++j) a1 = fma(w[j], v9[j], a1);
+    clear();
+    couple(cp, 4, 0);  // node q + 1 (top corners), plane below it
+    a2 = 0.0;
+#pragma unroll
+    for (int j = 0; j < 9; ++j) a2 = fma(w[j], v9[j], a2);
+  };
+  auto shift = [&]() {
+    a0 = a1;
+    a1 = a2;
+    c0 = c1;
+    xprev = v9[4];
+  };
+  double preA[4], preB[4];
+  double nbA = 0.0, ndA = 0.0, nbB = 0.0, ndB = 0.0;
+  load_bd(z0, nbA, ndA);
+  load_bd(z0 + 1, nbB, ndB);
+  fetch(z0 - 1, preA);
+  fetch(z0, preB);
+  store(0, z0 - 1, preA);
+  store(1, z0, preB);
+#pragma unroll
+  for (int a = 0; a < 4; ++a) cp[a] = 0.0;
+  __syncthreads();
+  if (active) {  // planes z0 - 1 and z0: the first two thirds of node z0, the first of z0 + 1
+    readn(0);
+    add_plane();
+    shift();
+    readn(1);
+    add_plane();
+    shift();
+  }
+  __syncthreads();
+  fetch(z0 + 1, preA);
+  store(0, z0 + 1, preA);
+  fetch(z0 + 2, preA);
+  fetch(z0 + 3, preB);
+  __syncthreads();
+  double contrib = 0.0;
+  const bool dxy = active && (((L.mask & 1u) && R.ox + x == 0) || ((L.mask & 2u) && R.ox + x == L.cx - 1) ||
+                              ((L.mask & 4u) && R.oy + y == 0) || ((L.mask & 8u) && R.oy + y == L.cy - 1));
+  auto plane = [&](int zz, double(&pre)[4], double& b2, double& d2) {
+    const int sp = (zz - z0) & 1;  // slot holding plane zz + 1
+    const bool work = active && zz < z1;
+    if (work) readn(sp);
+    if (zz + 2 <= z1) store(sp ^ 1, zz + 2, pre);  // plane zz + 2 replaces plane zz
+    fetch(zz + 4, pre);
+    const double cb = b2, cd = d2;
+    load_bd(zz + 2, b2, d2);
+    if (work) {
+      add_plane();
+      const int64_t gi = R.off + (int64_t)zz * sz + (int64_t)y * sy + x;
+      const int gz = R.oz + zz;
+      double acc = a0, ctr = c0, xs = xprev;
+      if (dxy || ((L.mask & 16u) && gz == 0) || ((L.mask & 32u) && gz == L.cz - 1)) {  // a Dirichlet row
+        xs = p.x[gi];
+        ctr = sym[coef_index(gi, 0, kSymPts)];
+        acc = ctr * xs;
+      }
+      const bool edge = x == 0 || x == R.ex - 1 || y == 0 || y == R.ey - 1 || zz == 0 || zz == R.ez - 1;
+      if (edge && is_shared(L, R, x, y, zz)) write_partial<OP, double>(p, gi, acc, xs, cd);  // finished by k_iface
+      else if constexpr (kPreB) contrib += finish_pre<OP, DOT, double, true>(p, gi, acc, 1, xs, ctr, cb, cd);
+      else contrib += finish<OP, DOT, double, true>(p, gi, acc, 1, xs, ctr);
+      shift();
+    }
+    __syncthreads();
+  };
+  // both halves run on every pass, see k_stencil_table
+  for (int zz = z0; zz < z1; zz += 2) {
+    plane(zz, preA, nbA, ndA);
+    plane(zz + 1, preB, nbB, ndB);
+  }
+  if constexpr (DOT || OP == StencilOp::CgQ) {
+    double v = contrib;
+    for (int o = 32; o > 0; o >>= 1) v += __shfl_down(v, o, 64);
+    __shared__ double sm[NT / 64];
+    if ((t & 63) == 0) sm[t >> 6] = v;
+    __syncthreads();
+    if (t == 0) {
+      double s = 0.0;
+      for (int i = 0; i < NT / 64; ++i) s += sm[i];
+      partials[blockIdx.x] = s;
+    }
+  }
+}
+
 // ----------------------------------------------------------- interface groups
 // ng2: the first ng2 groups have two copies each (their copies start at 2 g, no gptr read).
 template <int NDOF, class V, StencilOp OP, bool DOT>
@@ -760,9 +966,11 @@ static int64_t run(const Level& L, const StencilArgs& a, hipStream_t st) {
   // the regions' class tables in this arithmetic's type
   const V* table = static_cast<const V*>(a.lowp ? L.class_table_lo.p : L.class_table.p);
   const int* table_ok = a.lowp ? L.class_table_lo_ok.as<int>() : L.class_table_ok.as<int>();
-  // region-table split: the served regions' whole-row tiles, then the other regions' 2.5D tiles
-  const bool split = NPTS == 27 && NDOF == 1 && kSameType && L.use_split && table &&
-                     (L.use_tiles || L.other_tiles.empty()) && (OP != StencilOp::CgQ || L.split_dot);
+  // region-table split: the served regions' whole-row tiles, then the other regions' element tiles or
+  // 2.5D tiles
+  const bool elem = NPTS == 27 && NDOF == 1 && std::is_same<V, double>::value && kSameType && !L.elem_tiles.empty();
+  const bool split = NPTS == 27 && NDOF == 1 && kSameType && L.use_split && (table || elem) &&
+                     (L.use_tiles || elem || L.other_tiles.empty()) && (OP != StencilOp::CgQ || L.split_dot);
   const bool tiled = NPTS == 27 && NDOF == 1 && (L.use_tiles || split);
   const int ntiles = (int)L.tiles.size();
   const int grid3 = (L.tile_grid > 0 && L.tile_grid < ntiles) ? L.tile_grid : ntiles;
@@ -795,12 +1003,19 @@ static int64_t run(const Level& L, const StencilArgs& a, hipStream_t st) {
         }
       };
       if (split) {
-        const int64_t nd = (int64_t)L.table_tiles.size(), no = (int64_t)L.other_tiles.size();
+        const int64_t nd = (int64_t)L.table_tiles.size(), no = (int64_t)(elem ? L.elem_tiles : L.other_tiles).size();
         RMG_REQUIRE(L.table_served.size() == (size_t)L.nreg, RMG_ERR_ARG, "internal: class tables without their split");
-        if constexpr (kSameType)
-          RMG_LAUNCH((k_stencil_table<V, OP, DOT>), dim3(nd), dim3(kTableThreads), 0, st, v,
-                     L.d_table_tiles.as<Tile3>(), table, p, a.partials);
-        if (no > 0) stream((int)no, L.d_other_tiles.as<Tile3>(), (int)no, a.partials ? a.partials + nd : nullptr);
+        if constexpr (kSameType) {
+          if (nd > 0)
+            RMG_LAUNCH((k_stencil_table<V, OP, DOT>), dim3(nd), dim3(kTableThreads), 0, st, v,
+                       L.d_table_tiles.as<Tile3>(), table, p, a.partials);
+        }
+        if constexpr (kSameType && std::is_same<V, double>::value) {
+          if (elem)
+            RMG_LAUNCH((k_stencil_elem<OP, DOT>), dim3(no), dim3(kTableThreads), 0, st, v, L.d_elem_tiles.as<Tile3>(),
+                       L.elem.as<double>(), L.elem_k, sym, p, a.partials ? a.partials + nd : nullptr);
+        }
+        if (!elem && no > 0) stream((int)no, L.d_other_tiles.as<Tile3>(), (int)no, a.partials ? a.partials + nd : nullptr);
         nparts = nd + no;
       } else {
         stream(grid3, L.d_tiles.as<Tile3>(), ntiles, a.partials);

@@ -122,6 +122,8 @@ void clear_split(Level& L) {
   L.other_tiles.clear();
   L.d_table_tiles.release();
   L.d_other_tiles.release();
+  L.elem_tiles.clear();
+  L.d_elem_tiles.release();
 }
 
 // Lanes of a table tile of ty rows of extent ex: the rows' inner x-nodes (x in [2, ex - 2)) padded
@@ -136,12 +138,21 @@ static int table_rows(const RegionGeo& R) {
   return ty;
 }
 
-// Planes per table tile.  A block marches its planes one after the other at about the same pace
-// whatever else runs, after a start-up of about kTableStart planes' time, and kTableSlots blocks run
-// at once: of all depths, the one that makes (rounds of blocks) x (planes + start-up) least; beyond
-// a few rounds the blocks' ends even out and the rounds are no longer whole.
-static int table_planes(const Level& L, const std::vector<int>& served) {
-  constexpr int kTableSlots = 768, kTableStart = 4;
+// Rows of an element tile: one lane a node, two loads per lane for a plane of nodes with its halo and
+// for a layer of elements.
+static int elem_rows(const RegionGeo& R) {
+  int ty = 0;
+  while (ty < R.ey && R.ex * (ty + 1) <= kTableThreads && (R.ex + 2) * (ty + 3) <= 2 * kTableThreads) ++ty;
+  return ty;
+}
+
+// Planes per tile of the regions k with in(k), rows(R) rows a tile.  A block marches its planes one
+// after the other at about the same pace whatever else runs, after a start-up of about kStart planes'
+// time, and `slots` blocks run at once: of all depths, the one that makes (rounds of blocks) x (planes +
+// start-up) least; beyond a few rounds the blocks' ends even out and the rounds are no longer whole.
+template <class In, class Rows>
+static int march_planes(const Level& L, int slots, In in, Rows rows) {
+  constexpr int kStart = 4;
   if (L.deep_table) return kTablePlanes;
   double best = 1e300;
   int planes = kTablePlanes;
@@ -149,14 +160,14 @@ static int table_planes(const Level& L, const std::vector<int>& served) {
     int64_t tiles = 0;
     int deepest = 1;
     for (int k = 0; k < L.nreg; ++k) {
-      if (!served[k]) continue;
+      if (!in(k)) continue;
       const RegionGeo& R = L.regs[k];
-      const int ty = table_rows(R), nz = (R.ez + p - 1) / p;
+      const int ty = rows(R), nz = (R.ez + p - 1) / p;
       tiles += (int64_t)((R.ey + ty - 1) / ty) * nz;
       deepest = std::max(deepest, (R.ez + nz - 1) / nz);
     }
-    const double r = (double)tiles / kTableSlots;
-    const double cost = (r < 4.0 ? std::ceil(r) : r) * (deepest + kTableStart);
+    const double r = (double)tiles / slots;
+    const double cost = (r < 4.0 ? std::ceil(r) : r) * (deepest + kStart);
     if (cost < best) {
       best = cost;
       planes = p;
@@ -165,36 +176,59 @@ static int table_planes(const Level& L, const std::vector<int>& served) {
   return planes;
 }
 
+bool elem_fits(const Level& L, const std::vector<int>& served) {
+  for (int k = 0; k < L.nreg; ++k)
+    if (!served[k] && elem_rows(L.regs[k]) < 1) return false;
+  return true;
+}
+
 bool split_fits(const Level& L, const std::vector<int>& served) {
   for (int k = 0; k < L.nreg; ++k)
     if (served[k] && table_rows(L.regs[k]) < 1) return false;
   return true;
 }
 
-// Served regions (at least 5 nodes a side): whole-row tiles, rows and planes shared out evenly.
-void make_split(Level& L, const std::vector<int>& served) {
+// Whole-row tiles of region k, at most ty rows and `planes` planes, both shared out evenly.
+static void add_tiles(const RegionGeo& R, int k, int tymax, int planes, std::vector<Tile3>& out) {
+  const int nty = (R.ey + tymax - 1) / tymax;
+  const int ntz = (R.ez + planes - 1) / planes;
+  for (int iz = 0, z0 = 0; iz < ntz; ++iz) {
+    const int nz = R.ez / ntz + (iz < R.ez % ntz ? 1 : 0);
+    for (int j = 0, y0 = 0; j < nty; ++j) {
+      const int ty = R.ey / nty + (j < R.ey % nty ? 1 : 0);
+      out.push_back(Tile3{k, 0, y0, z0, R.ex, ty, nz, 0});
+      y0 += ty;
+    }
+    z0 += nz;
+  }
+}
+
+// Served regions (at least 5 nodes a side) run table tiles (three blocks a CU); the others, with elem,
+// element tiles (two).
+void make_split(Level& L, const std::vector<int>& served, bool elem) {
   std::vector<int> keep = served;
   clear_split(L);
   L.table_served = keep;
   L.use_split = true;
-  const int planes = table_planes(L, keep);
+  auto is_served = [&](int k) { return keep[k] != 0; };
+  auto is_other = [&](int k) { return keep[k] == 0; };
+  const int planes = march_planes(L, 768, is_served, table_rows);
   for (int k = 0; k < L.nreg; ++k) {
     if (!keep[k]) continue;
     const RegionGeo& R = L.regs[k];
     RMG_REQUIRE(R.ex >= 5 && R.ey >= 5 && R.ez >= 5, RMG_ERR_ARG, "internal: table region under 5 nodes a side");
     const int tymax = table_rows(R);
     RMG_REQUIRE(tymax >= 1, RMG_ERR_ARG, "internal: region row wider than a table tile");
-    const int nty = (R.ey + tymax - 1) / tymax;
-    const int ntz = (R.ez + planes - 1) / planes;
-    for (int iz = 0, z0 = 0; iz < ntz; ++iz) {
-      const int nz = R.ez / ntz + (iz < R.ez % ntz ? 1 : 0);
-      for (int j = 0, y0 = 0; j < nty; ++j) {
-        const int ty = R.ey / nty + (j < R.ey % nty ? 1 : 0);
-        L.table_tiles.push_back(Tile3{k, 0, y0, z0, R.ex, ty, nz, 0});
-        y0 += ty;
-      }
-      z0 += nz;
-    }
+    add_tiles(R, k, tymax, planes, L.table_tiles);
+  }
+  if (elem) {
+    const int eplanes = march_planes(L, 512, is_other, elem_rows);
+    for (int k = 0; k < L.nreg; ++k)
+      if (!keep[k]) add_tiles(L.regs[k], k, elem_rows(L.regs[k]), eplanes, L.elem_tiles);
+    for (const Tile3& T : L.elem_tiles)
+      RMG_REQUIRE(T.tx * T.ty <= kTableThreads && (T.tx + 2) * (T.ty + 2) <= 2 * kTableThreads && T.ty >= 1, RMG_ERR_ARG,
+                  "internal: element tile does not fit its block");
+    upload(L.d_elem_tiles, L.elem_tiles);
   }
   for (const Tile3& T : L.table_tiles) {
     const RegionGeo& R = L.regs[T.region];

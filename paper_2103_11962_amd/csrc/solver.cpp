@@ -42,7 +42,7 @@ KernelTimer::~KernelTimer() {
 static int64_t partial_capacity(const Level& L) {
   // node blocks, 2.5D tiles or the region-table split (whole-region table tiles, other regions'
   // tiles), then the interface groups
-  const int64_t split = (int64_t)(L.table_tiles.size() + L.tiles.size());
+  const int64_t split = (int64_t)(L.table_tiles.size() + std::max(L.tiles.size(), L.elem_tiles.size()));
   return std::max({(int64_t)L.blocks.size(), (int64_t)L.tiles.size(), split}) + (L.ngroups + kBlock - 1) / kBlock + 16;
 }
 
@@ -142,7 +142,7 @@ static std::string tune_key(const Level& L, int level, int precision) {
 }
 
 static void apply_choice(Level& L, const TuneChoice& c) {
-  L.use_split = c.mode != 0 && !L.table_tiles.empty();
+  L.use_split = c.mode != 0 && !L.table_served.empty();
   if (c.mode == 0) {
     L.use_tiles = false;
     L.tile_grid = 0;
