@@ -533,7 +533,6 @@ void amg_setup(rmg_handle* h, Level& L) {
   upload(L.comp_owner, owner, st);
   L.cvec.alloc(sizeof(double) * (size_t)L.nc);
   L.cvec2.alloc(sizeof(double) * (size_t)L.nc);
-  L.abar_host.clear();
   // levels: aggregate, smooth the tentative prolongator, Galerkin product
   for (;;) {
     amg->lv.push_back(std::make_unique<AmgLevel>());

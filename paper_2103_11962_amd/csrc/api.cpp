@@ -119,6 +119,7 @@ rmg_handle::~rmg_handle() {
 void rmg::bind_handle(rmg_handle* h) {
   RMG_HIP(hipSetDevice(h->device));
   current_allocator() = h->alloc;
+  current_recycler() = &h->recycler;
 }
 
 static void use_device(rmg_handle* h) {
@@ -178,7 +179,7 @@ rmg_status rmg_create(rmg_handle** out, int device, void* stream, const rmg_allo
   rmg_handle* h = new rmg_handle();
   h->device = device;
   h->stream = static_cast<hipStream_t>(stream);
-  if (alloc) h->alloc = DevAlloc{alloc->alloc, alloc->free, alloc->ctx};
+  if (alloc) h->alloc = h->recycler.from = DevAlloc{alloc->alloc, alloc->free, alloc->ctx};
   rmg_options_default(&h->opt);
   try {
     bind_handle(h);
@@ -211,6 +212,7 @@ rmg_status rmg_build_regions(rmg_handle* h, int dim, int ndof, int nreg, const i
   RMG_REQUIRE(nreg >= 1 && extent && origin, RMG_ERR_ARG, "need nreg >= 1 and extent/origin arrays");
   RMG_REQUIRE(mask < (1u << (2 * dim)), RMG_ERR_ARG, "dirichlet mask has bits beyond 2*dim");
   h->have_regions = h->have_operator = h->have_hierarchy = false;
+  h->recycler.flush();
   hybrid_destroy(h);
   amg_destroy(h);
   h->region_kind.clear();
@@ -269,6 +271,7 @@ rmg_status rmg_set_region_stencil(rmg_handle* h, int region, int npts, const dou
   Level& L = level_of(h, 0);
   RMG_REQUIRE(region >= 0 && region < h->nreg, RMG_ERR_ARG, "region index out of range");
   RMG_REQUIRE(coef != nullptr, RMG_ERR_ARG, "null coefficient pointer");
+  RecycleScope keep(h->recycler, false);
   const bool ok = (h->dim == 3 && npts == 27) || (h->dim == 2 && (npts == 5 || npts == 9));
   RMG_REQUIRE(ok, RMG_ERR_ARG, "npts must be 27 in 3D and 5 or 9 in 2D");
   bool any = false;
@@ -358,6 +361,7 @@ rmg_status rmg_set_composite_stencil(rmg_handle* h, int npts, const double* coef
   Level& L = level_of(h, 0);
   RMG_REQUIRE(coef != nullptr, RMG_ERR_ARG, "null coefficient pointer");
   check_composite_split(h, npts);
+  RecycleScope keep(h->recycler, false);
   DBuf tmp;
   const double* src = coef;
   if (!on_device) {
@@ -376,6 +380,7 @@ rmg_status rmg_set_composite_csr(rmg_handle* h, int npts, int64_t nnz, const int
   Level& L = level_of(h, 0);
   RMG_REQUIRE(rowptr && (nnz == 0 || (colind && values)) && nnz >= 0, RMG_ERR_ARG, "null CSR array or nnz < 0");
   check_composite_split(h, npts);
+  RecycleScope keep(h->recycler, false);
   const int64_t n = L.ncomp;
   // row pointers are checked on the host before any kernel reads through them
   std::vector<int64_t> rp(n + 1);
@@ -442,6 +447,7 @@ rmg_status rmg_assemble_q1(rmg_handle* h, int pde, double hsize, const double* e
     for (int k = 0; k < h->nreg; ++k)
       RMG_REQUIRE(youngs[k] > 0.0 && std::isfinite(youngs[k]), RMG_ERR_NUMERIC, "Young's moduli must be positive");
   }
+  RecycleScope keep(h->recycler, false);
   begin_operator_change(h, L);
   h->region_set.assign(h->nreg, false);
   L.npts = 27;
@@ -547,6 +553,7 @@ rmg_status rmg_setup_hierarchy(rmg_handle* h, const rmg_options* opt) {
   h->have_hierarchy = false;
   h->drop_graphs();
   const auto t0 = std::chrono::steady_clock::now();
+  RecycleScope keep(h->recycler, true);
   setup_hierarchy(h);
   RMG_HIP(hipStreamSynchronize(h->stream));
   h->setup_ms = std::chrono::duration<double, std::milli>(std::chrono::steady_clock::now() - t0).count();
@@ -805,8 +812,9 @@ rmg_status rmg_get_coarse_matrix(rmg_handle* h, double* host_out) {
   require_hierarchy(h);
   RMG_REQUIRE(host_out, RMG_ERR_ARG, "null output");
   Level& L = *h->levels.back();
-  RMG_REQUIRE(!L.abar_host.empty(), RMG_ERR_NOT_SETUP, "no dense coarse matrix (the AMG coarse solver is in use)");
-  std::memcpy(host_out, L.abar_host.data(), sizeof(double) * L.abar_host.size());
+  RMG_REQUIRE(L.ainv.p != nullptr, RMG_ERR_NOT_SETUP, "no dense coarse matrix (the AMG coarse solver is in use)");
+  const std::vector<double> abar = coarse_matrix(h, L);
+  std::copy(abar.begin(), abar.end(), host_out);
   API_END
 }
 

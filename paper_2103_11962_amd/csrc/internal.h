@@ -41,12 +41,51 @@ struct DevAlloc {
   void* ctx = nullptr;
 };
 DevAlloc& current_allocator();
+
+// Large device buffers that a handle's rebuild of its operator or hierarchy released, kept for the
+// rest of that rebuild: a repeated assembly and setup needs the same sizes again, and giving 12 GB
+// back and asking for them anew costs more than the setup where the driver has to wipe them (a step
+// of assembly, setup and solve on 64 regions of 82^3 took 84 ms or up to 457 ms).  Filled only inside
+// the entry points that set an operator or the hierarchy, emptied at the end of the setup, before a
+// new set of regions, when an allocation fails and with the handle; what it holds between an
+// assembly and its setup, the handle held before the assembly.
+struct Recycler {
+  struct Entry {
+    void* p;
+    size_t bytes;
+  };
+  std::vector<Entry> held;
+  DevAlloc from;      // the handle's provider, to which everything held goes back
+  bool open = false;  // inside an entry point that rebuilds
+  void* take(size_t bytes);  // a held buffer of exactly this size, or nullptr
+  void flush();
+  ~Recycler() { flush(); }
+};
+constexpr size_t kRecycleMin = (size_t)1 << 20;  // smaller buffers go straight back
+Recycler*& current_recycler();                   // of the handle whose entry point runs on this thread
 // Restores the thread's provider when an entry point returns; bind_handle(h) selects h's device
 // and provider for the rest of the entry point.
 struct AllocatorScope {
   DevAlloc saved;
-  AllocatorScope() : saved(current_allocator()) { current_allocator() = DevAlloc(); }
-  ~AllocatorScope() { current_allocator() = saved; }
+  Recycler* saved_recycler;
+  AllocatorScope() : saved(current_allocator()), saved_recycler(current_recycler()) {
+    current_allocator() = DevAlloc();
+    current_recycler() = nullptr;
+  }
+  ~AllocatorScope() {
+    current_allocator() = saved;
+    current_recycler() = saved_recycler;
+  }
+};
+// Opens a handle's recycler for the rest of an entry point; flush: and empties it at the end.
+struct RecycleScope {
+  Recycler& r;
+  bool flush;
+  RecycleScope(Recycler& r_, bool flush_) : r(r_), flush(flush_) { r.open = true; }
+  ~RecycleScope() {
+    r.open = false;
+    if (flush) r.flush();
+  }
 };
 
 // Body of a C entry point: library errors become a status and the thread's last error.
@@ -263,7 +302,6 @@ struct Level {
   DBuf ainv;       // double [nc][nc]
   DBuf comp_owner; // int32 [ncomp] regional node index of the owner copy
   DBuf cvec, cvec2;  // double [nc]
-  std::vector<double> abar_host;  // dense composite coarse operator (for inspection)
 
   int ncoef() const { return npts * ndof * ndof; }
   int64_t ndofs() const { return n * ndof; }
@@ -333,6 +371,7 @@ struct rmg_handle {
   rmg::Hybrid* hy = nullptr;
   rmg::Amg* amg = nullptr;  // AMG coarse solver below the region hierarchy (coarse_amg = 1)
   rmg::DevAlloc alloc;     // device memory provider (empty: hipMalloc)
+  rmg::Recycler recycler;
   double setup_ms = 0.0;   // wall time of the last rmg_setup_hierarchy
   ~rmg_handle();
 };
@@ -365,6 +404,8 @@ bool split_fits(const Level& L, const std::vector<int>& served);
 void make_transfer_tiles(Level& F, const Level& C, bool rows);
 void clear_split(Level& L);
 void build_coarse_solver(rmg_handle* h, Level& L);
+// The coarsest level's dense composite operator (host, row-major).
+std::vector<double> coarse_matrix(rmg_handle* h, Level& L);
 
 // amg.cpp: AMG coarse solver on the coarsest region level's composite operator (Section 3.5).
 // amg_setup builds it from L's stencils (L.nc, comp_owner, cvec, cvec2 set as for the direct

@@ -114,6 +114,9 @@ void launch_coarse_gather(const Level& L, bool lowp, const void* b, hipStream_t 
 void launch_coarse_scatter(const Level& L, bool lowp, void* u, hipStream_t st);
 // y = A x, A row-major n x n (one wavefront per row).
 void launch_dense_gemv(int n, const double* A, const double* x, double* y, hipStream_t st);
+// Dense composite operator of the coarsest level (row-major), summed over the regions in ascending
+// order; rank: each regional node's rank among its node's copies, nranks the most copies a node has.
+void launch_coarse_assemble(const Level& L, const int* rank, int nranks, double* A, hipStream_t st);
 // In-place blocked Gauss-Jordan inversion of an SPD n x n matrix (row-major); synchronises st.
 void launch_gauss_jordan(double* A, int n, hipStream_t st);
 void launch_check_inverse(const double* A, int n, int* flag, hipStream_t st);

@@ -1152,46 +1152,65 @@ __global__ __launch_bounds__(kBlock) void k_rap_axis(const RegionGeo* __restrict
 }
 
 // Separable product for a scalar 3D level with geometric interpolation: passes x, y, z through two
-// intermediate grids (coarse along x; coarse along x and y), then the Dirichlet coarse rows.
+// intermediate grids (coarse along x; coarse along x and y), then the Dirichlet coarse rows.  The
+// regions go through in groups whose larger intermediate stays below kRapGroupBytes, so that it is
+// read back from the caches and the two buffers stay small (64 regions of 82^3 in one group: 2.6 and
+// 0.9 GB).
+constexpr int64_t kRapGroupBytes = (int64_t)160 << 20;
+
 static void launch_rap_separable(const Level& F, Level& C, hipStream_t st) {
   std::vector<RegionGeo> g1(F.regs), g2(F.regs);
   std::vector<BlockDesc> b1, b2;
-  int64_t n1 = 0, n2 = 0;
+  struct Group {
+    size_t b1, b2, bc;  // first blocks of the two intermediates and of the coarse level
+  };
+  std::vector<Group> groups;
+  int64_t n1 = 0, n2 = 0, most1 = 0, most2 = 0;
   for (int k = 0; k < F.nreg; ++k) {
     g1[k].ex = C.regs[k].ex;
     g2[k].ex = C.regs[k].ex;
     g2[k].ey = C.regs[k].ey;
     for (RegionGeo* g : {&g1[k], &g2[k]}) g->n = g->ex * g->ey * g->ez;
+    if (k == 0 || (n1 + g1[k].n) * 27 * (int64_t)sizeof(double) > kRapGroupBytes) {
+      groups.push_back({b1.size(), b2.size(), (size_t)C.region_block[k]});
+      n1 = n2 = 0;
+    }
     g1[k].off = n1;
     g2[k].off = n2;
     for (int s0 = 0; s0 < g1[k].n; s0 += kBlock) b1.push_back(BlockDesc{k, s0});
     for (int s0 = 0; s0 < g2[k].n; s0 += kBlock) b2.push_back(BlockDesc{k, s0});
     n1 += g1[k].n;
     n2 += g2[k].n;
+    most1 = std::max(most1, n1);
+    most2 = std::max(most2, n2);
   }
+  groups.push_back({b1.size(), b2.size(), C.blocks.size()});
   DBuf dg1, dg2, db1, db2, s1, s2;
   dg1.alloc(sizeof(RegionGeo) * g1.size());
   dg2.alloc(sizeof(RegionGeo) * g2.size());
   db1.alloc(sizeof(BlockDesc) * b1.size());
   db2.alloc(sizeof(BlockDesc) * b2.size());
-  RMG_HIP(hipMemcpyAsync(dg1.p, g1.data(), dg1.bytes, hipMemcpyHostToDevice, st));
-  RMG_HIP(hipMemcpyAsync(dg2.p, g2.data(), dg2.bytes, hipMemcpyHostToDevice, st));
-  RMG_HIP(hipMemcpyAsync(db1.p, b1.data(), db1.bytes, hipMemcpyHostToDevice, st));
-  RMG_HIP(hipMemcpyAsync(db2.p, b2.data(), db2.bytes, hipMemcpyHostToDevice, st));
-  s1.alloc(sizeof(double) * coef_elems(n1, 27));
-  s2.alloc(sizeof(double) * coef_elems(n2, 27));
+  RMG_HIP(hipMemcpyAsync(dg1.p, g1.data(), sizeof(RegionGeo) * g1.size(), hipMemcpyHostToDevice, st));
+  RMG_HIP(hipMemcpyAsync(dg2.p, g2.data(), sizeof(RegionGeo) * g2.size(), hipMemcpyHostToDevice, st));
+  RMG_HIP(hipMemcpyAsync(db1.p, b1.data(), sizeof(BlockDesc) * b1.size(), hipMemcpyHostToDevice, st));
+  RMG_HIP(hipMemcpyAsync(db2.p, b2.data(), sizeof(BlockDesc) * b2.size(), hipMemcpyHostToDevice, st));
+  s1.alloc(sizeof(double) * coef_elems(most1, 27));
+  s2.alloc(sizeof(double) * coef_elems(most2, 27));
   const LevelView cv = C.view();
   const bool tables = F.class_table.p && F.class_table_ok.p;
-  RMG_LAUNCH((k_rap_axis<0, false>), dim3(b1.size()), dim3(kBlock), 0, st, F.d_regs.as<RegionGeo>(),
-             dg1.as<RegionGeo>(), db1.as<BlockDesc>(), F.coef.as<double>(), s1.as<double>(), cv,
-             F.coef_sym.as<double>(), tables ? F.class_table.as<double>() : nullptr,
-             tables ? F.class_table_ok.as<int>() : nullptr);
-  RMG_LAUNCH((k_rap_axis<1, false>), dim3(b2.size()), dim3(kBlock), 0, st, dg1.as<RegionGeo>(),
-             dg2.as<RegionGeo>(), db2.as<BlockDesc>(), s1.as<double>(), s2.as<double>(), cv, nullptr, nullptr,
-             nullptr);
-  RMG_LAUNCH((k_rap_axis<2, true>), dim3(C.blocks.size()), dim3(kBlock), 0, st, dg2.as<RegionGeo>(),
-             C.d_regs.as<RegionGeo>(), C.d_blocks.as<BlockDesc>(), s2.as<double>(), C.coef.as<double>(), cv, nullptr,
-             nullptr, nullptr);
+  for (size_t g = 0; g + 1 < groups.size(); ++g) {
+    const Group &a = groups[g], &e = groups[g + 1];
+    RMG_LAUNCH((k_rap_axis<0, false>), dim3(e.b1 - a.b1), dim3(kBlock), 0, st, F.d_regs.as<RegionGeo>(),
+               dg1.as<RegionGeo>(), db1.as<BlockDesc>() + a.b1, F.coef.as<double>(), s1.as<double>(), cv,
+               F.coef_sym.as<double>(), tables ? F.class_table.as<double>() : nullptr,
+               tables ? F.class_table_ok.as<int>() : nullptr);
+    RMG_LAUNCH((k_rap_axis<1, false>), dim3(e.b2 - a.b2), dim3(kBlock), 0, st, dg1.as<RegionGeo>(),
+               dg2.as<RegionGeo>(), db2.as<BlockDesc>() + a.b2, s1.as<double>(), s2.as<double>(), cv, nullptr, nullptr,
+               nullptr);
+    RMG_LAUNCH((k_rap_axis<2, true>), dim3(e.bc - a.bc), dim3(kBlock), 0, st, dg2.as<RegionGeo>(),
+               C.d_regs.as<RegionGeo>(), C.d_blocks.as<BlockDesc>() + a.bc, s2.as<double>(), C.coef.as<double>(), cv,
+               nullptr, nullptr, nullptr);
+  }
   LAUNCH_CHECK();
   // Dirichlet coarse rows, one thread each from the list of them (rows or planes on a Dirichlet
   // face entirely, else the two end nodes of the row)
@@ -1378,6 +1397,42 @@ void launch_coarse_solve(const Level& L, bool lowp, const void* b, void* u, hipS
                      L.cvec2.as<double>());
   LAUNCH_CHECK();
   launch_coarse_scatter(L, lowp, u, st);
+}
+
+// Adds the stencils of the regional nodes of one rank among their node's copies to the dense composite
+// operator: at most one of them per composite row, so no two threads meet, and rank after rank every
+// entry is summed over the regions in ascending order.  (Assembled on the host and uploaded, 2,197
+// rows of 64 regions took 7 ms of the setup; the passes take 0.1 ms.)
+__global__ __launch_bounds__(kBlock) void k_coarse_assemble(LevelView L, const double* __restrict__ coef,
+                                                            const int* __restrict__ rank, int r, int nc,
+                                                            double* __restrict__ A) {
+  const BlockDesc bd = L.blocks[blockIdx.x];
+  const RegionGeo R = L.regs[bd.region];
+  const int li = bd.start + (int)threadIdx.x;
+  if (li >= R.n || rank[R.off + li] != r) return;
+  int x, y, z;
+  decompose(R, li, x, y, z);
+  const int nd = L.ndof, nb = nd * nd, ncoef = L.npts * nb;
+  const int64_t i = comp_index(L, R.ox + x, R.oy + y, R.oz + z);
+  for (int s = 0; s < L.npts; ++s) {
+    const int dx = s % 3 - 1, dy = (s / 3) % 3 - 1, dz = L.npts == 27 ? s / 9 - 1 : 0;
+    if ((unsigned)(x + dx) >= (unsigned)R.ex || (unsigned)(y + dy) >= (unsigned)R.ey ||
+        (unsigned)(z + dz) >= (unsigned)R.ez)
+      continue;
+    const int64_t j = comp_index(L, R.ox + x + dx, R.oy + y + dy, R.oz + z + dz);
+    for (int a = 0; a < nd; ++a)
+      for (int b = 0; b < nd; ++b)
+        A[(i * nd + a) * nc + (j * nd + b)] += coef[coef_index(R.off + li, s * nb + a * nd + b, ncoef)];
+  }
+}
+
+void launch_coarse_assemble(const Level& L, const int* rank, int nranks, double* A, hipStream_t st) {
+  const int nc = (int)(L.ncomp * L.ndof);
+  launch_zero((int64_t)nc * nc, A, st);
+  for (int r = 0; r < nranks; ++r)
+    RMG_LAUNCH(k_coarse_assemble, dim3(L.blocks.size()), dim3(kBlock), 0, st, L.view(), L.coef.as<double>(), rank, r, nc,
+               A);
+  LAUNCH_CHECK();
 }
 
 // ------------------------------------------ coarse inverse: blocked Gauss-Jordan (SPD, in place)

@@ -15,30 +15,71 @@ DevAlloc& current_allocator() {
   return a;
 }
 
+Recycler*& current_recycler() {
+  thread_local Recycler* r = nullptr;
+  return r;
+}
+
+static bool same_provider(const DevAlloc& a, const DevAlloc& b) {
+  return a.alloc == b.alloc && a.free == b.free && a.ctx == b.ctx;
+}
+
+static void give_back(void* p, const DevAlloc& from) {
+  if (from.free) from.free(p, from.ctx);
+  else (void)hipFree(p);
+}
+
+void* Recycler::take(size_t bytes) {
+  for (size_t i = 0; i < held.size(); ++i)
+    if (held[i].bytes == bytes) {
+      void* p = held[i].p;
+      held.erase(held.begin() + i);
+      return p;
+    }
+  return nullptr;
+}
+
+void Recycler::flush() {
+  std::vector<Entry> gone;
+  gone.swap(held);
+  for (const Entry& e : gone) give_back(e.p, from);
+}
+
 void DBuf::alloc(size_t nbytes) {
+  const DevAlloc& a = current_allocator();
+  Recycler* r = current_recycler();
+  if (p && nbytes == bytes && nbytes >= kRecycleMin && r && r->open && same_provider(from, a)) return;  // as it is
   release();
   if (nbytes == 0) return;
-  const DevAlloc& a = current_allocator();
-  if (a.alloc) {
-    p = a.alloc(nbytes, a.ctx);
-    if (!p) fail(RMG_ERR_OOM, "device memory provider returned no memory for " + std::to_string(nbytes) + " bytes");
-    from = a;
-  } else {
-    hipError_t e = hipMalloc(&p, nbytes);
-    if (e != hipSuccess) {
-      p = nullptr;
-      fail(e == hipErrorOutOfMemory ? RMG_ERR_OOM : RMG_ERR_DEVICE,
-           "hipMalloc of " + std::to_string(nbytes) + " bytes failed: " + hipGetErrorString(e));
+  if (r && r->open && nbytes >= kRecycleMin && same_provider(r->from, a)) p = r->take(nbytes);
+  for (int attempt = 0; !p; ++attempt) {
+    // out of memory: what the recycler holds is given back before the second and last try
+    const bool last = attempt == 1 || !r || r->held.empty();
+    if (a.alloc) {
+      p = a.alloc(nbytes, a.ctx);
+      if (!p && last)
+        fail(RMG_ERR_OOM, "device memory provider returned no memory for " + std::to_string(nbytes) + " bytes");
+    } else {
+      hipError_t e = hipMalloc(&p, nbytes);
+      if (e != hipSuccess) {
+        p = nullptr;
+        if (e != hipErrorOutOfMemory || last)
+          fail(e == hipErrorOutOfMemory ? RMG_ERR_OOM : RMG_ERR_DEVICE,
+               "hipMalloc of " + std::to_string(nbytes) + " bytes failed: " + hipGetErrorString(e));
+        (void)hipGetLastError();
+      }
     }
-    from = DevAlloc();
+    if (!p) r->flush();
   }
+  from = a;
   bytes = nbytes;
 }
 
 void DBuf::release() {
   if (p) {
-    if (from.free) from.free(p, from.ctx);
-    else (void)hipFree(p);
+    Recycler* r = current_recycler();
+    if (r && r->open && bytes >= kRecycleMin && same_provider(r->from, from)) r->held.push_back({p, bytes});
+    else give_back(p, from);
   }
   p = nullptr;
   bytes = 0;
@@ -372,6 +413,27 @@ void make_transfer_tiles(Level& F, const Level& C, bool rows_and_planes) {
   upload(F.d_ptiles, F.ptiles);
 }
 
+// Sorts (composite index << 32 | regional index) pairs that are in ascending order of the regional
+// index: a stable sort by the composite index alone, eleven bits a pass (290k pairs of a 1.4M-node
+// level: 9 ms by comparisons, under 2 ms so).
+static void sort_by_composite(std::vector<uint64_t>& keys, int64_t ncomp) {
+  constexpr int kBits = 11, kBuckets = 1 << kBits;
+  std::vector<uint64_t> other(keys.size());
+  std::vector<size_t> at(kBuckets);
+  for (int shift = 32; shift == 32 || (ncomp - 1) >> (shift - 32) > 0; shift += kBits) {
+    std::fill(at.begin(), at.end(), 0);
+    for (uint64_t k : keys) ++at[(k >> shift) & (kBuckets - 1)];
+    size_t sum = 0;
+    for (size_t& a : at) {
+      const size_t n = a;
+      a = sum;
+      sum += n;
+    }
+    for (uint64_t k : keys) other[at[(k >> shift) & (kBuckets - 1)]++] = k;
+    keys.swap(other);
+  }
+}
+
 // Offsets, block table and interface groups of a level whose regs/comp are set.
 void build_tables(Level& L) {
   int64_t off = 0;
@@ -407,9 +469,12 @@ void build_tables(Level& L) {
         }
       }
   }
-  std::sort(keys.begin(), keys.end());
+  sort_by_composite(keys, L.ncomp);
   std::vector<int64_t> gptr;
   std::vector<int32_t> gcopy, gcomp;
+  gptr.reserve(keys.size() / 2 + 1);
+  gcopy.reserve(keys.size());
+  gcomp.reserve(keys.size() / 2);
   gptr.push_back(0);
   for (size_t i = 0; i < keys.size();) {
     size_t j = i;
@@ -427,16 +492,19 @@ void build_tables(Level& L) {
   // Order groups by multiplicity (faces, then edges, then corners) so a wavefront mostly sees
   // groups of one size.
   const int64_t ng = (int64_t)gcomp.size();
-  std::vector<int64_t> order(ng);
-  for (int64_t g = 0; g < ng; ++g) order[g] = g;
-  std::stable_sort(order.begin(), order.end(), [&](int64_t a, int64_t b) {
-    return (gptr[a + 1] - gptr[a]) < (gptr[b + 1] - gptr[b]);
-  });
+  int64_t most = 0;
+  for (int64_t g = 0; g < ng; ++g) most = std::max(most, gptr[g + 1] - gptr[g]);
+  std::vector<int64_t> first(most + 2, 0), order(ng);  // stable counting sort
+  for (int64_t g = 0; g < ng; ++g) ++first[gptr[g + 1] - gptr[g] + 1];
+  for (int64_t m = 1; m <= most + 1; ++m) first[m] += first[m - 1];
+  for (int64_t g = 0; g < ng; ++g) order[first[gptr[g + 1] - gptr[g]]++] = g;
   std::vector<int64_t> gptr2(1, 0);
   std::vector<int32_t> gcopy2, gcomp2;
+  gptr2.reserve(ng + 1);
   gcopy2.reserve(gcopy.size());
+  gcomp2.reserve(ng);
   for (int64_t g : order) {
-    for (int64_t c = gptr[g]; c < gptr[g + 1]; ++c) gcopy2.push_back(gcopy[c]);
+    gcopy2.insert(gcopy2.end(), gcopy.begin() + gptr[g], gcopy.begin() + gptr[g + 1]);
     gptr2.push_back((int64_t)gcopy2.size());
     gcomp2.push_back(gcomp[g]);
   }
@@ -575,20 +643,15 @@ Level* make_coarse_level(const Level& F) {
   return C.release();
 }
 
-// Coarsest level: Abar = Psi-bar [[Abar]] Psi-bar^T assembled densely on the host from the
-// regional stencils, then inverted on the device (Section 3.5, direct solver).
-void build_coarse_solver(rmg_handle* h, Level& L) {
+// Dense Abar = Psi-bar [[Abar]] Psi-bar^T on the host, summed over the regions in ascending order (for
+// inspection).
+std::vector<double> coarse_matrix(rmg_handle* h, Level& L) {
   hipStream_t st = h->stream;
   const int nd = L.ndof, nb = nd * nd, ncoef = L.ncoef();
-  const int64_t nc64 = L.ncomp * nd;
-  RMG_REQUIRE(nc64 <= 20000, RMG_ERR_ARG, "coarsest composite problem too large for the dense solver");
-  const int nc = (int)nc64;
-  L.nc = nc;
-  std::vector<double> coef(coef_elems(L.n, ncoef));
+  const size_t nc = (size_t)(L.ncomp * nd);
+  std::vector<double> coef(coef_elems(L.n, ncoef)), abar(nc * nc, 0.0);
   RMG_HIP(hipMemcpyAsync(coef.data(), L.coef.p, sizeof(double) * coef.size(), hipMemcpyDeviceToHost, st));
   RMG_HIP(hipStreamSynchronize(st));
-  L.abar_host.assign((size_t)nc * nc, 0.0);
-  std::vector<int32_t> owner(L.ncomp, -1);
   for (int k = 0; k < L.nreg; ++k) {
     const RegionGeo& R = L.regs[k];
     for (int z = 0; z < R.ez; ++z)
@@ -596,30 +659,46 @@ void build_coarse_solver(rmg_handle* h, Level& L) {
         for (int x = 0; x < R.ex; ++x) {
           const int64_t li = ((int64_t)z * R.ey + y) * R.ex + x;
           const int64_t i = ((int64_t)(R.oz + z) * L.comp[1] + (R.oy + y)) * L.comp[0] + (R.ox + x);
-          if (owner[i] < 0) owner[i] = (int32_t)(R.off + li);
           for (int s = 0; s < L.npts; ++s) {
-            int dx, dy, dz;
-            if (L.npts == 27) {
-              dx = s % 3 - 1;
-              dy = (s / 3) % 3 - 1;
-              dz = s / 9 - 1;
-            } else {
-              dx = s % 3 - 1;
-              dy = s / 3 - 1;
-              dz = 0;
-            }
+            const int dx = s % 3 - 1, dy = (s / 3) % 3 - 1, dz = L.npts == 27 ? s / 9 - 1 : 0;
             if (x + dx < 0 || x + dx >= R.ex || y + dy < 0 || y + dy >= R.ey || z + dz < 0 || z + dz >= R.ez) continue;
             const int64_t j = ((int64_t)(R.oz + z + dz) * L.comp[1] + (R.oy + y + dy)) * L.comp[0] + (R.ox + x + dx);
             for (int a = 0; a < nd; ++a)
-              for (int b = 0; b < nd; ++b) {
-                const double v = coef[coef_index(R.off + li, s * nb + a * nd + b, ncoef)];
-                if (v != 0.0) L.abar_host[(size_t)(i * nd + a) * nc + (j * nd + b)] += v;
-              }
+              for (int b = 0; b < nd; ++b)
+                abar[(size_t)(i * nd + a) * nc + (j * nd + b)] += coef[coef_index(R.off + li, s * nb + a * nd + b, ncoef)];
           }
         }
   }
+  return abar;
+}
+
+// Coarsest level: the same Abar assembled and inverted on the device (Section 3.5, direct solver).
+void build_coarse_solver(rmg_handle* h, Level& L) {
+  hipStream_t st = h->stream;
+  const int64_t nc64 = L.ncomp * L.ndof;
+  RMG_REQUIRE(nc64 <= 20000, RMG_ERR_ARG, "coarsest composite problem too large for the dense solver");
+  const int nc = (int)nc64;
+  L.nc = nc;
+  // each composite node's owner copy, and each regional node's rank among its node's copies
+  std::vector<int32_t> owner(L.ncomp, -1), copies(L.ncomp, 0), rank(L.n);
+  int nranks = 0;
+  for (int k = 0; k < L.nreg; ++k) {
+    const RegionGeo& R = L.regs[k];
+    for (int z = 0; z < R.ez; ++z)
+      for (int y = 0; y < R.ey; ++y)
+        for (int x = 0; x < R.ex; ++x) {
+          const int64_t i = ((int64_t)(R.oz + z) * L.comp[1] + (R.oy + y)) * L.comp[0] + (R.ox + x);
+          const int64_t ri = R.off + ((int64_t)z * R.ey + y) * R.ex + x;
+          if (owner[i] < 0) owner[i] = (int32_t)ri;
+          rank[ri] = copies[i]++;
+          nranks = std::max(nranks, copies[i]);
+        }
+  }
+  DBuf drank;
+  drank.alloc(sizeof(int32_t) * rank.size());
+  RMG_HIP(hipMemcpyAsync(drank.p, rank.data(), sizeof(int32_t) * rank.size(), hipMemcpyHostToDevice, st));
   L.ainv.alloc(sizeof(double) * (size_t)nc * nc);
-  RMG_HIP(hipMemcpyAsync(L.ainv.p, L.abar_host.data(), sizeof(double) * (size_t)nc * nc, hipMemcpyHostToDevice, st));
+  launch_coarse_assemble(L, drank.as<int>(), nranks, L.ainv.as<double>(), st);
   L.comp_owner.alloc(sizeof(int32_t) * owner.size());
   RMG_HIP(hipMemcpyAsync(L.comp_owner.p, owner.data(), sizeof(int32_t) * owner.size(), hipMemcpyHostToDevice, st));
   L.cvec.alloc(sizeof(double) * nc);
