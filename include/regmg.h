@@ -157,13 +157,15 @@ typedef struct {
                          operator is the same everywhere inside, as the structured regions of the
                          Q1 Laplacian, the per-region diffusion and elasticity problems give), the
                          region's couplings come from its 125 x 27 class table (whole-row tiles on
-                         scalar levels of 2.5D tiles or at least 150,000 nodes, each node's class row
-                         on node blocks; the low-precision V-cycle has a table of its own values) instead of being
+                         scalar levels of 2.5D tiles or at least 150,000 nodes and, all regions
+                         served, on 3-dof levels of at least 400,000, each node's class row on
+                         node blocks; the low-precision V-cycle has a table of its own values) instead of being
                          streamed from memory.  The regions of an RMG_PDE_DIFFUSION finest level
                          that no table serves assemble their couplings on the fly in FP64 (levels
                          of 2.5D tiles or at least 150,000 nodes).  Results are bit for bit those
                          of 0, which always streams the couplings */
-  int tile_planes;    /* planes per 2.5D tile: 0 (default) chooses (41 on FP64 levels that keep at
+  int tile_planes;    /* planes per 2.5D tile (non-zero also runs the table tiles of 3-dof levels of
+                         any size): 0 (default) chooses (41 on FP64 levels that keep at
                          least 1024 such tiles, else 21); 21 or 41 forces that depth on every
                          tiled level, so that a problem small enough for the oracle runs the launch
                          shape of the large ones (used by the parity tests) */

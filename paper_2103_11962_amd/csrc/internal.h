@@ -141,6 +141,10 @@ constexpr int kTileThreadsF32 = 256;
 // rows in 768, 312 us for seven in 640).
 constexpr int kTableThreads = 512;
 constexpr int kTablePlanes = 41;
+// Threads per tile of a 3-dof table region (k_stencil_table3) and staged values per thread and plane at
+// most: about 150 VGPRs in FP64, so twelve waves a CU, two such blocks.
+constexpr int kTable3Threads = 384;
+constexpr int kTable3Fetch = 5;
 // Largest (tx + 2)(ty + 2) over tiles of at most nt nodes (tx * ty <= nt): the single row, ty = 1.
 constexpr int tile_plane_cap(int nt) { return 3 * (nt + 2); }
 // Region tables: a node's class along an axis of extent e >= 5 is its coordinate on the two low
@@ -246,6 +250,7 @@ struct Level {
   // With the tables: the served regions run whole-row tiles that take every coupling from the
   // tables (k_stencil_table), the other regions the level's streaming 2.5D tiles.  Built with the
   // tables (make_split), refreshed when the tiles change.
+  bool split_lo = true;              // the low-precision tables serve the same regions
   bool use_split = false;            // run the split (an autotuned level may prefer node blocks)
   bool split_auto = false;           // a level without 2.5D tiles may run table tiles when they serve all of it
   // the split also runs the CG product, whose (p, q) sums follow the launch's tiles: not with an FP32
@@ -399,6 +404,9 @@ void make_split(Level& L, const std::vector<int>& served, bool elem);
 bool elem_fits(const Level& L, const std::vector<int>& served);
 // Whether every served region's rows fit a table tile.
 bool split_fits(const Level& L, const std::vector<int>& served);
+// The same for a 3-dof level all of whose regions are served (k_stencil_table3); false if a region's
+// rows do not fit.
+bool make_split3(Level& L);
 // Row-and-plane tiles of the transfers between F and the next level C (F.rtiles, F.ptiles), or
 // none when `rows` is false or a region's rows are too long for them.
 void make_transfer_tiles(Level& F, const Level& C, bool rows);

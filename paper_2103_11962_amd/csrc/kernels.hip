@@ -2114,6 +2114,11 @@ static void class_table_launch(const Level& L, const C* sym, const float* centre
 // a step is a few microseconds of latency either way and the tiles are too few for the chip.
 constexpr int64_t kTableMinNodes = 150000;
 
+// 3-dof levels: table tiles from this many nodes on.  On 185k nodes (27 regions of 19^3) a step takes
+// 110 us in tiles, whose few planes do not cover their start-up, and 30 us on node blocks; on 4.5M
+// nodes 272 and 405 us.
+constexpr int64_t kTable3MinNodes = 400000;
+
 static void make_class_table(Level& L, hipStream_t st) {
   DBuf& tab = L.class_table;
   DBuf& ok = L.class_table_ok;
@@ -2133,7 +2138,10 @@ static void make_class_table(Level& L, hipStream_t st) {
     tab.release();
     ok.release();
   }
-  if (L.ndof != 1) return;
+  if (L.ndof == 3) {
+    if (served == L.nreg && L.split_auto && (L.deep_table || L.n >= kTable3MinNodes)) make_split3(L);
+    return;
+  }
   // regions that the tables do not serve: assembled on the fly where the level has its elements
   const bool elem = L.elem.p && served < L.nreg && elem_fits(L, flags);
   if (served == 0 && !elem) return;
@@ -2148,6 +2156,7 @@ static void make_class_table(Level& L, hipStream_t st) {
 // so the FP32 copy is served where the FP64 operator is; the centre blocks beside BF16 storage carry
 // a row-sum correction, and the check clears regions where those differ within a class.
 static void make_class_table_lo(Level& L, hipStream_t st) {
+  L.split_lo = true;
   L.class_table_lo.alloc(sizeof(float) * kClasses * kClassPts * L.ndof * L.ndof * L.nreg);
   L.class_table_lo_ok.alloc(sizeof(int) * L.nreg);
   float* tab = L.class_table_lo.as<float>();
@@ -2157,6 +2166,11 @@ static void make_class_table_lo(Level& L, hipStream_t st) {
     const uint16_t* sym = L.coef_lo_sym.as<uint16_t>();
     if (L.ndof == 3) class_table_launch<3, float, uint16_t>(L, sym, centre, tab, ok, st);
     else class_table_launch<1, float, uint16_t>(L, sym, centre, tab, ok, st);
+    std::vector<int> flags(L.nreg);
+    RMG_HIP(hipMemcpyAsync(flags.data(), ok, sizeof(int) * L.nreg, hipMemcpyDeviceToHost, st));
+    RMG_HIP(hipStreamSynchronize(st));
+    for (int k = 0; k < L.nreg; ++k)
+      if (!L.table_served.empty() && L.table_served[k] && !flags[k]) L.split_lo = false;
   } else {
     const int64_t ne = (int64_t)kClasses * kClassPts * L.ndof * L.ndof * L.nreg;
     launch_f64_to_f32(ne, L.class_table.as<double>(), tab, st);

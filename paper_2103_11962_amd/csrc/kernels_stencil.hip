@@ -691,6 +691,279 @@ __global__ __launch_bounds__(kTableThreads) __attribute__((amdgpu_waves_per_eu(s
   }
 }
 
+// ------------------------------------------------- region-table tiles, 3 dofs
+
+// k_stencil_table for 3-dof levels: 3 x 3 coupling blocks, 243 products a node, from the region's
+// table by scalar loads.  A tile is a few whole rows without their x-face nodes, or (pad 1) the four
+// x-face columns of up to 64 rows, a wavefront a column, so that in either a wavefront's nodes are
+// almost all of one class.  Planes of three-vectors pass through two LDS slots as there, and each plane
+// read adds its products to the running sums of the three nodes it neighbours in z; every node's
+// sums are k_stencil's, product for product, so the results are bit for bit those of node blocks.
+// 27 regions of 55^3 (4.5M nodes): CG product 405 us on node blocks, 272 here, the last smoothing step
+// with its inner product 487 and 446, an FP32 Chebyshev step 171 (streaming BF16 blocks 478).  A step is
+// bound by the latency between planes: 128 to 168 VGPRs leave twelve wavefronts a CU, whose 31 scalar
+// loads and one plane's memory latency a step the 243 products (1,000 cycles) only half cover.  Taking
+// the x-face columns' classes one after the other by scalar loads instead of from LDS cost 440 us (their
+// 20 classes of 2 KB do not fit the scalar cache), one plane in flight instead of two 10% more.
+template <class V, StencilOp OP, bool DOT>
+__global__ __launch_bounds__(kTable3Threads) __attribute__((amdgpu_waves_per_eu(sizeof(V) == 4 ? 4 : 3))) void k_stencil_table3(
+                                                                   LevelView L, const Tile3* __restrict__ tiles,
+                                                                   const V* __restrict__ table, OpP<V> p,
+                                                                   double* __restrict__ partials) {
+  constexpr int NT = kTable3Threads, kFetch = kTable3Fetch;
+  constexpr bool kPreB = OP == StencilOp::Residual || OP == StencilOp::ResidualScaled || OP == StencilOp::Cheb ||
+                         OP == StencilOp::ChebFirst;
+  constexpr bool kPreD = OP == StencilOp::Cheb;
+  constexpr bool kOwn = std::is_same<V, double>::value;  // D~^-1 of a one-region row as 1 / its centre entry
+  __shared__ V pl[2][kFetch * NT];
+  // x-face tiles: the couplings of the plane's 20 classes (five along y, four along x), the part of each
+  // stencil plane from the z class of the node that it belongs to
+  constexpr int kCols = 20, kRow = kClassPts * 9;
+  __shared__ V ft[kCols * kRow];
+  const Tile3 T = tiles[xcd_item((int)blockIdx.x, (int)gridDim.x)];
+  const RegionGeo R = L.regs[T.region];
+  // the table in the constant address space: no store of this kernel reaches it, so uniform reads are
+  // scalar loads (the compiler does not prove that by itself across a loop with this many accesses)
+  using Tab = const V __attribute__((address_space(4)))*;
+  const Tab tab = (Tab)(uintptr_t)(table + (int64_t)T.region * kClasses * kClassPts * 9);
+  const int t = threadIdx.x;
+  const bool face = T.pad != 0;
+  int row = 0, x = 2, col = 3;
+  bool active = false;
+  if (face) {
+    const int w = t >> 6, l = t & 63;
+    if (w < 4 && l < T.ty) {
+      row = l;
+      x = w < 2 ? w : R.ex - 4 + w;
+      col = w < 2 ? w + 1 : w + 3;
+      active = true;
+    }
+  } else if (t < T.ty * (R.ex - 4)) {
+    row = t / (R.ex - 4);
+    x = 2 + t - row * (R.ex - 4);
+    col = x + 1;
+    active = true;
+  }
+  const int y = T.y0 + row;
+  const int cxy = axis_class(y, R.ey) * 5 + axis_class(x, R.ex);
+  // staged columns: the whole row with its halo, or x = -1 .. 2 and ex - 3 .. ex
+  const int WC = 3 * (face ? 8 : R.ex + 2), PL = (T.ty + 2) * WC;
+  const int sy = R.ex, sz = R.ex * R.ey;
+  const V* __restrict__ xr = p.x + R.off * 3;
+  int off[kFetch];
+  unsigned inside = 0;
+#pragma unroll
+  for (int k = 0; k < kFetch; ++k) {
+    const int idx = min(t + k * NT, PL - 1), r = idx / WC, c = idx - r * WC, q = c / 3;
+    const int xx = face && q >= 4 ? R.ex - 7 + q : q - 1, yy = T.y0 - 1 + r;
+    if ((unsigned)yy < (unsigned)R.ey && (unsigned)xx < (unsigned)R.ex) inside |= 1u << k;
+    off[k] = (min(max(yy, 0), R.ey - 1) * sy + min(max(xx, 0), R.ex - 1)) * 3 + c - 3 * q;
+  }
+  auto fetch = [&](int zz, V(&pre)[kFetch]) {
+    const V* __restrict__ xz = xr + (int64_t)min(max(zz, 0), R.ez - 1) * sz * 3;
+#pragma unroll
+    for (int k = 0; k < kFetch; ++k) pre[k] = xz[off[k]];
+  };
+  auto store = [&](int slot, int zz, const V(&pre)[kFetch]) {
+    const bool zin = (unsigned)zz < (unsigned)R.ez;
+#pragma unroll
+    for (int k = 0; k < kFetch; ++k) {
+      const int idx = t + k * NT;
+      if (idx < PL) pl[slot][idx] = zin && (inside >> k & 1u) ? pre[k] : (V)0;
+    }
+  };
+  V v[27];  // this lane's 3 x 3 neighbours' three-vectors on the plane read last
+  auto readn = [&](int slot) __attribute__((always_inline)) {
+#pragma unroll
+    for (int j = 0; j < 9; ++j)
+#pragma unroll
+      for (int b = 0; b < 3; ++b) v[j * 3 + b] = pl[slot][(row + j / 3) * WC + (col - 1 + j % 3) * 3 + b];
+  };
+  const int z0 = T.z0, z1 = T.z0 + T.nz;
+  auto load_bd = [&](int z2, V(&b2)[3], V(&d2)[3]) {  // inactive lanes and planes past the tile: a valid node
+    const int64_t g = (R.off + (int64_t)min(z2, z1 - 1) * sz + (int64_t)y * sy + x) * 3;
+#pragma unroll
+    for (int a = 0; a < 3; ++a) {
+      if constexpr (kPreB) b2[a] = p.b[g + a];
+      if constexpr (kPreD) d2[a] = p.out[g + a];  // u_(k-2), see finish_value
+    }
+  };
+  // running sums as in k_stencil_table
+  V a0[3] = {}, a1[3] = {}, a2[3] = {}, ctr[3] = {}, xprev[3] = {};
+  auto czc = [&](int z) { return min(max(axis_class(z, R.ez), 0), 4); };
+  int key = -1;  // z classes of the couplings in ft
+  auto load_faces = [&](int q) {  // every thread of an x-face tile, before the plane's products
+    const int c0 = czc(q - 1), c1 = czc(q), c2 = czc(q + 1), want = (c0 * 5 + c1) * 5 + c2;
+    if (want == key) return;
+    key = want;
+    for (int e = t; e < kCols * kRow; e += NT) {
+      const int u = e / kRow, i = e - u * kRow, cx = (u & 3) < 2 ? (u & 3) : (u & 3) + 1;
+      const int cz = i < 81 ? c2 : (i < 162 ? c1 : c0);
+      ft[e] = tab[((cz * 5 + (u >> 2)) * 5 + cx) * kRow + i];
+    }
+    __syncthreads();
+  };
+  const int fu = (axis_class(y, R.ey) * 4 + min(t >> 6, 3)) * kRow;
+  auto add_plane = [&](int q) __attribute__((always_inline)) {
+#pragma unroll
+    for (int a = 0; a < 3; ++a) a2[a] = (V)0;
+    if (face) {  // each lane reads its class's couplings, one row of a block at a time
+      auto part = [&](int s0, V(&acc)[3]) __attribute__((always_inline)) {
+#pragma unroll
+        for (int j = 0; j < 9; ++j) {
+          V cf[9];
+#pragma unroll
+          for (int e = 0; e < 9; ++e) cf[e] = ft[fu + (s0 + j) * 9 + e];
+#pragma unroll
+          for (int a = 0; a < 3; ++a)
+#pragma unroll
+            for (int b = 0; b < 3; ++b) acc[a] = fma(cf[a * 3 + b], v[j * 3 + b], acc[a]);
+          if (j % 2) __asm__ volatile("" ::: "memory");
+        }
+      };
+      part(18, a0);
+      part(9, a1);
+      part(0, a2);
+      if constexpr (kOwn) {  // (of the node that this plane completes: class czc(q - 1))
+        const int cz = czc(q - 1) * 25 + cxy;
+#pragma unroll
+        for (int a = 0; a < 3; ++a) ctr[a] = tab[cz * kRow + 13 * 9 + a * 4];
+      }
+      return;
+    }
+    uint64_t left = __builtin_amdgcn_ballot_w64(true);
+    while (left) {
+      const int c = __builtin_amdgcn_readlane(cxy, (int)__builtin_ctzll(left));
+      int o0 = __builtin_amdgcn_readfirstlane((czc(q - 1) * 25 + c) * kClassPts * 9);
+      int o1 = __builtin_amdgcn_readfirstlane((czc(q) * 25 + c) * kClassPts * 9);
+      int o2 = __builtin_amdgcn_readfirstlane((czc(q + 1) * 25 + c) * kClassPts * 9);
+      __asm__ volatile("" : "+s"(o0), "+s"(o1), "+s"(o2));
+      const bool mine = cxy == c;
+      if (mine) {
+        const Tab t0 = tab + o0 + 18 * 9, t1 = tab + o1 + 9 * 9, t2 = tab + o2;
+#pragma unroll
+        for (int j = 0; j < 9; ++j)
+#pragma unroll
+          for (int a = 0; a < 3; ++a)
+#pragma unroll
+            for (int b = 0; b < 3; ++b) a0[a] = fma(t0[(j * 3 + a) * 3 + b], v[j * 3 + b], a0[a]);
+#pragma unroll
+        for (int j = 0; j < 9; ++j)
+#pragma unroll
+          for (int a = 0; a < 3; ++a)
+#pragma unroll
+            for (int b = 0; b < 3; ++b) a1[a] = fma(t1[(j * 3 + a) * 3 + b], v[j * 3 + b], a1[a]);
+#pragma unroll
+        for (int j = 0; j < 9; ++j)
+#pragma unroll
+          for (int a = 0; a < 3; ++a)
+#pragma unroll
+            for (int b = 0; b < 3; ++b) a2[a] = fma(t2[(j * 3 + a) * 3 + b], v[j * 3 + b], a2[a]);
+        if constexpr (kOwn) {
+#pragma unroll
+          for (int a = 0; a < 3; ++a) ctr[a] = tab[o0 + 13 * 9 + a * 4];
+        }
+      }
+      left &= ~__builtin_amdgcn_ballot_w64(mine);
+    }
+  };
+  auto shift = [&]() {
+#pragma unroll
+    for (int a = 0; a < 3; ++a) {
+      a0[a] = a1[a];
+      a1[a] = a2[a];
+      xprev[a] = v[12 + a];
+    }
+  };
+  V preA[kFetch], preB[kFetch];
+  fetch(z0 - 1, preA);
+  fetch(z0, preB);
+  store(0, z0 - 1, preA);
+  store(1, z0, preB);
+  fetch(z0 + 1, preA);
+  fetch(z0 + 2, preB);
+  __syncthreads();
+  if (face) load_faces(z0 - 1);
+  if (active) {
+    readn(0);
+    add_plane(z0 - 1);
+    shift();
+  }
+  __syncthreads();
+  if (face) load_faces(z0);
+  if (active) {
+    readn(1);
+    add_plane(z0);
+    shift();
+  }
+  __syncthreads();
+  store(0, z0 + 1, preA);
+  fetch(z0 + 3, preA);
+  __syncthreads();
+  double contrib = 0.0;
+  auto plane = [&](int zz, V(&pre)[kFetch]) __attribute__((always_inline)) {
+    const int sp = (zz - z0) & 1;  // slot holding plane zz + 1
+    const bool work = active && zz < z1;
+    if (face) load_faces(zz + 1);
+    if (work) readn(sp);
+    if (zz + 2 <= z1) store(sp ^ 1, zz + 2, pre);  // plane zz + 2 replaces plane zz
+    V cb[3] = {}, cd[3] = {};
+    load_bd(zz, cb, cd);  // used after the plane's 243 products; issued before the fetch, so not behind it
+    fetch(zz + 4, pre);
+    if (work) {
+      add_plane(zz + 1);
+      const int64_t node = R.off + (int64_t)zz * sz + (int64_t)y * sy + x;
+      const bool edge = x == 0 || x == R.ex - 1 || y == 0 || y == R.ey - 1 || zz == 0 || zz == R.ez - 1;
+      if (edge && is_shared(L, R, x, y, zz)) {  // finished by k_iface
+#pragma unroll
+        for (int a = 0; a < 3; ++a) write_partial<OP, V>(p, node * 3 + a, a0[a], xprev[a], cd[a]);
+      } else {
+        bool block = false;
+        if constexpr (OP == StencilOp::Cheb || OP == StencilOp::ChebFirst) {
+          if (p.dinv9) {
+            V dold[3], out[3], dd[3];
+#pragma unroll
+            for (int a = 0; a < 3; ++a)
+              dold[a] = OP == StencilOp::Cheb ? prev_correction(p, xprev[a], cd[a]) : xprev[a];
+            contrib += finish_block3_value<OP, DOT, V>(p, node, a0, xprev, dold, out, dd);
+#pragma unroll
+            for (int a = 0; a < 3; ++a) p.out[node * 3 + a] = out[a];
+            block = true;
+          }
+        }
+        if (!block) {
+#pragma unroll
+          for (int a = 0; a < 3; ++a) {
+            if constexpr (kPreB)
+              contrib += finish_pre<OP, DOT, V, kOwn>(p, node * 3 + a, a0[a], 1, xprev[a], ctr[a], cb[a], cd[a]);
+            else
+              contrib += finish<OP, DOT, V, kOwn>(p, node * 3 + a, a0[a], 1, xprev[a], ctr[a]);
+          }
+        }
+      }
+      shift();
+    }
+    __syncthreads();
+  };
+  // both halves run on every pass, see k_stencil_table
+  for (int zz = z0; zz < z1; zz += 2) {
+    plane(zz, preB);
+    plane(zz + 1, preA);
+  }
+  if constexpr (DOT || OP == StencilOp::CgQ) {
+    double s1 = contrib;
+    for (int o = 32; o > 0; o >>= 1) s1 += __shfl_down(s1, o, 64);
+    __shared__ double sm[NT / 64];
+    if ((t & 63) == 0) sm[t >> 6] = s1;
+    __syncthreads();
+    if (t == 0) {
+      double s = 0.0;
+      for (int i = 0; i < NT / 64; ++i) s += sm[i];
+      partials[blockIdx.x] = s;
+    }
+  }
+}
+
 // ------------------------------------------------------- element tiles
 
 // Whole-row tiles of regions of the finest level whose operator was assembled from element-wise
@@ -971,11 +1244,19 @@ static int64_t run(const Level& L, const StencilArgs& a, hipStream_t st) {
   const bool elem = NPTS == 27 && NDOF == 1 && std::is_same<V, double>::value && kSameType && !L.elem_tiles.empty();
   const bool split = NPTS == 27 && NDOF == 1 && kSameType && L.use_split && (table || elem) &&
                      (L.use_tiles || elem || L.other_tiles.empty()) && (OP != StencilOp::CgQ || L.split_dot);
-  const bool tiled = NPTS == 27 && NDOF == 1 && (L.use_tiles || split);
+  const bool split3 = NPTS == 27 && NDOF == 3 && L.use_split && table && (!a.lowp || L.split_lo);
+  const bool tiled = NPTS == 27 && ((NDOF == 1 && (L.use_tiles || split)) || split3);
   const int ntiles = (int)L.tiles.size();
   const int grid3 = (L.tile_grid > 0 && L.tile_grid < ntiles) ? L.tile_grid : ntiles;
   int64_t nparts = grid3;  // partial sums written by the tiled launches
   if (a.ev0) RMG_HIP(hipEventRecord(a.ev0, st));
+  if constexpr (NPTS == 27 && NDOF == 3) {
+    if (split3) {
+      nparts = (int64_t)L.table_tiles.size();
+      RMG_LAUNCH((k_stencil_table3<V, OP, DOT>), dim3(nparts), dim3(kTable3Threads), 0, st, v,
+                 L.d_table_tiles.as<Tile3>(), table, p, a.partials);
+    }
+  }
   if constexpr (NPTS == 27 && NDOF == 1) {
     if (tiled) {
       const C* sym = nullptr;

@@ -191,8 +191,9 @@ static int elem_rows(const RegionGeo& R) {
 // after the other at about the same pace whatever else runs, after a start-up of about kStart planes'
 // time, and `slots` blocks run at once: of all depths, the one that makes (rounds of blocks) x (planes +
 // start-up) least; beyond a few rounds the blocks' ends even out and the rounds are no longer whole.
-template <class In, class Rows>
-static int march_planes(const Level& L, int slots, In in, Rows rows) {
+// extra(R, p): further blocks of a region beside the tiles.
+template <class In, class Rows, class Extra>
+static int march_planes(const Level& L, int slots, In in, Rows rows, Extra extra) {
   constexpr int kStart = 4;
   if (L.deep_table) return kTablePlanes;
   double best = 1e300;
@@ -204,7 +205,7 @@ static int march_planes(const Level& L, int slots, In in, Rows rows) {
       if (!in(k)) continue;
       const RegionGeo& R = L.regs[k];
       const int ty = rows(R), nz = (R.ez + p - 1) / p;
-      tiles += (int64_t)((R.ey + ty - 1) / ty) * nz;
+      tiles += (int64_t)((R.ey + ty - 1) / ty) * nz + extra(R, p);
       deepest = std::max(deepest, (R.ez + nz - 1) / nz);
     }
     const double r = (double)tiles / slots;
@@ -253,7 +254,8 @@ void make_split(Level& L, const std::vector<int>& served, bool elem) {
   L.use_split = true;
   auto is_served = [&](int k) { return keep[k] != 0; };
   auto is_other = [&](int k) { return keep[k] == 0; };
-  const int planes = march_planes(L, 768, is_served, table_rows);
+  auto none = [](const RegionGeo&, int) { return 0; };
+  const int planes = march_planes(L, 768, is_served, table_rows, none);
   for (int k = 0; k < L.nreg; ++k) {
     if (!keep[k]) continue;
     const RegionGeo& R = L.regs[k];
@@ -263,7 +265,7 @@ void make_split(Level& L, const std::vector<int>& served, bool elem) {
     add_tiles(R, k, tymax, planes, L.table_tiles);
   }
   if (elem) {
-    const int eplanes = march_planes(L, 512, is_other, elem_rows);
+    const int eplanes = march_planes(L, 512, is_other, elem_rows, none);
     for (int k = 0; k < L.nreg; ++k)
       if (!keep[k]) add_tiles(L.regs[k], k, elem_rows(L.regs[k]), eplanes, L.elem_tiles);
     for (const Tile3& T : L.elem_tiles)
@@ -281,6 +283,46 @@ void make_split(Level& L, const std::vector<int>& served, bool elem) {
     if (!keep[T.region]) L.other_tiles.push_back(T);
   upload(L.d_table_tiles, L.table_tiles);
   upload(L.d_other_tiles, L.other_tiles);
+}
+
+// Tiles of k_stencil_table3: whole rows without their four x-face nodes (pad 0), and the four x-face
+// columns of up to 64 rows (pad 1), a wavefront each.  The columns' couplings come from LDS, lane by lane,
+// at about a third of the pace, so their tiles are a third as deep.
+bool make_split3(Level& L) {
+  clear_split(L);
+  auto rows = [](const RegionGeo& R) {
+    int ty = 0;
+    while (ty < R.ey && (R.ex - 4) * (ty + 1) <= kTable3Threads &&
+           3 * (R.ex + 2) * (ty + 3) <= kTable3Fetch * kTable3Threads)
+      ++ty;
+    return ty;
+  };
+  for (const RegionGeo& R : L.regs)
+    if (R.ex < 5 || R.ey < 5 || R.ez < 5 || rows(R) < 1) return false;
+  static_assert(3 * 8 * (64 + 2) <= kTable3Fetch * kTable3Threads && kTable3Threads >= 256, "x-face tiles");
+  auto face_planes = [](int p) { return std::max(3, p / 3); };
+  const int planes = march_planes(L, 512, [](int) { return true; }, rows, [&](const RegionGeo& R, int p) {
+    return (R.ey + 63) / 64 * ((R.ez + face_planes(p) - 1) / face_planes(p));
+  });
+  for (int k = 0; k < L.nreg; ++k) {
+    const RegionGeo& R = L.regs[k];
+    const size_t first = L.table_tiles.size();
+    add_tiles(R, k, 64, face_planes(planes), L.table_tiles);
+    for (size_t i = first; i < L.table_tiles.size(); ++i) L.table_tiles[i].pad = 1;
+    add_tiles(R, k, rows(R), planes, L.table_tiles);
+  }
+  for (const Tile3& T : L.table_tiles) {
+    const RegionGeo& R = L.regs[T.region];
+    const int cols = T.pad ? 8 : R.ex + 2;
+    RMG_REQUIRE(3 * cols * (T.ty + 2) <= kTable3Fetch * kTable3Threads &&
+                    (T.pad ? T.ty <= 64 : T.ty * (R.ex - 4) <= kTable3Threads) && T.y0 + T.ty <= R.ey &&
+                    T.z0 + T.nz <= R.ez && T.ty >= 1 && T.nz >= 1,
+                RMG_ERR_ARG, "internal: 3-dof table tile does not fit its block");
+  }
+  L.table_served.assign(L.nreg, 1);
+  L.use_split = true;
+  upload(L.d_table_tiles, L.table_tiles);
+  return true;
 }
 
 // Transfer tiles.  Restriction: a block of kBlock threads owns whole coarse rows (one thread per
