@@ -155,7 +155,6 @@ static void reserve_data(rmg_mlp* m, int64_t need) {
 
 static void reserve_work(rmg_mlp* m, int64_t n, int64_t nloss) {
   if (n > m->wcap) {
-    m->Z.alloc(sizeof(float) * kMlpOut * (size_t)n);
     m->dZ.alloc(sizeof(float) * kMlpOut * (size_t)n);
     m->A1.alloc(sizeof(float) * kMlpH * (size_t)n);
     m->A2.alloc(sizeof(float) * kMlpH * (size_t)n);
@@ -176,17 +175,24 @@ static void loss_grad(rmg_mlp* m, int slot) {
   const int64_t n = m->n;
   hipStream_t st = m->stream;
   const float* X = m->X.as<float>();
-  float* Z = m->Z.as<float>();
   float* A1 = m->A1.as<float>();
   float* A2 = m->A2.as<float>();
   float* dZ = m->dZ.as<float>();
   float* D1 = m->D1.as<float>();
   float* D2 = m->D2.as<float>();
-  mlp_forward(n, X, m->theta.as<float>(), Z, A1, A2, st);
-  const int64_t np = mlp_loss(n, Z, m->E.as<float>(), X, m->loss_kind, dZ, m->partials.as<double>(), st);
+  const bool l2 = m->loss_kind == RMG_MLP_LOSS_L2;
+  int64_t np;
+  if (l2) {
+    np = mlp_fused_l2(n, X, m->E.as<float>(), m->theta.as<float>(), A1, A2, dZ, D1, D2, m->partials.as<double>(), st);
+  } else {
+    if (!m->Z.p || m->Z.bytes < sizeof(float) * kMlpOut * (size_t)n) m->Z.alloc(sizeof(float) * kMlpOut * (size_t)n);
+    float* Z = m->Z.as<float>();
+    mlp_forward(n, X, m->theta.as<float>(), Z, A1, A2, st);
+    np = mlp_loss_energy(n, Z, m->E.as<float>(), X, dZ, m->partials.as<double>(), st);
+    mlp_backact(n, dZ, A1, A2, m->theta.as<float>(), D1, D2, st);
+  }
   launch_reduce(m->partials.as<double>(), np, m->losses.as<double>(), slot, st);
-  mlp_backact(n, dZ, A1, A2, m->theta.as<float>(), D1, D2, st);
-  mlp_weight_grads(n, X, A1, A2, dZ, D1, D2, m->grad.as<float>(), m->part.as<float>(), st);
+  mlp_weight_grads(n, X, A1, A2, dZ, l2, D1, D2, m->grad.as<float>(), m->part.as<float>(), st);
   m->have_grad = true;
 }
 

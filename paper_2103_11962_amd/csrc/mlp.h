@@ -23,20 +23,23 @@ void cell_node_table(CellNode* nodes, signed char* pos2node);
 
 // Z = MLP(X) for n samples; A1, A2 (pre-activations, [n][64]) are stored when non-null.
 void mlp_forward(int64_t n, const float* X, const float* theta, float* Z, float* A1, float* A2, hipStream_t st);
-// Loss partial sums (one double per block of samples; mlp_loss_partials(n) of them, also the
-// returned count) and dZ = dloss/dZ / n.
+// Most partial sums of a loss over n samples.
 int64_t mlp_loss_partials(int64_t n);
-// kind 0: interpolation error in L2; 1: in the energy norm of the cell's local operator (needs X).
-int64_t mlp_loss(int64_t n, const float* Z, const float* E, const float* X, int kind, float* dZ, double* partials,
-                 hipStream_t st);
+// Partial sums of the energy-norm loss (the returned count) and dZ = dloss/dZ / n.
+int64_t mlp_loss_energy(int64_t n, const float* Z, const float* E, const float* X, float* dZ, double* partials,
+                        hipStream_t st);
+// Forward pass, L2 loss and activation gradients in one: pre-activations A1, A2, dZ = dloss/dZ / n with
+// its 208 columns in output-slot order, D1, D2, and the returned count of loss partial sums.
+int64_t mlp_fused_l2(int64_t n, const float* X, const float* E, const float* theta, float* A1, float* A2, float* dZ,
+                     float* D1, float* D2, double* partials, hipStream_t st);
 // Activation gradients of the two hidden layers.
 void mlp_backact(int64_t n, const float* dZ, const float* A1, const float* A2, const float* theta, float* D1,
                  float* D2, hipStream_t st);
 // Weight gradients (flat, parameter order) from the activation gradients; part holds
-// mlp_grad_partials() floats.
+// mlp_grad_partials() floats; slots: dZ's columns are in output-slot order.
 int64_t mlp_grad_partials();
-void mlp_weight_grads(int64_t n, const float* X, const float* A1, const float* A2, const float* dZ, const float* D1,
-                      const float* D2, float* grad, float* part, hipStream_t st);
+void mlp_weight_grads(int64_t n, const float* X, const float* A1, const float* A2, const float* dZ, bool slots,
+                      const float* D1, const float* D2, float* grad, float* part, hipStream_t st);
 // Adam step t (from 1).
 void mlp_adam(float* theta, const float* grad, float* m, float* v, int t, double lr, hipStream_t st);
 
