@@ -242,7 +242,8 @@ rmg_status rmg_build_regions(rmg_handle* h, int dim, int ndof, int nreg, const i
   h->cg_q.alloc(nb);
   h->cg_z.alloc(nb);
   h->cg_b.alloc(nb);
-  h->partials.alloc(sizeof(double) * ((int64_t)L.blocks.size() + (L.ngroups + kBlock - 1) / kBlock + 16));
+  h->partials.alloc(sizeof(double) * ((int64_t)L.blocks.size() +
+                                         std::max((L.ngroups + kBlock - 1) / kBlock, (int64_t)L.ncopyblk) + 16));
   h->have_regions = true;
   API_END
 }

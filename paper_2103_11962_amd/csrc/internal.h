@@ -187,6 +187,21 @@ struct LevelView {
   int ndof;          // unknowns per node (1, or 3 for elasticity)
 };
 
+// Levels of at most this many nodes finish their shared nodes in the node-block kernels themselves: there
+// an interface kernel is a launch and one more chain of dependent loads (4 to 8 us) for a few us of work.
+// Measured with the line at 100,000 and at 600,000 nodes: 8 regions of 82^3 (level 1 of 175,616 nodes)
+// 583 and 577 us a V-cycle, 700 x 720 five-point Gauss-Seidel (504,000 nodes) 10.99 and 10.92 ms a solve.
+// Above the line tiles run most levels, and their shared nodes are many.
+constexpr int64_t kFuseNodes = 600000;
+
+// Interface copies in blocks, for the node-block kernels that finish the shared nodes themselves (small
+// levels): block k serves copies start[k] .. start[k + 1], whole groups of at most kBlock copies together.
+struct CopyView {
+  const int4* info;  // {regional node, its region, the group's first copy within the block, copies in the group}
+  const int* start;
+  int nblocks;       // 0: no such tables
+};
+
 // Device buffer owned by the library.
 struct DBuf {
   void* p = nullptr;
@@ -236,6 +251,10 @@ struct Level {
   DBuf d_gptr;    // int64 [ngroups+1]
   DBuf d_gcopy;   // int32 regional node indices
   DBuf d_gcomp;   // int32 composite node index of each group
+  // levels of at most kFuseNodes nodes: the interface copies in blocks (CopyView), else empty
+  DBuf d_copies, d_copy_start;
+  DBuf d_owner;  // with them: int32 per regional node, 1 on a group's first copy
+  int ncopyblk = 0;
   // operator (FP64, wave-tiled, ncoef() values per node: npts blocks of ndof x ndof)
   DBuf coef;
   DBuf coef_sym;     // symmetric scalar 27-point levels: the upper half (kSymPts per node), else empty
@@ -306,11 +325,15 @@ struct Level {
   int nc = 0;
   DBuf ainv;       // double [nc][nc]
   DBuf comp_owner; // int32 [ncomp] regional node index of the owner copy
+  DBuf comp_ptr, comp_copy;  // dense solver: int32 CSR of every composite node's copies
   DBuf cvec, cvec2;  // double [nc]
 
   int ncoef() const { return npts * ndof * ndof; }
   int64_t ndofs() const { return n * ndof; }
   LevelView view() const;
+  CopyView copies() const { return {d_copies.as<int4>(), d_copy_start.as<int>(), ncopyblk}; }
+  // shared nodes finished by the node-block kernels (the unbatched option keeps one launch per region)
+  bool fused_groups() const { return n <= kFuseNodes && !per_region; }
 };
 
 }  // namespace rmg
@@ -430,7 +453,9 @@ void setup_hierarchy(rmg_handle* h);
 // owned copies, summed by the last smoothing step, goes to that scalar slot.
 // start_ready: the level's zero-guess start u_0 = c D~^-1 b is already in its u (written by the CG
 // update), so the cycle does not compute it.
-void vcycle(rmg_handle* h, int level, bool lowp, const void* b, void* z, int dot_slot = -1, bool start_ready = false);
+// dot_post: CG scalar update after that sum (launch_reduce).
+void vcycle(rmg_handle* h, int level, bool lowp, const void* b, void* z, int dot_slot = -1, bool start_ready = false,
+            int dot_post = -1);
 // z = M^-1 r (one V-cycle in the configured precision); FP64 regional vectors.
 void apply_preconditioner(rmg_handle* h, const double* r, double* z);
 void pcg(rmg_handle* h, const double* b, double* x, double rtol, int maxit, rmg_solve_info* info,

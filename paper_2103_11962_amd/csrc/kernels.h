@@ -59,8 +59,9 @@ void launch_group_reduce(const int64_t* gptr, const int* gcopy, int64_t ngroups,
 // Owner-masked composite dot product (FP64): partial sums written to `partials`; returns their count.
 int64_t launch_dot(const Level& L, const double* a, const double* b, double* partials, hipStream_t st);
 
-// Deterministic sum of `n` partials into scalars[slot].
-void launch_reduce(const double* partials, int64_t n, double* scalars, int slot, hipStream_t st);
+// Deterministic sum of `n` partials into scalars[slot]; post >= 0: then the CG scalar update of that
+// mode (below) in the same launch.
+void launch_reduce(const double* partials, int64_t n, double* scalars, int slot, hipStream_t st, int post = -1);
 
 // Pointwise: u = c * dinv * b, the first Chebyshev step from a zero guess (the step after it runs
 // as ChebFirst with its c1: its previous correction is u itself).
@@ -68,7 +69,15 @@ void launch_cheb_zero(const Level& L, bool lowp, const void* b, const void* dinv
                       const void* dinv9 = nullptr);
 
 // Restriction level -> level+1 (input already divided by multiplicity), including coarse interface sum.
-void launch_restrict(const Level& F, const Level& C, bool lowp, const void* r_scaled, void* w, hipStream_t st);
+// start (small coarse levels only, else ignored): also the coarse zero-guess start u = c dinv w, as
+// launch_cheb_zero; returns whether it was written.
+struct CoarseStart {
+  const void* dinv;
+  double c;
+  void* u;
+};
+bool launch_restrict(const Level& F, const Level& C, bool lowp, const void* r_scaled, void* w, hipStream_t st,
+                     const CoarseStart* start = nullptr);
 // Prolongation u += P ubar (level+1 -> level).
 void launch_prolong_add(const Level& F, const Level& C, bool lowp, const void* ubar, void* u, hipStream_t st);
 // Coarse-major restriction weights (F.rw, 125 per coarse node) from the stored weights F.pw.
@@ -147,9 +156,8 @@ int64_t launch_cg_update(const Level& L, double* scalars, double* x, double* r, 
                          double c0 = 0.0, double* u0 = nullptr);
 // p = z + beta p.
 void launch_cg_direction(int64_t n, double* scalars, const double* z, double* p, hipStream_t st);
-// mode 0: alpha = rz / pq; mode 1: beta = rz_new / rz, rz = rz_new;
-// mode 2 (flexible CG): beta = -alpha (z_new, q) / rz, rz = rz_new.
-void launch_cg_scalars(double* scalars, int mode, hipStream_t st);
+// CG scalar updates (launch_reduce's post): mode 0: alpha = rz / pq; mode 1: beta = rz_new / rz,
+// rz = rz_new; mode 2 (flexible CG): beta = -alpha (z_new, q) / rz, rz = rz_new.
 void launch_copy(int64_t n, const double* src, double* dst, hipStream_t st);
 void launch_zero(int64_t n, double* dst, hipStream_t st);
 

@@ -70,23 +70,44 @@ constexpr int kUpdateDescs = 2;
 
 static int64_t reduction_blocks(const Level& L, int per) { return cdiv((int64_t)L.blocks.size(), per); }
 
+// Owned copies: the node blocks (one-region nodes), then blocks over the interface groups (first copies).
 template <int NDOF>
-__global__ __launch_bounds__(kBlock) void k_dot_nodes(LevelView L, const double* __restrict__ a,
-                                                      const double* __restrict__ b, double* __restrict__ partials) {
+__device__ __forceinline__ double dot_groups_block(const int64_t* __restrict__ gptr, const int* __restrict__ gcopy,
+                                                   int64_t ng, int block, const double* __restrict__ a,
+                                                   const double* __restrict__ b) {
+  const int64_t g = (int64_t)block * kBlock + threadIdx.x;
   double c = 0.0;
-  for (int j = 0; j < kDescsPerBlock; ++j) {
-    const int64_t d = (int64_t)blockIdx.x * kDescsPerBlock + j;
-    if (d >= L.nblocks) break;
-    const BlockDesc bd = L.blocks[d];
-    const RegionGeo R = L.regs[bd.region];
-    const int li = bd.start + (int)threadIdx.x;
-    if (li < R.n) {
-      int x, y, z;
-      decompose(R, li, x, y, z);
-      if (!is_shared(L, R, x, y, z)) {
-        const int64_t gi = (R.off + li) * NDOF;
+  if (g < ng) {
+    const int64_t i = (int64_t)gcopy[gptr[g]] * NDOF;
 #pragma unroll
-        for (int k = 0; k < NDOF; ++k) c += a[gi + k] * b[gi + k];
+    for (int k = 0; k < NDOF; ++k) c += a[i + k] * b[i + k];
+  }
+  return c;
+}
+
+template <int NDOF>
+__global__ __launch_bounds__(kBlock) void k_dot(LevelView L, int nb, const int64_t* __restrict__ gptr,
+                                                const int* __restrict__ gcopy, int64_t ng,
+                                                const double* __restrict__ a, const double* __restrict__ b,
+                                                double* __restrict__ partials) {
+  double c = 0.0;
+  if ((int)blockIdx.x >= nb) {
+    c = dot_groups_block<NDOF>(gptr, gcopy, ng, (int)blockIdx.x - nb, a, b);
+  } else {
+    for (int j = 0; j < kDescsPerBlock; ++j) {
+      const int64_t d = (int64_t)blockIdx.x * kDescsPerBlock + j;
+      if (d >= L.nblocks) break;
+      const BlockDesc bd = L.blocks[d];
+      const RegionGeo R = L.regs[bd.region];
+      const int li = bd.start + (int)threadIdx.x;
+      if (li < R.n) {
+        int x, y, z;
+        decompose(R, li, x, y, z);
+        if (!is_shared(L, R, x, y, z)) {
+          const int64_t gi = (R.off + li) * NDOF;
+#pragma unroll
+          for (int k = 0; k < NDOF; ++k) c += a[gi + k] * b[gi + k];
+        }
       }
     }
   }
@@ -98,14 +119,7 @@ template <int NDOF>
 __global__ __launch_bounds__(kBlock) void k_dot_groups(const int64_t* __restrict__ gptr, const int* __restrict__ gcopy,
                                                        int64_t ng, const double* __restrict__ a,
                                                        const double* __restrict__ b, double* __restrict__ partials) {
-  const int64_t g = (int64_t)blockIdx.x * kBlock + threadIdx.x;
-  double c = 0.0;
-  if (g < ng) {
-    const int64_t i = (int64_t)gcopy[gptr[g]] * NDOF;
-#pragma unroll
-    for (int k = 0; k < NDOF; ++k) c += a[i + k] * b[i + k];
-  }
-  const double s = block_sum(c);
+  const double s = block_sum(dot_groups_block<NDOF>(gptr, gcopy, ng, (int)blockIdx.x, a, b));
   if (threadIdx.x == 0) partials[blockIdx.x] = s;
 }
 
@@ -123,17 +137,33 @@ static int64_t dot_groups(const Level& L, const double* a, const double* b, doub
 }
 
 int64_t launch_dot(const Level& L, const double* a, const double* b, double* partials, hipStream_t st) {
-  const int64_t nb = reduction_blocks(L, kDescsPerBlock);
-  if (L.ndof == 3) RMG_LAUNCH(k_dot_nodes<3>, dim3(nb), dim3(kBlock), 0, st, L.view(), a, b, partials);
-  else RMG_LAUNCH(k_dot_nodes<1>, dim3(nb), dim3(kBlock), 0, st, L.view(), a, b, partials);
+  const int64_t nb = reduction_blocks(L, kDescsPerBlock), ngb = L.ngroups > 0 ? cdiv(L.ngroups, kBlock) : 0;
+  if (L.ndof == 3)
+    RMG_LAUNCH(k_dot<3>, dim3(nb + ngb), dim3(kBlock), 0, st, L.view(), (int)nb, L.d_gptr.as<int64_t>(),
+               L.d_gcopy.as<int>(), L.ngroups, a, b, partials);
+  else
+    RMG_LAUNCH(k_dot<1>, dim3(nb + ngb), dim3(kBlock), 0, st, L.view(), (int)nb, L.d_gptr.as<int64_t>(),
+               L.d_gcopy.as<int>(), L.ngroups, a, b, partials);
   LAUNCH_CHECK();
-  return nb + dot_groups(L, a, b, partials + nb, st);
+  return nb + ngb;
 }
 
 constexpr int kReduceThreads = 1024;
 
+__device__ __forceinline__ void cg_scalars(double* s, int mode) {
+  if (mode == 0) {
+    s[kAlpha] = s[kRZ] / s[kPQ];
+  } else if (mode == 1) {
+    s[kBeta] = s[kRZnew] / s[kRZ];
+    s[kRZ] = s[kRZnew];
+  } else if (mode == 2) {
+    s[kBeta] = -s[kAlpha] * s[kZQ] / s[kRZ];
+    s[kRZ] = s[kRZnew];
+  }
+}
+
 __global__ __launch_bounds__(kReduceThreads) void k_reduce(const double* __restrict__ partials, int64_t n,
-                                                           double* scalars, int slot) {
+                                                           double* scalars, int slot, int post) {
   // eight strided sums per thread, so that eight loads are in flight
   double sj[8] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
   int64_t i = threadIdx.x;
@@ -150,11 +180,14 @@ __global__ __launch_bounds__(kReduceThreads) void k_reduce(const double* __restr
     if ((int)threadIdx.x < w) sm[threadIdx.x] += sm[threadIdx.x + w];
     __syncthreads();
   }
-  if (threadIdx.x == 0) scalars[slot] = sm[0];
+  if (threadIdx.x == 0) {
+    scalars[slot] = sm[0];
+    cg_scalars(scalars, post);
+  }
 }
 
-void launch_reduce(const double* partials, int64_t n, double* scalars, int slot, hipStream_t st) {
-  RMG_LAUNCH(k_reduce, dim3(1), dim3(kReduceThreads), 0, st, partials, n, scalars, slot);
+void launch_reduce(const double* partials, int64_t n, double* scalars, int slot, hipStream_t st, int post) {
+  RMG_LAUNCH(k_reduce, dim3(1), dim3(kReduceThreads), 0, st, partials, n, scalars, slot, post);
   LAUNCH_CHECK();
 }
 
@@ -438,17 +471,8 @@ __device__ __forceinline__ double pweight(const double* __restrict__ pw, const R
 // by multiplicity), per dof.  Coarse Dirichlet nodes receive nothing (free fine nodes do not
 // interpolate from them).
 template <int DIM, int NDOF, class V>
-__global__ __launch_bounds__(kBlock) void k_restrict(LevelView F, LevelView C, const V* __restrict__ r,
-                                                     V* __restrict__ w) {
-  const BlockDesc bd = C.blocks[blockIdx.x];
-  const RegionGeo RC = C.regs[bd.region];
-  const RegionGeo RF = F.regs[bd.region];
-  const int li = bd.start + (int)threadIdx.x;
-  if (li >= RC.n) return;
-  int X, Y, Z;
-  decompose(RC, li, X, Y, Z);
-  const int64_t gi = RC.off + li;
-  V acc[NDOF];
+__device__ __forceinline__ void restrict_node(const LevelView& C, const RegionGeo& RC, const RegionGeo& RF, int X, int Y,
+                                              int Z, const V* __restrict__ r, V (&acc)[NDOF]) {
 #pragma unroll
   for (int a = 0; a < NDOF; ++a) acc[a] = (V)0;
   if (!is_dirichlet(C, RC.ox + X, RC.oy + Y, RC.oz + Z)) {
@@ -461,6 +485,8 @@ __global__ __launch_bounds__(kBlock) void k_restrict(LevelView F, LevelView C, c
     double wxs[5];
 #pragma unroll
     for (int t = 0; t < 5; ++t) wxs[t] = tap(t - 2, mxl, mxr);
+    // the fine nodes outside the spans are loaded from the nearest node of the box and not summed, so
+    // a plane's loads are all in flight
     const int tzlo = DIM == 3 ? -2 : 0, tzhi = DIM == 3 ? 2 : 0;
 #pragma unroll 1
     for (int tz = tzlo; tz <= tzhi; ++tz) {
@@ -468,28 +494,106 @@ __global__ __launch_bounds__(kBlock) void k_restrict(LevelView F, LevelView C, c
       if ((unsigned)fz >= (unsigned)RF.ez) continue;
       const double wz = DIM == 3 ? tap(tz, mzl, mzr) : 1.0;
       if (wz == 0.0) continue;
+      V v[5][5][NDOF];
+#pragma unroll
       for (int ty = -2; ty <= 2; ++ty) {
-        const int fy = py + ty;
-        if ((unsigned)fy >= (unsigned)RF.ey) continue;
-        const double wy = tap(ty, myl, myr);
-        if (wy == 0.0) continue;
-        const double wzy = wz * wy;
-        const int base = (fz * RF.ey + fy) * RF.ex;
+        const int base = (fz * RF.ey + min(max(py + ty, 0), RF.ey - 1)) * RF.ex;
 #pragma unroll
         for (int tx = -2; tx <= 2; ++tx) {
-          const int fx = px + tx;
-          if ((unsigned)fx >= (unsigned)RF.ex) continue;
+          const int fx = min(max(px + tx, 0), RF.ex - 1);
+#pragma unroll
+          for (int a = 0; a < NDOF; ++a) v[ty + 2][tx + 2][a] = rr[(int64_t)(base + fx) * NDOF + a];
+        }
+      }
+#pragma unroll
+      for (int ty = -2; ty <= 2; ++ty) {
+        const double wy = tap(ty, myl, myr);
+        const bool rok = (unsigned)(py + ty) < (unsigned)RF.ey && wy != 0.0;
+        const double wzy = wz * wy;
+#pragma unroll
+        for (int tx = -2; tx <= 2; ++tx) {
           const double wx = wxs[tx + 2];
-          if (wx == 0.0) continue;
+          const bool ok = rok && (unsigned)(px + tx) < (unsigned)RF.ex && wx != 0.0;
           const V wt = (V)(wzy * wx);
 #pragma unroll
-          for (int a = 0; a < NDOF; ++a) acc[a] += wt * rr[(int64_t)(base + fx) * NDOF + a];
+          for (int a = 0; a < NDOF; ++a) {
+            const V t = acc[a] + wt * v[ty + 2][tx + 2][a];
+            acc[a] = ok ? t : acc[a];
+          }
         }
       }
     }
   }
+}
+
+template <int DIM, int NDOF, class V>
+__global__ __launch_bounds__(kBlock) void k_restrict(LevelView F, LevelView C, const V* __restrict__ r,
+                                                     V* __restrict__ w) {
+  const BlockDesc bd = C.blocks[blockIdx.x];
+  const RegionGeo RC = C.regs[bd.region];
+  const RegionGeo RF = F.regs[bd.region];
+  const int li = bd.start + (int)threadIdx.x;
+  if (li >= RC.n) return;
+  int X, Y, Z;
+  decompose(RC, li, X, Y, Z);
+  V acc[NDOF];
+  restrict_node<DIM, NDOF, V>(C, RC, RF, X, Y, Z, r, acc);
+  const int64_t gi = RC.off + li;
 #pragma unroll
   for (int a = 0; a < NDOF; ++a) w[gi * NDOF + a] = acc[a];
+}
+
+// The same on a small coarse level with its interface sum and, with u, the coarse zero-guess start
+// u = c0 dinv w: one launch for three.  Blocks from nb on take the interface copies, one per thread,
+// and sum a group's restrictions in ascending region order, as k_iface_sum.
+template <int DIM, int NDOF, class V>
+__global__ __launch_bounds__(kBlock) void k_restrict_all(LevelView F, LevelView C, CopyView G, int nb,
+                                                         const V* __restrict__ r, V* __restrict__ w,
+                                                         const V* __restrict__ dinv, V c0, V* __restrict__ u) {
+  __shared__ V part[kBlock * NDOF];
+  V sum[NDOF];
+  int64_t gi = -1;
+  if ((int)blockIdx.x < nb) {
+    const BlockDesc bd = C.blocks[blockIdx.x];
+    const RegionGeo RC = C.regs[bd.region];
+    const int li = bd.start + (int)threadIdx.x;
+    if (li < RC.n) {
+      int X, Y, Z;
+      decompose(RC, li, X, Y, Z);
+      if (!is_shared(C, RC, X, Y, Z)) {
+        gi = RC.off + li;
+        restrict_node<DIM, NDOF, V>(C, RC, F.regs[bd.region], X, Y, Z, r, sum);
+      }
+    }
+  } else {
+    const int c0i = G.start[blockIdx.x - nb], cnt = G.start[blockIdx.x - nb + 1] - c0i, t = threadIdx.x;
+    int4 ci = make_int4(0, 0, 0, 0);
+    if (t < cnt) {
+      ci = G.info[c0i + t];
+      const RegionGeo RC = C.regs[ci.y];
+      int X, Y, Z;
+      decompose(RC, (int)(ci.x - RC.off), X, Y, Z);
+      restrict_node<DIM, NDOF, V>(C, RC, F.regs[ci.y], X, Y, Z, r, sum);
+#pragma unroll
+      for (int a = 0; a < NDOF; ++a) part[t * NDOF + a] = sum[a];
+    }
+    __syncthreads();
+    if (t < cnt) {
+      gi = ci.x;
+#pragma unroll
+      for (int a = 0; a < NDOF; ++a) {
+        V s = (V)0;
+        for (int k = ci.z; k < ci.z + ci.w; ++k) s += part[k * NDOF + a];
+        sum[a] = s;
+      }
+    }
+  }
+  if (gi < 0) return;
+#pragma unroll
+  for (int a = 0; a < NDOF; ++a) {
+    w[gi * NDOF + a] = sum[a];
+    if (u) u[gi * NDOF + a] = c0 * (dinv[gi * NDOF + a] * sum[a]);
+  }
 }
 
 // The same restriction by rows and planes (tiles of make_transfer_tiles): a block owns whole
@@ -678,8 +782,24 @@ __global__ __launch_bounds__(kBlock) void k_restrict_rw(LevelView F, LevelView C
 }
 
 template <int NDOF, class V>
-static void restrict_t(const Level& F, const Level& C, const V* r, V* w, hipStream_t st) {
+static bool restrict_t(const Level& F, const Level& C, const V* r, V* w, hipStream_t st, const CoarseStart* start) {
   const double* pw = F.pw.as<double>();
+  // Small coarse levels: restriction, interface sum and zero-guess start in one launch.  Against the
+  // rows-and-planes kernel, k_iface_sum and k_cheb_zero: 64 regions of 10^3 coarse nodes 16.3 + 6.9 + 4.8
+  // and 26.4 us, 85,000 ragged 17.6 + 5.6 + 3.8 and 23.9 us, 6,000 ragged 14.1 + 5.0 + 2.2 and 12.8 us.
+  if (!pw && C.fused_groups() && (C.ngroups == 0 || C.ncopyblk > 0)) {
+    const V* dinv = start ? static_cast<const V*>(start->dinv) : nullptr;
+    V* u = start ? static_cast<V*>(start->u) : nullptr;
+    const V c0 = start ? (V)start->c : (V)0;
+    const int nb = (int)C.blocks.size();
+    const dim3 g(nb + C.ncopyblk), b(kBlock);
+    if (F.dim == 3)
+      RMG_LAUNCH((k_restrict_all<3, NDOF, V>), g, b, 0, st, F.view(), C.view(), C.copies(), nb, r, w, dinv, c0, u);
+    else
+      RMG_LAUNCH((k_restrict_all<2, NDOF, V>), g, b, 0, st, F.view(), C.view(), C.copies(), nb, r, w, dinv, c0, u);
+    LAUNCH_CHECK();
+    return u != nullptr;
+  }
   if (!pw && !F.rtiles.empty()) {
     const dim3 g(F.rtiles.size()), b(kBlock);
     RMG_REQUIRE(F.rtile_vals <= (int64_t)kXferStagePerThread * kBlock, RMG_ERR_ARG,
@@ -693,7 +813,7 @@ static void restrict_t(const Level& F, const Level& C, const V* r, V* w, hipStre
                  F.rtile_vals, r, w);
     LAUNCH_CHECK();
     iface_sum_inplace<V>(C, w, st);
-    return;
+    return false;
   }
   const dim3 g(C.blocks.size()), b(kBlock);
   if constexpr (NDOF == 1) {
@@ -702,7 +822,7 @@ static void restrict_t(const Level& F, const Level& C, const V* r, V* w, hipStre
       RMG_LAUNCH((k_restrict_rw<V>), g, b, 0, st, F.view(), C.view(), r, w, F.rw.as<double>());
       LAUNCH_CHECK();
       iface_sum_inplace<V>(C, w, st);
-      return;
+      return false;
     }
   }
   if (F.dim == 3)
@@ -711,16 +831,17 @@ static void restrict_t(const Level& F, const Level& C, const V* r, V* w, hipStre
     RMG_LAUNCH((k_restrict<2, NDOF, V>), g, b, 0, st, F.view(), C.view(), r, w);
   LAUNCH_CHECK();
   iface_sum_inplace<V>(C, w, st);
+  return false;
 }
 
-void launch_restrict(const Level& F, const Level& C, bool lowp, const void* r_scaled, void* w, hipStream_t st) {
+bool launch_restrict(const Level& F, const Level& C, bool lowp, const void* r, void* w, hipStream_t st,
+                     const CoarseStart* start) {
   if (lowp) {
-    if (F.ndof == 3) restrict_t<3, float>(F, C, (const float*)r_scaled, (float*)w, st);
-    else restrict_t<1, float>(F, C, (const float*)r_scaled, (float*)w, st);
-  } else {
-    if (F.ndof == 3) restrict_t<3, double>(F, C, (const double*)r_scaled, (double*)w, st);
-    else restrict_t<1, double>(F, C, (const double*)r_scaled, (double*)w, st);
+    if (F.ndof == 3) return restrict_t<3, float>(F, C, (const float*)r, (float*)w, st, start);
+    return restrict_t<1, float>(F, C, (const float*)r, (float*)w, st, start);
   }
+  if (F.ndof == 3) return restrict_t<3, double>(F, C, (const double*)r, (double*)w, st, start);
+  return restrict_t<1, double>(F, C, (const double*)r, (double*)w, st, start);
 }
 
 // One thread per fine node: u += sum_C P_fC ubar_C over the (up to 2 per axis) coarse nodes of
@@ -1294,25 +1415,25 @@ void launch_to_regional(const Level& L, const double* comp, double* reg, hipStre
   LAUNCH_CHECK();
 }
 
-__global__ __launch_bounds__(kBlock) void k_to_composite_nodes(LevelView L, const double* __restrict__ reg,
-                                                               double* __restrict__ comp) {
-  const BlockDesc bd = L.blocks[blockIdx.x];
-  const RegionGeo R = L.regs[bd.region];
-  const int li = bd.start + (int)threadIdx.x;
-  if (li >= R.n) return;
-  int x, y, z;
-  decompose(R, li, x, y, z);
-  if (is_shared(L, R, x, y, z)) return;
-  const int64_t ci = comp_index(L, R.ox + x, R.oy + y, R.oz + z) * L.ndof;
-  for (int a = 0; a < L.ndof; ++a) comp[ci + a] = reg[(R.off + li) * L.ndof + a];
-}
-
-__global__ __launch_bounds__(kBlock) void k_to_composite_groups(const int64_t* __restrict__ gptr,
-                                                                const int* __restrict__ gcopy,
-                                                                const int* __restrict__ gcomp, int64_t ng, int ndof,
-                                                                const double* __restrict__ reg,
-                                                                double* __restrict__ comp, int average) {
-  const int64_t g = (int64_t)blockIdx.x * kBlock + threadIdx.x;
+// The node blocks write the one-region nodes, the blocks from nb on the interface groups.
+__global__ __launch_bounds__(kBlock) void k_to_composite(LevelView L, int nb, const int64_t* __restrict__ gptr,
+                                                         const int* __restrict__ gcopy, const int* __restrict__ gcomp,
+                                                         int64_t ng, const double* __restrict__ reg,
+                                                         double* __restrict__ comp, int average) {
+  const int ndof = L.ndof;
+  if ((int)blockIdx.x < nb) {
+    const BlockDesc bd = L.blocks[blockIdx.x];
+    const RegionGeo R = L.regs[bd.region];
+    const int li = bd.start + (int)threadIdx.x;
+    if (li >= R.n) return;
+    int x, y, z;
+    decompose(R, li, x, y, z);
+    if (is_shared(L, R, x, y, z)) return;
+    const int64_t ci = comp_index(L, R.ox + x, R.oy + y, R.oz + z) * ndof;
+    for (int a = 0; a < ndof; ++a) comp[ci + a] = reg[(R.off + li) * ndof + a];
+    return;
+  }
+  const int64_t g = (int64_t)((int)blockIdx.x - nb) * kBlock + threadIdx.x;
   if (g >= ng) return;
   const int64_t a0 = gptr[g], e = gptr[g + 1];
   for (int a = 0; a < ndof; ++a) {
@@ -1329,14 +1450,10 @@ __global__ __launch_bounds__(kBlock) void k_to_composite_groups(const int64_t* _
 }
 
 void launch_to_composite(const Level& L, const double* reg, double* comp, int average, hipStream_t st) {
-  RMG_LAUNCH(k_to_composite_nodes, dim3(L.blocks.size()), dim3(kBlock), 0, st, L.view(), reg, comp);
+  const int nb = (int)L.blocks.size();
+  RMG_LAUNCH(k_to_composite, dim3(nb + (L.ngroups > 0 ? cdiv(L.ngroups, kBlock) : 0)), dim3(kBlock), 0, st, L.view(),
+             nb, L.d_gptr.as<int64_t>(), L.d_gcopy.as<int>(), L.d_gcomp.as<int>(), L.ngroups, reg, comp, average);
   LAUNCH_CHECK();
-  if (L.ngroups > 0) {
-    RMG_LAUNCH(k_to_composite_groups, dim3(cdiv(L.ngroups, kBlock)), dim3(kBlock), 0, st,
-                       L.d_gptr.as<int64_t>(), L.d_gcopy.as<int>(), L.d_gcomp.as<int>(), L.ngroups, L.ndof, reg,
-                       comp, average);
-    LAUNCH_CHECK();
-  }
 }
 
 // ------------------------------------------------------- coarse solve
@@ -1390,9 +1507,51 @@ void launch_coarse_scatter(const Level& L, bool lowp, void* u, hipStream_t st) {
   LAUNCH_CHECK();
 }
 
+// The whole solve in one launch: every block gathers the owner copies of b into LDS, one wavefront per
+// row multiplies (k_gemv's sums) and writes the row's value to all its copies.
+template <class V>
+__global__ __launch_bounds__(256) void k_coarse_solve(int n, int ndof, const double* __restrict__ A,
+                                                      const int* __restrict__ owner, const int* __restrict__ cptr,
+                                                      const int* __restrict__ ccopy, const V* __restrict__ b,
+                                                      V* __restrict__ u) {
+  extern __shared__ double cx[];
+  for (int t = threadIdx.x; t < n; t += 256) {
+    const int i = t / ndof;
+    cx[t] = (double)b[(int64_t)owner[i] * ndof + (t - i * ndof)];
+  }
+  __syncthreads();
+  const int lane = threadIdx.x & 63;
+  const int row = blockIdx.x * 4 + (threadIdx.x >> 6);
+  if (row >= n) return;
+  const double* __restrict__ a = A + (int64_t)row * n;
+  double s = 0.0;
+  for (int j = lane; j < n; j += 64) s += a[j] * cx[j];
+  for (int o = 32; o > 0; o >>= 1) s += __shfl_down(s, o, 64);
+  s = __shfl(s, 0, 64);
+  const int i = row / ndof, e = cptr[i + 1];
+  for (int c = cptr[i] + lane; c < e; c += 64) u[(int64_t)ccopy[c] * ndof + (row - i * ndof)] = (V)s;
+}
+
+// Up to this many unknowns the gathered right-hand side (32 KB) fits every block's LDS beside a second
+// block's.  One launch for three: 288 unknowns 2.1 + 4.1 + 3.1 -> 5.2 us,
+// 2,197 unknowns 4.7 + 19.8 + 4.7 -> 26.4 us.
+constexpr int kCoarseOneLaunch = 4096;
+
 void launch_coarse_solve(const Level& L, bool lowp, const void* b, void* u, hipStream_t st) {
-  launch_coarse_gather(L, lowp, b, st);
   const int n = L.nc;
+  if (n <= kCoarseOneLaunch) {
+    const dim3 g(cdiv(n, 4)), t(256);
+    const size_t lds = sizeof(double) * (size_t)n;
+    if (lowp)
+      RMG_LAUNCH(k_coarse_solve<float>, g, t, lds, st, n, L.ndof, L.ainv.as<double>(), L.comp_owner.as<int>(),
+                 L.comp_ptr.as<int>(), L.comp_copy.as<int>(), (const float*)b, (float*)u);
+    else
+      RMG_LAUNCH(k_coarse_solve<double>, g, t, lds, st, n, L.ndof, L.ainv.as<double>(), L.comp_owner.as<int>(),
+                 L.comp_ptr.as<int>(), L.comp_copy.as<int>(), (const double*)b, (double*)u);
+    LAUNCH_CHECK();
+    return;
+  }
+  launch_coarse_gather(L, lowp, b, st);
   RMG_LAUNCH(k_gemv, dim3(cdiv(n, 4)), dim3(256), 0, st, n, L.ainv.as<double>(), L.cvec.as<double>(),
                      L.cvec2.as<double>());
   LAUNCH_CHECK();
@@ -2239,7 +2398,8 @@ __global__ __launch_bounds__(kBlock) void k_cg_update(LevelView L, const double*
                                                       const double* __restrict__ p, const double* __restrict__ q,
                                                       double* __restrict__ partials, const double* __restrict__ dinv,
                                                       double c0, double* __restrict__ u0,
-                                                      const double* __restrict__ table, const int* __restrict__ table_ok) {
+                                                      const double* __restrict__ table, const int* __restrict__ table_ok,
+                                                      const int* __restrict__ owners) {
   const double alpha = scalars[kAlpha];
   double c = 0.0;
   for (int j = 0; j < kUpdateDescs; ++j) {
@@ -2252,6 +2412,8 @@ __global__ __launch_bounds__(kBlock) void k_cg_update(LevelView L, const double*
       int xx, yy, zz;
       decompose(R, li, xx, yy, zz);
       const bool own = !is_shared(L, R, xx, yy, zz);
+      bool counts = own;
+      if (owners && !own) counts = owners[R.off + li] != 0;
 #pragma unroll
       for (int a = 0; a < NDOF; ++a) {
         const int64_t gi = (R.off + li) * NDOF + a;
@@ -2270,7 +2432,7 @@ __global__ __launch_bounds__(kBlock) void k_cg_update(LevelView L, const double*
           }
           u0[gi] = c0 * (di * rn);
         }
-        if (own) c += rn * rn;
+        if (counts) c += rn * rn;
       }
     }
   }
@@ -2284,15 +2446,15 @@ int64_t launch_cg_update(const Level& L, double* scalars, double* x, double* r, 
   RMG_REQUIRE(!u0 || (L.ndof == 1 && dinv), RMG_ERR_ARG, "internal: fused zero-guess start needs a scalar level");
   if (L.ndof == 3)
     RMG_LAUNCH(k_cg_update<3>, dim3(nb), dim3(kBlock), 0, st, L.view(), scalars, x, r, p, q, partials, nullptr,
-               0.0, nullptr, nullptr, nullptr);
+               0.0, nullptr, nullptr, nullptr, L.d_owner.as<int>());
   else {
     // the class tables give D~^-1 of the served regions' one-region rows (when dinv is the level's own)
     const bool tab = u0 && dinv == L.dinv.as<double>() && L.npts == 27 && L.class_table.p && L.class_table_ok.p;
     RMG_LAUNCH(k_cg_update<1>, dim3(nb), dim3(kBlock), 0, st, L.view(), scalars, x, r, p, q, partials, dinv, c0,
-               u0, tab ? L.class_table.as<double>() : nullptr, tab ? L.class_table_ok.as<int>() : nullptr);
+               u0, tab ? L.class_table.as<double>() : nullptr, tab ? L.class_table_ok.as<int>() : nullptr, L.d_owner.as<int>());
   }
   LAUNCH_CHECK();
-  return nb + dot_groups(L, r, r, partials + nb, st);
+  return L.d_owner.p ? nb : nb + dot_groups(L, r, r, partials + nb, st);
 }
 
 __global__ void k_cg_direction(int64_t n, const double* __restrict__ scalars, const double* __restrict__ z,
@@ -2305,23 +2467,6 @@ __global__ void k_cg_direction(int64_t n, const double* __restrict__ scalars, co
 
 void launch_cg_direction(int64_t n, double* scalars, const double* z, double* p, hipStream_t st) {
   RMG_LAUNCH(k_cg_direction, dim3(cdiv(n, kBlock)), dim3(kBlock), 0, st, n, scalars, z, p);
-  LAUNCH_CHECK();
-}
-
-__global__ void k_cg_scalars(double* s, int mode) {
-  if (mode == 0) {
-    s[kAlpha] = s[kRZ] / s[kPQ];
-  } else if (mode == 1) {
-    s[kBeta] = s[kRZnew] / s[kRZ];
-    s[kRZ] = s[kRZnew];
-  } else {
-    s[kBeta] = -s[kAlpha] * s[kZQ] / s[kRZ];
-    s[kRZ] = s[kRZnew];
-  }
-}
-
-void launch_cg_scalars(double* scalars, int mode, hipStream_t st) {
-  RMG_LAUNCH(k_cg_scalars, dim3(1), dim3(1), 0, st, scalars, mode);
   LAUNCH_CHECK();
 }
 

@@ -156,14 +156,93 @@ __device__ __forceinline__ auto coefv(const C* __restrict__ cf, const float* __r
 // regions whose flag in table_ok is set: a node's 27 couplings (3 x 3 blocks on 3-dof levels) are
 // its class's (the values the half stencil applies, bit for bit), read from the small table
 // instead of from its own and its neighbours' records.
+template <int NPTS, int NDOF, class V, class C, bool SYM>
+__device__ __forceinline__ void node_product(const C* __restrict__ coef, const float* __restrict__ centre,
+                                             const V* __restrict__ xv, const V* __restrict__ table,
+                                             const int* __restrict__ table_ok, int region, const RegionGeo& R, int li,
+                                             int x, int y, int z, bool inner, V (&acc)[NDOF]) {
+  constexpr int NB = NDOF * NDOF;
+  constexpr int NCOEF = SYM ? kSymPts * NB : NPTS * NB;
+  constexpr bool kTab = NPTS == 27 && SYM;
+  const int64_t gi = R.off + li;
+  const V* __restrict__ xr = xv + R.off * NDOF;
+  const C* __restrict__ cf = coef + coef_index(gi, 0, NCOEF);
+  const int sy = R.ex, sz = R.ex * R.ey;
+  const bool tabbed = kTab && table && table_ok[region];
+  const V* __restrict__ tc =
+      tabbed ? table + ((int64_t)region * kClasses +
+                        (axis_class(z, R.ez) * 5 + axis_class(y, R.ey)) * 5 + axis_class(x, R.ex)) * kClassPts * NB
+             : nullptr;
+#pragma unroll
+  for (int a = 0; a < NDOF; ++a) acc[a] = (V)0;
+  // Scalar: a coupling that leaves the box loads from the node itself and its sum is not taken, so
+  // every load is unconditional and many are in flight.
+  auto sum = [&](auto coupling) __attribute__((always_inline)) {
+#pragma unroll
+    for (int s = 0; s < NPTS; ++s) {
+      int dx, dy, dz;
+      stencil_offset<NPTS>(s, dx, dy, dz);
+      const bool ok = inner || ((unsigned)(x + dx) < (unsigned)R.ex && (unsigned)(y + dy) < (unsigned)R.ey &&
+                                (unsigned)(z + dz) < (unsigned)R.ez);
+      if (NDOF == 3 && !ok) continue;  // (a block is nine loads already; all 27 in flight would spill)
+      const int nb = ok ? li + dx + dy * sy + dz * sz : li;
+#pragma unroll
+      for (int a = 0; a < NDOF; ++a) {
+        V t = acc[a];
+#pragma unroll
+        for (int b = 0; b < NDOF; ++b) t += coupling(s, a, b, nb) * xr[nb * NDOF + b];
+        acc[a] = ok ? t : acc[a];
+      }
+    }
+  };
+  if (kTab && tabbed) {
+    sum([&](int s, int a, int b, int) { return tc[(s * NDOF + a) * NDOF + b]; });
+  } else if constexpr (SYM) {
+    sum([&](int s, int a, int b, int nb) -> V {
+      if (s > 13) return (V)CoefLoad<C>::get(cf + ((s - 13) * NB + a * NDOF + b) * kTile);
+      if (s < 13)
+        return (V)CoefLoad<C>::get(coef + coef_index(R.off + nb, 0, NCOEF) + ((13 - s) * NB + b * NDOF + a) * kTile);
+      if (sizeof(C) == 2) return (V)centre[gi * NB + a * NDOF + b];
+      return (V)CoefLoad<C>::get(cf + (a * NDOF + b) * kTile);
+    });
+  } else {
+    sum([&](int s, int a, int b, int) { return (V)coefv<NPTS, NDOF, C>(cf, centre, gi, s, a, b); });
+  }
+}
+
+template <int NPTS>
+__device__ __forceinline__ bool inner_node(const RegionGeo& R, int x, int y, int z) {
+  return x > 0 && x < R.ex - 1 && y > 0 && y < R.ey - 1 && (NPTS != 27 || (z > 0 && z < R.ez - 1));
+}
+
+// Writes a one-region node's result; returns its contribution to the op's inner product.
+template <int NDOF, StencilOp OP, bool DOT, class V>
+__device__ __forceinline__ double finish_node(const OpP<V>& p, int64_t gi, const V (&acc)[NDOF], const V* xs) {
+  double contrib = 0.0;
+  if constexpr (NDOF == 3 && (OP == StencilOp::Cheb || OP == StencilOp::ChebFirst)) {
+    if (p.dinv9) {
+      V xv[3], dold[3], out[3], dd[3];
+#pragma unroll
+      for (int a = 0; a < 3; ++a) {
+        xv[a] = xs[a];
+        dold[a] = OP == StencilOp::Cheb ? prev_correction(p, xv[a], p.out[gi * 3 + a]) : xv[a];
+      }
+      contrib += finish_block3_value<OP, DOT, V>(p, gi, acc, xv, dold, out, dd);
+#pragma unroll
+      for (int a = 0; a < 3; ++a) p.out[gi * 3 + a] = out[a];
+      return contrib;
+    }
+  }
+#pragma unroll
+  for (int a = 0; a < NDOF; ++a) contrib += finish<OP, DOT, V>(p, gi * NDOF + a, acc[a], 1, xs[a]);
+  return contrib;
+}
+
 template <int NPTS, int NDOF, class V, class C, StencilOp OP, bool DOT, bool SYM>
 __global__ __launch_bounds__(kBlock) void k_stencil(LevelView L, const C* __restrict__ coef,
                                                     const float* __restrict__ centre, OpP<V> p,
                                                     double* __restrict__ partials, const V* __restrict__ table,
                                                     const int* __restrict__ table_ok) {
-  constexpr int NB = NDOF * NDOF;
-  constexpr int NCOEF = SYM ? kSymPts * NB : NPTS * NB;
-  constexpr bool kTab = NPTS == 27 && SYM;
   // every XCD runs a contiguous run of node blocks, so a block finds the records of the plane below
   // (its lower couplings on symmetric levels) in its own XCD's L2; its partial sum goes to the
   // node block's slot, as without the mapping
@@ -176,88 +255,110 @@ __global__ __launch_bounds__(kBlock) void k_stencil(LevelView L, const C* __rest
     int x, y, z;
     decompose(R, li, x, y, z);
     const int64_t gi = R.off + li;
-    const V* __restrict__ xr = p.x + R.off * NDOF;
-    const C* __restrict__ cf = coef + coef_index(gi, 0, NCOEF);
-    const int sy = R.ex, sz = R.ex * R.ey;
-    const bool inner = x > 0 && x < R.ex - 1 && y > 0 && y < R.ey - 1 && (NPTS != 27 || (z > 0 && z < R.ez - 1));
-    const bool tabbed = kTab && table && table_ok[bd.region];  // uniform over the block (one region)
-    const V* __restrict__ tc =
-        tabbed ? table + ((int64_t)bd.region * kClasses +
-                          (axis_class(z, R.ez) * 5 + axis_class(y, R.ey)) * 5 + axis_class(x, R.ex)) * kClassPts * NB
-               : nullptr;
+    const V* __restrict__ xs = p.x + gi * NDOF;
+    const bool inner = inner_node<NPTS>(R, x, y, z);
     V acc[NDOF];
-#pragma unroll
-    for (int a = 0; a < NDOF; ++a) acc[a] = (V)0;
-#pragma unroll
-    for (int s = 0; s < NPTS; ++s) {
-      int dx, dy, dz;
-      stencil_offset<NPTS>(s, dx, dy, dz);
-      const bool ok = inner || ((unsigned)(x + dx) < (unsigned)R.ex && (unsigned)(y + dy) < (unsigned)R.ey &&
-                                (unsigned)(z + dz) < (unsigned)R.ez);
-      if (ok) {
-        const int nb = li + dx + dy * sy + dz * sz;
-        if constexpr (SYM) {
-          if (kTab && tabbed) {
-#pragma unroll
-            for (int a = 0; a < NDOF; ++a)
-#pragma unroll
-              for (int b = 0; b < NDOF; ++b) acc[a] += tc[(s * NDOF + a) * NDOF + b] * xr[nb * NDOF + b];
-          } else if (s >= 13) {
-#pragma unroll
-            for (int a = 0; a < NDOF; ++a)
-#pragma unroll
-              for (int b = 0; b < NDOF; ++b) {
-                V c;
-                if (sizeof(C) == 2 && s == 13) c = (V)centre[gi * NB + a * NDOF + b];
-                else c = (V)CoefLoad<C>::get(cf + ((s - 13) * NB + a * NDOF + b) * kTile);
-                acc[a] += c * xr[nb * NDOF + b];
-              }
-          } else {
-            const C* __restrict__ cn = coef + coef_index(R.off + nb, 0, NCOEF);
-#pragma unroll
-            for (int a = 0; a < NDOF; ++a)
-#pragma unroll
-              for (int b = 0; b < NDOF; ++b)
-                acc[a] += (V)CoefLoad<C>::get(cn + ((13 - s) * NB + b * NDOF + a) * kTile) * xr[nb * NDOF + b];
-          }
-        } else {
-#pragma unroll
-          for (int a = 0; a < NDOF; ++a)
-#pragma unroll
-            for (int b = 0; b < NDOF; ++b)
-              acc[a] += (V)coefv<NPTS, NDOF, C>(cf, centre, gi, s, a, b) * xr[nb * NDOF + b];
-        }
-      }
-    }
+    node_product<NPTS, NDOF, V, C, SYM>(coef, centre, p.x, table, table_ok, bd.region, R, li, x, y, z, inner, acc);
     if (!inner && is_shared(L, R, x, y, z)) {
 #pragma unroll
       for (int a = 0; a < NDOF; ++a)  // summed over copies by k_iface
-        write_partial<OP, V>(p, gi * NDOF + a, acc[a], xr[li * NDOF + a], p.out[gi * NDOF + a]);
+        write_partial<OP, V>(p, gi * NDOF + a, acc[a], xs[a], p.out[gi * NDOF + a]);
     } else {
-      bool block = false;
-      if constexpr (NDOF == 3 && (OP == StencilOp::Cheb || OP == StencilOp::ChebFirst)) {
-        if (p.dinv9) {
-          V xs[3], dold[3], out[3], dd[3];
-#pragma unroll
-          for (int a = 0; a < 3; ++a) {
-            xs[a] = xr[li * 3 + a];
-            dold[a] = OP == StencilOp::Cheb ? prev_correction(p, xs[a], p.out[gi * 3 + a]) : xs[a];
-          }
-          contrib += finish_block3_value<OP, DOT, V>(p, gi, acc, xs, dold, out, dd);
-#pragma unroll
-          for (int a = 0; a < 3; ++a) p.out[gi * 3 + a] = out[a];
-          block = true;
-        }
-      }
-      if (!block) {
-#pragma unroll
-        for (int a = 0; a < NDOF; ++a) contrib += finish<OP, DOT, V>(p, gi * NDOF + a, acc[a], 1, xr[li * NDOF + a]);
-      }
+      contrib = finish_node<NDOF, OP, DOT, V>(p, gi, acc, xs);
     }
   }
   if constexpr (DOT || OP == StencilOp::CgQ) {
     const double s = block_sum(contrib);
     if (threadIdx.x == 0) partials[blk] = s;
+  }
+}
+
+// The same on a small level with the interface groups in the same launch: the node blocks skip the
+// shared nodes, and the blocks from nb on take their copies, one per thread with a group's copies in
+// one block.  A copy's product goes through LDS; every copy then sums its group's in k_iface's order,
+// finishes the node from the first copy's values as k_iface does, and writes its own entry, so the
+// results are k_iface's bit for bit.  Such a level is bound by the launch and by one chain of dependent
+// loads (descriptor, region, couplings); the interface kernel was a second launch with a second chain.
+// (Stencil and interface kernel before, this kernel now, an FP64 27-point Chebyshev step in ragged
+// regions: 6,000 nodes 8.5 + 5.6 and 5.8 us, 85,000 nodes 9.4 + 5.8 and 9.2 us.)
+template <int NPTS, int NDOF, class V, class C, StencilOp OP, bool DOT, bool SYM>
+__global__ __launch_bounds__(kBlock) void k_stencil_fused(LevelView L, CopyView G, int nb, const C* __restrict__ coef,
+                                                          const float* __restrict__ centre, OpP<V> p,
+                                                          double* __restrict__ partials, const V* __restrict__ table,
+                                                          const int* __restrict__ table_ok) {
+  __shared__ V part[kBlock * NDOF];
+  double contrib = 0.0;
+  const int t = threadIdx.x;
+  if ((int)blockIdx.x < nb) {
+    const BlockDesc bd = L.blocks[blockIdx.x];
+    const RegionGeo R = L.regs[bd.region];
+    const int li = bd.start + t;
+    if (li < R.n) {
+      int x, y, z;
+      decompose(R, li, x, y, z);
+      const bool inner = inner_node<NPTS>(R, x, y, z);
+      if (inner || !is_shared(L, R, x, y, z)) {
+        const int64_t gi = R.off + li;
+        V acc[NDOF];
+        node_product<NPTS, NDOF, V, C, SYM>(coef, centre, p.x, table, table_ok, bd.region, R, li, x, y, z, inner, acc);
+        contrib = finish_node<NDOF, OP, DOT, V>(p, gi, acc, p.x + gi * NDOF);
+      }
+    }
+  } else {
+    const int first = G.start[blockIdx.x - nb], cnt = G.start[blockIdx.x - nb + 1] - first;
+    int4 ci = make_int4(0, 0, 0, 0);
+    int64_t n0 = 0;  // the group's first copy
+    V uprev[NDOF];
+#pragma unroll
+    for (int a = 0; a < NDOF; ++a) uprev[a] = (V)0;
+    if (t < cnt) {
+      ci = G.info[first + t];
+      n0 = G.info[first + ci.z].x;
+      const RegionGeo R = L.regs[ci.y];
+      const int li = (int)(ci.x - R.off);
+      int x, y, z;
+      decompose(R, li, x, y, z);
+      V acc[NDOF];
+      node_product<NPTS, NDOF, V, C, SYM>(coef, centre, p.x, table, table_ok, ci.y, R, li, x, y, z, false, acc);
+#pragma unroll
+      for (int a = 0; a < NDOF; ++a) {
+        part[t * NDOF + a] = acc[a];
+        if constexpr (OP == StencilOp::Cheb) uprev[a] = p.out[n0 * NDOF + a];  // before the first copy writes it
+      }
+    }
+    __syncthreads();
+    if (t < cnt) {
+      V z[NDOF], xs[NDOF], dold[NDOF], out[NDOF], dd[NDOF];
+#pragma unroll
+      for (int a = 0; a < NDOF; ++a) {
+        V s = (V)0;
+        for (int k = ci.z; k < ci.z + ci.w; ++k) s += part[k * NDOF + a];
+        z[a] = s;
+        xs[a] = p.x[n0 * NDOF + a];
+        dold[a] = OP == StencilOp::Cheb ? prev_correction(p, xs[a], uprev[a]) : xs[a];
+        dd[a] = (V)0;
+      }
+      bool block = false;
+      double c = 0.0;
+      if constexpr (NDOF == 3 && (OP == StencilOp::Cheb || OP == StencilOp::ChebFirst)) {
+        if (p.dinv9) {
+          c = finish_block3_value<OP, DOT, V>(p, n0, z, xs, dold, out, dd);
+          block = true;
+        }
+      }
+      if (!block) {
+#pragma unroll
+        for (int a = 0; a < NDOF; ++a)
+          c += finish_value<OP, DOT, V>(p, n0 * NDOF + a, z[a], ci.w, xs[a], (V)0, dold[a], out[a], dd[a]);
+      }
+#pragma unroll
+      for (int a = 0; a < NDOF; ++a) p.out[(int64_t)ci.x * NDOF + a] = out[a];
+      if (t == ci.z) contrib = c;  // a shared node counts once, by its first copy
+    }
+  }
+  if constexpr (DOT || OP == StencilOp::CgQ) {
+    const double s = block_sum(contrib);
+    if (t == 0) partials[blockIdx.x] = s;
   }
 }
 
@@ -1248,6 +1349,10 @@ static int64_t run(const Level& L, const StencilArgs& a, hipStream_t st) {
   const bool tiled = NPTS == 27 && ((NDOF == 1 && (L.use_tiles || split)) || split3);
   const int ntiles = (int)L.tiles.size();
   const int grid3 = (L.tile_grid > 0 && L.tile_grid < ntiles) ? L.tile_grid : ntiles;
+  // the interface groups in the node blocks' launch; unbatched levels (one launch per region, then the
+  // interface kernel) only where a sum is taken, so that it is grouped as the batched one
+  constexpr bool kSums = DOT || OP == StencilOp::CgQ;
+  const bool fused = !tiled && L.n <= kFuseNodes && L.ncopyblk > 0 && (kSums || !L.per_region);
   int64_t nparts = grid3;  // partial sums written by the tiled launches
   if (a.ev0) RMG_HIP(hipEventRecord(a.ev0, st));
   if constexpr (NPTS == 27 && NDOF == 3) {
@@ -1305,6 +1410,38 @@ static int64_t run(const Level& L, const StencilArgs& a, hipStream_t st) {
   }
   if (!tiled) {
     const C* symc = static_cast<const C*>(a.lowp ? L.coef_lo_sym.p : L.coef_sym.p);
+    if (fused) {
+      // nb node blocks of vk and nc copy blocks
+      auto blocks = [&](const LevelView& vk, int nb, int nc, double* part) {
+        const dim3 g(nb + nc), t(kBlock);
+        if constexpr (NPTS == 27) {
+          if (symc) {
+            RMG_LAUNCH((k_stencil_fused<NPTS, NDOF, V, C, OP, DOT, true>), g, t, 0, st, vk, L.copies(), nb, symc,
+                       centre, p, part, table, table_ok);
+            return;
+          }
+        }
+        RMG_LAUNCH((k_stencil_fused<NPTS, NDOF, V, C, OP, DOT, false>), g, t, 0, st, vk, L.copies(), nb, coef, centre,
+                   p, part, (const V*)nullptr, (const int*)nullptr);
+      };
+      const int nb = (int)L.blocks.size();
+      if (L.per_region) {
+        for (int k = 0; k < L.nreg; ++k) {
+          const int b0 = L.region_block[k], n = L.region_block[k + 1] - b0;
+          if (n == 0) continue;
+          LevelView vk = v;
+          vk.blocks = v.blocks + b0;
+          vk.nblocks = n;
+          blocks(vk, n, 0, a.partials ? a.partials + b0 : nullptr);
+        }
+        blocks(v, 0, L.ncopyblk, a.partials ? a.partials + nb : nullptr);
+      } else {
+        blocks(v, nb, L.ncopyblk, a.partials);
+      }
+      LAUNCH_CHECK();
+      if (a.ev1) RMG_HIP(hipEventRecord(a.ev1, st));
+      return kSums ? (int64_t)nb + L.ncopyblk : 0;
+    }
     auto node = [&](const LevelView& vk, int nblocks, double* part) {
       if constexpr (NPTS == 27) {
         if (symc) {

@@ -550,6 +550,29 @@ void build_tables(Level& L) {
     gptr2.push_back((int64_t)gcopy2.size());
     gcomp2.push_back(gcomp[g]);
   }
+  L.d_copies.release();
+  L.d_copy_start.release();
+  L.d_owner.release();
+  L.ncopyblk = 0;
+  if (ng > 0 && L.n <= kFuseNodes && most <= kBlock) {
+    std::vector<int4> info(gcopy2.size());
+    std::vector<int32_t> start(1, 0), owner(L.n, 0);
+    for (int64_t g = 0; g < ng; ++g) {
+      const int32_t a0 = (int32_t)gptr2[g], m = (int32_t)(gptr2[g + 1] - gptr2[g]);
+      if (a0 + m - start.back() > kBlock) start.push_back(a0);
+      owner[gcopy2[a0]] = 1;
+      for (int32_t c = a0; c < a0 + m; ++c) {
+        const auto it = std::upper_bound(L.regs.begin(), L.regs.end(), (int64_t)gcopy2[c],
+                                         [](int64_t i, const RegionGeo& R) { return i < R.off; });
+        info[c] = make_int4(gcopy2[c], (int)(it - L.regs.begin()) - 1, a0 - start.back(), m);
+      }
+    }
+    start.push_back((int32_t)gcopy2.size());
+    L.ncopyblk = (int)start.size() - 1;
+    upload(L.d_copies, info);
+    upload(L.d_copy_start, start);
+    upload(L.d_owner, owner);
+  }
   L.ngroups = ng;
   L.ngroups2 = 0;
   while (L.ngroups2 < ng && gptr2[L.ngroups2 + 1] - gptr2[L.ngroups2] == 2) ++L.ngroups2;
@@ -736,6 +759,19 @@ void build_coarse_solver(rmg_handle* h, Level& L) {
           nranks = std::max(nranks, copies[i]);
         }
   }
+  // the copies of every composite node (the solve writes its result to all of them)
+  std::vector<int32_t> cptr(L.ncomp + 1, 0), ccopy(L.n);
+  for (int64_t i = 0; i < L.ncomp; ++i) cptr[i + 1] = cptr[i] + copies[i];
+  for (int k = 0; k < L.nreg; ++k) {
+    const RegionGeo& R = L.regs[k];
+    for (int li = 0; li < R.n; ++li) {
+      const int x = li % R.ex, y = li / R.ex % R.ey, z = li / (R.ex * R.ey);
+      const int64_t i = ((int64_t)(R.oz + z) * L.comp[1] + (R.oy + y)) * L.comp[0] + (R.ox + x);
+      ccopy[cptr[i] + rank[R.off + li]] = (int32_t)(R.off + li);
+    }
+  }
+  upload(L.comp_ptr, cptr);
+  upload(L.comp_copy, ccopy);
   DBuf drank;
   drank.alloc(sizeof(int32_t) * rank.size());
   RMG_HIP(hipMemcpyAsync(drank.p, rank.data(), sizeof(int32_t) * rank.size(), hipMemcpyHostToDevice, st));

@@ -41,9 +41,10 @@ KernelTimer::~KernelTimer() {
 
 static int64_t partial_capacity(const Level& L) {
   // node blocks, 2.5D tiles or the region-table split (whole-region table tiles, other regions'
-  // tiles), then the interface groups
+  // tiles), then the interface groups or, on small levels, their copies
   const int64_t split = (int64_t)(L.table_tiles.size() + std::max(L.tiles.size(), L.elem_tiles.size()));
-  return std::max({(int64_t)L.blocks.size(), (int64_t)L.tiles.size(), split}) + (L.ngroups + kBlock - 1) / kBlock + 16;
+  return std::max({(int64_t)L.blocks.size(), (int64_t)L.tiles.size(), split}) +
+         std::max((L.ngroups + kBlock - 1) / kBlock, (int64_t)L.ncopyblk) + 16;
 }
 
 static double* scal(rmg_handle* h) { return h->scalars.as<double>(); }
@@ -54,9 +55,9 @@ static void read_scalars(rmg_handle* h) {
   RMG_HIP(hipStreamSynchronize(h->stream));
 }
 
-static void dot(rmg_handle* h, const Level& L, const double* a, const double* b, int slot) {
+static void dot(rmg_handle* h, const Level& L, const double* a, const double* b, int slot, int post = -1) {
   const int64_t np = launch_dot(L, a, b, h->partials.as<double>(), h->stream);
-  launch_reduce(h->partials.as<double>(), np, scal(h), slot, h->stream);
+  launch_reduce(h->partials.as<double>(), np, scal(h), slot, h->stream, post);
 }
 
 // lambda_max(D~^-1 Psi^T Psi [[A]]) by power iteration: x <- x0/|x0|; y = D~^-1 A x,
@@ -712,7 +713,8 @@ void mg_solve(rmg_handle* h, const double* b, double* x, double rtol, int maxit,
   }
 }
 
-void vcycle(rmg_handle* h, int level, bool lowp, const void* b, void* z, int dot_slot, bool start_ready) {
+void vcycle(rmg_handle* h, int level, bool lowp, const void* b, void* z, int dot_slot, bool start_ready,
+            int dot_post) {
   const int nl = (int)h->levels.size();
   Level& L = *h->levels[level];
   hipStream_t st = h->stream;
@@ -769,9 +771,11 @@ void vcycle(rmg_handle* h, int level, bool lowp, const void* b, void* z, int dot
   launch_stencil_op(L, a, st);
   Level& C = *h->levels[level + 1];
   const Bufs BC = bufs(C, lowp);
-  launch_restrict(L, C, lowp, B.r, BC.b, st);
+  // a small coarse level's zero-guess start comes with the restriction
+  const CoarseStart cs{BC.dinv, level + 1 < nl - 1 ? C.cheb_c2[0] : 0.0, BC.u};
+  const bool started = launch_restrict(L, C, lowp, B.r, BC.b, st, level + 1 < nl - 1 && !BC.dinv9 ? &cs : nullptr);
   level_span_end(h, span);
-  vcycle(h, level + 1, lowp, BC.b, BC.u2);
+  vcycle(h, level + 1, lowp, BC.b, BC.u2, -1, started);
   span = level_span_begin(h, level);
   launch_prolong_add(L, C, lowp, BC.u2, buf[cur], st);
   for (int k = 0; k < K; ++k) {
@@ -779,7 +783,7 @@ void vcycle(rmg_handle* h, int level, bool lowp, const void* b, void* z, int dot
     const bool dot = k == K - 1 && dot_slot >= 0 && !lowp;
     const int64_t np =
         cheb_step(h, L, lowp, k, k == 0 ? ChebKind::Start : ChebKind::Next, b, buf[cur], buf[1 - cur], dot);
-    if (dot) launch_reduce(h->partials.as<double>(), np, scal(h), dot_slot, st);
+    if (dot) launch_reduce(h->partials.as<double>(), np, scal(h), dot_slot, st, dot_post);
     cur = 1 - cur;
   }
   level_span_end(h, span);
@@ -788,21 +792,23 @@ void vcycle(rmg_handle* h, int level, bool lowp, const void* b, void* z, int dot
 
 // z = M^-1 r with the configured precision (FP64 regional vectors in and out); with slot >= 0 also
 // (r, z) into that scalar slot, summed by the V-cycle's last Chebyshev step where it has one.
-// start_ready: the finest level's zero-guess start is already in its u (fused_start_ok).
-static void precondition(rmg_handle* h, const double* r, double* z, int slot = -1, bool start_ready = false) {
+// start_ready: the finest level's zero-guess start is already in its u (fused_start_ok); post: the CG
+// scalar update after the sum.
+static void precondition(rmg_handle* h, const double* r, double* z, int slot = -1, bool start_ready = false,
+                         int post = -1) {
   Level& L = *h->levels[0];
   if (h->hy) {
     hybrid_cycle(h, r, z);
   } else if (h->opt.precision == RMG_PREC_FP64) {
     const bool fused = slot >= 0 && h->opt.smoother <= 1 && h->levels.size() > 1;
-    vcycle(h, 0, false, r, z, fused ? slot : -1, start_ready);
+    vcycle(h, 0, false, r, z, fused ? slot : -1, start_ready, post);
     if (fused) return;
   } else {
     launch_f64_to_f32(L.ndofs(), r, L.b32.as<float>(), h->stream);
     vcycle(h, 0, true, L.b32.p, h->cg_z32.p);
     launch_f32_to_f64(L.ndofs(), h->cg_z32.as<float>(), z, h->stream);
   }
-  if (slot >= 0) dot(h, L, r, z, slot);
+  if (slot >= 0) dot(h, L, r, z, slot, post);
 }
 
 void apply_preconditioner(rmg_handle* h, const double* r, double* z) { precondition(h, r, z); }
@@ -900,8 +906,7 @@ static void pcg_impl(rmg_handle* h, const double* b, double* x, double rtol, int
     a.partials = part;
     if (timed) h->timers[kTimedCgQ].acquire(&a.ev0, &a.ev1);
     const int64_t np = launch_stencil_op(L, a, st);
-    launch_reduce(part, np, scal(h), kPQ, st);
-    launch_cg_scalars(scal(h), 0, st);
+    launch_reduce(part, np, scal(h), kPQ, st, 0);
     const int64_t nu = fused_start ? launch_cg_update(L, scal(h), x, r, p, q, part, st, L.dinv.as<double>(),
                                                       L.cheb_c2[0], L.u.as<double>())
                                    : launch_cg_update(L, scal(h), x, r, p, q, part, st);
@@ -909,13 +914,8 @@ static void pcg_impl(rmg_handle* h, const double* b, double* x, double rtol, int
   };
   // second half: z = M^-1 r, beta, p update
   auto body_b = [&]() {
-    precondition(h, r, z, kRZnew, fused_start);
-    if (flexible) {
-      dot(h, L, z, q, kZQ);
-      launch_cg_scalars(scal(h), 2, st);
-    } else {
-      launch_cg_scalars(scal(h), 1, st);
-    }
+    precondition(h, r, z, kRZnew, fused_start, flexible ? -1 : 1);
+    if (flexible) dot(h, L, z, q, kZQ, 2);
     launch_cg_direction(n, scal(h), z, p, st);
   };
   // r = b - A x0
