@@ -58,6 +58,10 @@ void launch_group_reduce(const int64_t* gptr, const int* gcopy, int64_t ngroups,
 
 // Owner-masked composite dot product (FP64): partial sums written to `partials`; returns their count.
 int64_t launch_dot(const Level& L, const double* a, const double* b, double* partials, hipStream_t st);
+int64_t dot_partials(const Level& L);  // that count
+// (r, z) and (z, q) of an FP32 z: n = dot_partials(L) sums of the first, then n of the second; returns n.
+int64_t launch_dot_lo(const Level& L, const float* z, const double* r, const double* q, double* partials,
+                      hipStream_t st);
 
 // Deterministic sum of `n` partials into scalars[slot]; post >= 0: then the CG scalar update of that
 // mode (below) in the same launch.
@@ -149,13 +153,21 @@ void launch_csr_to_stencil(const Level& L, const int64_t* rowptr, const int* col
 void launch_region_stencil_io(const Level& L, int region, double* soa, int to_level, hipStream_t st);
 
 // CG helpers (FP64).
-// x += alpha p; r -= alpha q; partial sums of owner-masked (r, r); with u0 (scalar levels) also
-// u0 = c0 * dinv * r, the V-cycle's zero-guess start from the new r (as launch_cheb_zero).
+// The FP32 V-cycle's right-hand side b and, with u, its zero-guess start u = c dinv b; b null: neither.
+struct LowStart {
+  float* b = nullptr;
+  const float* dinv = nullptr;
+  float c = 0.f;
+  float* u = nullptr;
+};
+// x += alpha p; r -= alpha q; partial sums of owner-masked (r, r); with u0 also
+// u0 = c0 * dinv * r, the V-cycle's zero-guess start from the new r (as launch_cheb_zero); lo as above, from the new r.
 int64_t launch_cg_update(const Level& L, double* scalars, double* x, double* r, const double* p,
                          const double* q, double* partials, hipStream_t st, const double* dinv = nullptr,
-                         double c0 = 0.0, double* u0 = nullptr);
+                         double c0 = 0.0, double* u0 = nullptr, LowStart lo = {});
 // p = z + beta p.
 void launch_cg_direction(int64_t n, double* scalars, const double* z, double* p, hipStream_t st);
+void launch_cg_direction(int64_t n, double* scalars, const float* z, double* p, hipStream_t st);
 // CG scalar updates (launch_reduce's post): mode 0: alpha = rz / pq; mode 1: beta = rz_new / rz,
 // rz = rz_new; mode 2 (flexible CG): beta = -alpha (z_new, q) / rz, rz = rz_new.
 void launch_copy(int64_t n, const double* src, double* dst, hipStream_t st);

@@ -70,19 +70,42 @@ constexpr int kUpdateDescs = 2;
 
 static int64_t reduction_blocks(const Level& L, int per) { return cdiv((int64_t)L.blocks.size(), per); }
 
-// Owned copies: the node blocks (one-region nodes), then blocks over the interface groups (first copies).
-template <int NDOF>
-__device__ __forceinline__ double dot_groups_block(const int64_t* __restrict__ gptr, const int* __restrict__ gcopy,
-                                                   int64_t ng, int block, const double* __restrict__ a,
-                                                   const double* __restrict__ b) {
+// Owned copies: the node blocks (one-region nodes), then blocks over the interface groups (first
+// copies); add(i) takes dof i into the thread's sums.
+template <int NDOF, class F>
+__device__ __forceinline__ void owned_groups(const int64_t* __restrict__ gptr, const int* __restrict__ gcopy, int64_t ng,
+                                             int block, F&& add) {
   const int64_t g = (int64_t)block * kBlock + threadIdx.x;
-  double c = 0.0;
   if (g < ng) {
     const int64_t i = (int64_t)gcopy[gptr[g]] * NDOF;
 #pragma unroll
-    for (int k = 0; k < NDOF; ++k) c += a[i + k] * b[i + k];
+    for (int k = 0; k < NDOF; ++k) add(i + k);
   }
-  return c;
+}
+
+template <int NDOF, class F>
+__device__ __forceinline__ void owned_dofs(const LevelView& L, int nb, const int64_t* __restrict__ gptr,
+                                           const int* __restrict__ gcopy, int64_t ng, F&& add) {
+  if ((int)blockIdx.x >= nb) {
+    owned_groups<NDOF>(gptr, gcopy, ng, (int)blockIdx.x - nb, add);
+    return;
+  }
+  for (int j = 0; j < kDescsPerBlock; ++j) {
+    const int64_t d = (int64_t)blockIdx.x * kDescsPerBlock + j;
+    if (d >= L.nblocks) break;
+    const BlockDesc bd = L.blocks[d];
+    const RegionGeo R = L.regs[bd.region];
+    const int li = bd.start + (int)threadIdx.x;
+    if (li < R.n) {
+      int x, y, z;
+      decompose(R, li, x, y, z);
+      if (!is_shared(L, R, x, y, z)) {
+        const int64_t gi = (R.off + li) * NDOF;
+#pragma unroll
+        for (int k = 0; k < NDOF; ++k) add(gi + k);
+      }
+    }
+  }
 }
 
 template <int NDOF>
@@ -91,35 +114,39 @@ __global__ __launch_bounds__(kBlock) void k_dot(LevelView L, int nb, const int64
                                                 const double* __restrict__ a, const double* __restrict__ b,
                                                 double* __restrict__ partials) {
   double c = 0.0;
-  if ((int)blockIdx.x >= nb) {
-    c = dot_groups_block<NDOF>(gptr, gcopy, ng, (int)blockIdx.x - nb, a, b);
-  } else {
-    for (int j = 0; j < kDescsPerBlock; ++j) {
-      const int64_t d = (int64_t)blockIdx.x * kDescsPerBlock + j;
-      if (d >= L.nblocks) break;
-      const BlockDesc bd = L.blocks[d];
-      const RegionGeo R = L.regs[bd.region];
-      const int li = bd.start + (int)threadIdx.x;
-      if (li < R.n) {
-        int x, y, z;
-        decompose(R, li, x, y, z);
-        if (!is_shared(L, R, x, y, z)) {
-          const int64_t gi = (R.off + li) * NDOF;
-#pragma unroll
-          for (int k = 0; k < NDOF; ++k) c += a[gi + k] * b[gi + k];
-        }
-      }
-    }
-  }
+  owned_dofs<NDOF>(L, nb, gptr, gcopy, ng, [&](int64_t i) { c += a[i] * b[i]; });
   const double s = block_sum(c);
   if (threadIdx.x == 0) partials[blockIdx.x] = s;
+}
+
+// (r, z) and (z, q) of an FP32 z in one pass over it; the second sums follow the first ones.
+template <int NDOF>
+__global__ __launch_bounds__(kBlock) void k_dot_lo(LevelView L, int nb, const int64_t* __restrict__ gptr,
+                                                   const int* __restrict__ gcopy, int64_t ng,
+                                                   const float* __restrict__ z, const double* __restrict__ r,
+                                                   const double* __restrict__ q, double* __restrict__ partials) {
+  double c = 0.0, e = 0.0;
+  owned_dofs<NDOF>(L, nb, gptr, gcopy, ng, [&](int64_t i) {
+    const double v = (double)z[i];
+    c += r[i] * v;
+    e += v * q[i];
+  });
+  const double s = block_sum(c);
+  __syncthreads();
+  const double t = block_sum(e);
+  if (threadIdx.x == 0) {
+    partials[blockIdx.x] = s;
+    partials[gridDim.x + blockIdx.x] = t;
+  }
 }
 
 template <int NDOF>
 __global__ __launch_bounds__(kBlock) void k_dot_groups(const int64_t* __restrict__ gptr, const int* __restrict__ gcopy,
                                                        int64_t ng, const double* __restrict__ a,
                                                        const double* __restrict__ b, double* __restrict__ partials) {
-  const double s = block_sum(dot_groups_block<NDOF>(gptr, gcopy, ng, (int)blockIdx.x, a, b));
+  double c = 0.0;
+  owned_groups<NDOF>(gptr, gcopy, ng, (int)blockIdx.x, [&](int64_t i) { c += a[i] * b[i]; });
+  const double s = block_sum(c);
   if (threadIdx.x == 0) partials[blockIdx.x] = s;
 }
 
@@ -146,6 +173,23 @@ int64_t launch_dot(const Level& L, const double* a, const double* b, double* par
                L.d_gcopy.as<int>(), L.ngroups, a, b, partials);
   LAUNCH_CHECK();
   return nb + ngb;
+}
+
+int64_t dot_partials(const Level& L) {
+  return reduction_blocks(L, kDescsPerBlock) + (L.ngroups > 0 ? cdiv(L.ngroups, kBlock) : 0);
+}
+
+int64_t launch_dot_lo(const Level& L, const float* z, const double* r, const double* q, double* partials,
+                      hipStream_t st) {
+  const int64_t nb = reduction_blocks(L, kDescsPerBlock), n = dot_partials(L);
+  if (L.ndof == 3)
+    RMG_LAUNCH(k_dot_lo<3>, dim3(n), dim3(kBlock), 0, st, L.view(), (int)nb, L.d_gptr.as<int64_t>(),
+               L.d_gcopy.as<int>(), L.ngroups, z, r, q, partials);
+  else
+    RMG_LAUNCH(k_dot_lo<1>, dim3(n), dim3(kBlock), 0, st, L.view(), (int)nb, L.d_gptr.as<int64_t>(),
+               L.d_gcopy.as<int>(), L.ngroups, z, r, q, partials);
+  LAUNCH_CHECK();
+  return n;
 }
 
 constexpr int kReduceThreads = 1024;
@@ -2390,8 +2434,9 @@ bool launch_make_sym(Level& L, bool lowp, hipStream_t st, bool table) {
 }
 
 // ------------------------------------------------------------------ CG
-// With u0 (scalar levels): also the V-cycle's zero-guess start from the new residual, u0 = c0 D~^-1 r,
-// as k_cheb_zero computes it.
+// With u0: also the V-cycle's zero-guess start from the new residual, u0 = c0 D~^-1 r,
+// as k_cheb_zero computes it.  With lo.b: also the FP32 V-cycle's right-hand side, the new residual
+// rounded, and with lo.u its zero-guess start.
 template <int NDOF>
 __global__ __launch_bounds__(kBlock) void k_cg_update(LevelView L, const double* __restrict__ scalars,
                                                       double* __restrict__ x, double* __restrict__ r,
@@ -2399,7 +2444,7 @@ __global__ __launch_bounds__(kBlock) void k_cg_update(LevelView L, const double*
                                                       double* __restrict__ partials, const double* __restrict__ dinv,
                                                       double c0, double* __restrict__ u0,
                                                       const double* __restrict__ table, const int* __restrict__ table_ok,
-                                                      const int* __restrict__ owners) {
+                                                      const int* __restrict__ owners, LowStart lo) {
   const double alpha = scalars[kAlpha];
   double c = 0.0;
   for (int j = 0; j < kUpdateDescs; ++j) {
@@ -2407,33 +2452,41 @@ __global__ __launch_bounds__(kBlock) void k_cg_update(LevelView L, const double*
     if (d >= L.nblocks) break;
     const BlockDesc bd = L.blocks[d];
     const RegionGeo R = L.regs[bd.region];
-    const int li = bd.start + (int)threadIdx.x;
-    if (li < R.n) {
+    // lanes take consecutive dofs (of 3-dof nodes too: three passes over the block's 256 nodes, each
+    // coalesced; a node's dofs per lane, stride 24 bytes, took 114 us on 13.5M dofs and
+    // 291 with lo; these take 106 and 141)
+#pragma unroll
+    for (int a = 0; a < NDOF; ++a) {
+      const int k = a * kBlock + (int)threadIdx.x;
+      const int li = bd.start + k / NDOF;
+      if (li >= R.n) break;
       int xx, yy, zz;
       decompose(R, li, xx, yy, zz);
       const bool own = !is_shared(L, R, xx, yy, zz);
       bool counts = own;
       if (owners && !own) counts = owners[R.off + li] != 0;
-#pragma unroll
-      for (int a = 0; a < NDOF; ++a) {
-        const int64_t gi = (R.off + li) * NDOF + a;
-        x[gi] = x[gi] + alpha * p[gi];
-        const double rn = r[gi] + (-alpha) * q[gi];
-        r[gi] = rn;
-        if (NDOF == 1 && u0) {
-          // a one-region row of a region served by its class table: D~^-1 is 1 / its class's centre
-          // coupling (the quotient the stored D~^-1 holds), so the row's D~^-1 is not read
-          double di;
-          if (table && own && table_ok[bd.region]) {
-            const int cls = (axis_class(zz, R.ez) * 5 + axis_class(yy, R.ey)) * 5 + axis_class(xx, R.ex);
-            di = 1.0 / table[((int64_t)bd.region * kClasses + cls) * kClassPts + 13];
-          } else {
-            di = dinv[gi];
-          }
-          u0[gi] = c0 * (di * rn);
+      const int64_t gi = (R.off + bd.start) * NDOF + k;
+      x[gi] = x[gi] + alpha * p[gi];
+      const double rn = r[gi] + (-alpha) * q[gi];
+      r[gi] = rn;
+      if (u0) {
+        // a one-region row of a region served by its class table: D~^-1 is 1 / its class's centre
+        // coupling (the quotient the stored D~^-1 holds), so the row's D~^-1 is not read
+        double di;
+        if (NDOF == 1 && table && own && table_ok[bd.region]) {
+          const int cls = (axis_class(zz, R.ez) * 5 + axis_class(yy, R.ey)) * 5 + axis_class(xx, R.ex);
+          di = 1.0 / table[((int64_t)bd.region * kClasses + cls) * kClassPts + 13];
+        } else {
+          di = dinv[gi];
         }
-        if (counts) c += rn * rn;
+        u0[gi] = c0 * (di * rn);
       }
+      if (lo.b) {
+        const float f = (float)rn;
+        lo.b[gi] = f;
+        if (lo.u) lo.u[gi] = lo.c * (lo.dinv[gi] * f);
+      }
+      if (counts) c += rn * rn;
     }
   }
   const double s = block_sum(c);
@@ -2441,32 +2494,39 @@ __global__ __launch_bounds__(kBlock) void k_cg_update(LevelView L, const double*
 }
 
 int64_t launch_cg_update(const Level& L, double* scalars, double* x, double* r, const double* p, const double* q,
-                         double* partials, hipStream_t st, const double* dinv, double c0, double* u0) {
+                         double* partials, hipStream_t st, const double* dinv, double c0, double* u0, LowStart lo) {
   const int64_t nb = reduction_blocks(L, kUpdateDescs);
-  RMG_REQUIRE(!u0 || (L.ndof == 1 && dinv), RMG_ERR_ARG, "internal: fused zero-guess start needs a scalar level");
+  RMG_REQUIRE(!u0 || dinv, RMG_ERR_ARG, "internal: fused zero-guess start needs D~^-1");
   if (L.ndof == 3)
-    RMG_LAUNCH(k_cg_update<3>, dim3(nb), dim3(kBlock), 0, st, L.view(), scalars, x, r, p, q, partials, nullptr,
-               0.0, nullptr, nullptr, nullptr, L.d_owner.as<int>());
+    RMG_LAUNCH(k_cg_update<3>, dim3(nb), dim3(kBlock), 0, st, L.view(), scalars, x, r, p, q, partials, dinv, c0,
+               u0, nullptr, nullptr, L.d_owner.as<int>(), lo);
   else {
     // the class tables give D~^-1 of the served regions' one-region rows (when dinv is the level's own)
     const bool tab = u0 && dinv == L.dinv.as<double>() && L.npts == 27 && L.class_table.p && L.class_table_ok.p;
     RMG_LAUNCH(k_cg_update<1>, dim3(nb), dim3(kBlock), 0, st, L.view(), scalars, x, r, p, q, partials, dinv, c0,
-               u0, tab ? L.class_table.as<double>() : nullptr, tab ? L.class_table_ok.as<int>() : nullptr, L.d_owner.as<int>());
+               u0, tab ? L.class_table.as<double>() : nullptr, tab ? L.class_table_ok.as<int>() : nullptr,
+               L.d_owner.as<int>(), lo);
   }
   LAUNCH_CHECK();
   return L.d_owner.p ? nb : nb + dot_groups(L, r, r, partials + nb, st);
 }
 
-__global__ void k_cg_direction(int64_t n, const double* __restrict__ scalars, const double* __restrict__ z,
+template <class V>
+__global__ void k_cg_direction(int64_t n, const double* __restrict__ scalars, const V* __restrict__ z,
                                double* __restrict__ p) {
   const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (i >= n) return;
   const double beta = scalars[kBeta];
-  p[i] = z[i] + beta * p[i];
+  p[i] = (double)z[i] + beta * p[i];
 }
 
 void launch_cg_direction(int64_t n, double* scalars, const double* z, double* p, hipStream_t st) {
-  RMG_LAUNCH(k_cg_direction, dim3(cdiv(n, kBlock)), dim3(kBlock), 0, st, n, scalars, z, p);
+  RMG_LAUNCH(k_cg_direction<double>, dim3(cdiv(n, kBlock)), dim3(kBlock), 0, st, n, scalars, z, p);
+  LAUNCH_CHECK();
+}
+
+void launch_cg_direction(int64_t n, double* scalars, const float* z, double* p, hipStream_t st) {
+  RMG_LAUNCH(k_cg_direction<float>, dim3(cdiv(n, kBlock)), dim3(kBlock), 0, st, n, scalars, z, p);
   LAUNCH_CHECK();
 }
 
