@@ -806,7 +806,7 @@ __global__ __launch_bounds__(kTableThreads) __attribute__((amdgpu_waves_per_eu(s
 // loads and one plane's memory latency a step the 243 products (1,000 cycles) only half cover.  Taking
 // the x-face columns' classes one after the other by scalar loads instead of from LDS cost 440 us (their
 // 20 classes of 2 KB do not fit the scalar cache), one plane in flight instead of two 10% more.
-template <class V, StencilOp OP, bool DOT>
+template <class V, StencilOp OP>
 __global__ __launch_bounds__(kTable3Threads) __attribute__((amdgpu_waves_per_eu(sizeof(V) == 4 ? 4 : 3))) void k_stencil_table3(
                                                                    LevelView L, const Tile3* __restrict__ tiles,
                                                                    const V* __restrict__ table, OpP<V> p,
@@ -1026,7 +1026,7 @@ __global__ __launch_bounds__(kTable3Threads) __attribute__((amdgpu_waves_per_eu(
 #pragma unroll
             for (int a = 0; a < 3; ++a)
               dold[a] = OP == StencilOp::Cheb ? prev_correction(p, xprev[a], cd[a]) : xprev[a];
-            contrib += finish_block3_value<OP, DOT, V>(p, node, a0, xprev, dold, out, dd);
+            contrib += finish_block3_value<OP, false, V>(p, node, a0, xprev, dold, out, dd);
 #pragma unroll
             for (int a = 0; a < 3; ++a) p.out[node * 3 + a] = out[a];
             block = true;
@@ -1036,9 +1036,9 @@ __global__ __launch_bounds__(kTable3Threads) __attribute__((amdgpu_waves_per_eu(
 #pragma unroll
           for (int a = 0; a < 3; ++a) {
             if constexpr (kPreB)
-              contrib += finish_pre<OP, DOT, V, kOwn>(p, node * 3 + a, a0[a], 1, xprev[a], ctr[a], cb[a], cd[a]);
+              contrib += finish_pre<OP, false, V, kOwn>(p, node * 3 + a, a0[a], 1, xprev[a], ctr[a], cb[a], cd[a]);
             else
-              contrib += finish<OP, DOT, V, kOwn>(p, node * 3 + a, a0[a], 1, xprev[a], ctr[a]);
+              contrib += finish<OP, false, V, kOwn>(p, node * 3 + a, a0[a], 1, xprev[a], ctr[a]);
           }
         }
       }
@@ -1051,7 +1051,7 @@ __global__ __launch_bounds__(kTable3Threads) __attribute__((amdgpu_waves_per_eu(
     plane(zz, preB);
     plane(zz + 1, preA);
   }
-  if constexpr (DOT || OP == StencilOp::CgQ) {
+  if constexpr (OP == StencilOp::CgQ) {
     double s1 = contrib;
     for (int o = 32; o > 0; o >>= 1) s1 += __shfl_down(s1, o, 64);
     __shared__ double sm[NT / 64];
@@ -1354,11 +1354,21 @@ static int64_t run(const Level& L, const StencilArgs& a, hipStream_t st) {
   constexpr bool kSums = DOT || OP == StencilOp::CgQ;
   const bool fused = !tiled && L.n <= kFuseNodes && L.ncopyblk > 0 && (kSums || !L.per_region);
   int64_t nparts = grid3;  // partial sums written by the tiled launches
+  if constexpr (NDOF == 3 && DOT) {
+    if (split3) {
+      // the sum in a pass of its own: in the step it spilled 30 registers, 446 us on 4.5M nodes, where
+      // the step takes 364 and the pass 22
+      StencilArgs step = a;
+      step.dot_rhs = false;
+      run<NPTS, NDOF, V, C, OP, false>(L, step, st);
+      return launch_dot(L, static_cast<const double*>(a.b), static_cast<const double*>(a.out), a.partials, st);
+    }
+  }
   if (a.ev0) RMG_HIP(hipEventRecord(a.ev0, st));
-  if constexpr (NPTS == 27 && NDOF == 3) {
+  if constexpr (NPTS == 27 && NDOF == 3 && !DOT) {
     if (split3) {
       nparts = (int64_t)L.table_tiles.size();
-      RMG_LAUNCH((k_stencil_table3<V, OP, DOT>), dim3(nparts), dim3(kTable3Threads), 0, st, v,
+      RMG_LAUNCH((k_stencil_table3<V, OP>), dim3(nparts), dim3(kTable3Threads), 0, st, v,
                  L.d_table_tiles.as<Tile3>(), table, p, a.partials);
     }
   }
