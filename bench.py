@@ -168,10 +168,10 @@ def _setup(h, w, **opts):
     return (time.perf_counter() - t0) * 1e3
 
 
-def _cheb_bytes(h, kind, precision, stored=True, nreg=None):
+def _cheb_bytes(h, kind, precision, stored=True, served=0.0):
     """Bytes per node of the level-0 Chebyshev step: the stencil blocks (stored: the ones the level
-    streams, full or upper half, see rmg_level_kernel, none for regions served by their class
-    tables when nreg is given; else the method's full 27 blocks) and the vectors u_(k-1), b,
+    streams, full or upper half, see rmg_level_kernel, none for the share of the regions that their class
+    tables serve; else the method's full 27 blocks) and the vectors u_(k-1), b,
     u_(k-2), D~^-1 read and u_k written (the method's step also reads and writes its direction
     vector d: one vector more each way); with BF16 storage the centre block comes from an FP32
     array.  Stored: the scalar tiled kernel in FP64 or FP32 computes D~^-1 of one-region rows
@@ -180,9 +180,12 @@ def _cheb_bytes(h, kind, precision, stored=True, nreg=None):
     nd = 1 if kind == "scalar" else 3
     nb = nd * nd
     coefs = lk["coefs"] if stored else 27 * nb
-    if stored and precision == 0 and nreg:
-        coefs *= 1.0 - h.level_table_regions(0) / nreg
     coefs_lo = lk["coefs_lo"] if stored else 27 * nb
+    if stored:
+        coefs *= 1.0 - served
+        if precision == 2:  # (nb of coefs_lo are the FP32 centre block)
+            return ((coefs_lo - nb) * 2 + nb * 4) * (1.0 - served) + 5 * nd * 4
+        coefs_lo *= 1.0 - served
     if stored:
         vecs = 4 if kind == "scalar" and lk["kernel"] in (1, 2) and precision in (0, 1) else 5
     else:
@@ -194,20 +197,20 @@ def _cheb_bytes(h, kind, precision, stored=True, nreg=None):
     return (coefs_lo - nb) * 2 + nb * 4 + vecs * nd * 4
 
 
-def _cheb_gbs(h, kind, precision, rows, stored=True, nreg=None):
+def _cheb_gbs(h, kind, precision, rows, stored=True, served=0.0):
     from paper_2103_11962_amd import regmg
 
     n, ms = h.profile_query(regmg.TIMED_CHEB)
     if n == 0:
         return None
-    return _cheb_bytes(h, kind, precision, stored, nreg) * rows / (ms / n * 1e-3) / 1e9
+    return _cheb_bytes(h, kind, precision, stored, served) * rows / (ms / n * 1e-3) / 1e9
 
 
 def variant_mixed(dev):
     """Elasticity 3x3x3 regions of 55^3: FP64 V-cycle vs FP32 vs FP32 with BF16 coefficients on level 0
     vs BF16 on the levels the measured convergence factor allows, FP64 with the nodal-block D~, and
-    FP64 streaming every block (region_table = 0: the FP64 V-cycle otherwise reads the per-region
-    elasticity blocks from the class tables, which the low-precision V-cycles do not have)."""
+    FP64 streaming every block (region_table = 0: the V-cycle otherwise reads the per-region
+    elasticity blocks from the class tables, in FP64, FP32 and BF16 alike)."""
     import numpy as np
 
     import synth
@@ -225,12 +228,16 @@ def variant_mixed(dev):
         peff = prec if prec != 3 else (2 if pl[0]["coef_type"] == 2 else 1)
         h.profile(True)
         ms, res, x = _timed_solves(h, b)
+        # equal FP64 blocks round to equal ones, so the low-precision tables serve the regions the
+        # FP64 ones do (level_table_regions counts those of an FP64 V-cycle)
+        if prec == 0:
+            served = h.level_table_regions(0) / len(w.extents)
         entry = {"setup_ms": setup_ms, "solve_ms": ms, "iterations": res["iterations"],
                  "true_relres": res["true_relres"],
                  "cheb_gbs": _cheb_gbs(h, "block3", peff, rows, stored=False),
                  "cheb_bytes_per_node": _cheb_bytes(h, "block3", peff, stored=False),
-                 "cheb_gbs_at_stored_bytes": _cheb_gbs(h, "block3", peff, rows, nreg=len(w.extents)),
-                 "cheb_stored_bytes_per_node": _cheb_bytes(h, "block3", peff, nreg=len(w.extents)),
+                 "cheb_gbs_at_stored_bytes": _cheb_gbs(h, "block3", peff, rows, served=served),
+                 "cheb_stored_bytes_per_node": _cheb_bytes(h, "block3", peff, served=served),
                  "table_regions": h.level_table_regions(0)}
         if prec == 3:
             entry["levels"] = [{"coef_type": p["coef_type"], "rho_fp32": p["rho_fp32"], "rho_bf16": p["rho_bf16"]}
@@ -258,6 +265,7 @@ def variant_batched(dev):
     w = synth.workload("c4")
     b = _to_dev(synth.rhs(w), dev)
     out = {}
+    served = 1.0  # the Laplacian's couplings are one set per class in every region
     cache = os.path.join(tempfile.gettempdir(), "regmg_bench_tune.txt")
     for name, opts in (("region_by_region", dict(precision=1, batched=0)),
                        ("batched", dict(precision=1, autotune=1, autotune_cache=cache, use_graph=1))):
@@ -269,8 +277,8 @@ def variant_batched(dev):
         out[name] = {"setup_ms": setup_ms, "solve_ms": ms, "iterations": res["iterations"],
                      "true_relres": res["true_relres"], "cheb_gbs": _cheb_gbs(h, "scalar", 1, rows, stored=False),
                      "cheb_bytes_per_row": _cheb_bytes(h, "scalar", 1, stored=False),
-                     "cheb_gbs_at_stored_bytes": _cheb_gbs(h, "scalar", 1, rows),
-                     "cheb_stored_bytes_per_row": _cheb_bytes(h, "scalar", 1)}
+                     "cheb_gbs_at_stored_bytes": _cheb_gbs(h, "scalar", 1, rows, served=served),
+                     "cheb_stored_bytes_per_row": _cheb_bytes(h, "scalar", 1, served=served)}
         if name == "batched":
             out[name]["tuning"] = h.tune_report().strip().splitlines()
         h.close()
