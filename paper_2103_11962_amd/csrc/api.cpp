@@ -785,6 +785,9 @@ rmg_status rmg_level_table_regions(rmg_handle* h, int level, int* nregions) {
     std::vector<int> flags(L.nreg);
     RMG_HIP(hipStreamSynchronize(h->stream));
     RMG_HIP(hipMemcpy(flags.data(), ok.p, sizeof(int) * L.nreg, hipMemcpyDeviceToHost));
+    // on 2.5D tiles, those that table tiles run
+    if (L.use_tiles && L.use_split) flags = L.table_served;
+    else if (L.use_tiles && L.ndof == 1) flags.clear();
     for (int f : flags) count += f != 0;
   }
   if (nregions) *nregions = count;

@@ -277,7 +277,7 @@ struct Level {
   // and the solve would no longer repeat the streamed one to FP64 accuracy
   bool split_dot = true;
   bool deep_table = false;           // table tiles kTablePlanes deep, however few (rmg_options.tile_planes)
-  std::vector<int> table_served;     // per region: 1 when the tables serve it
+  std::vector<int> table_served;     // per region: 1 when table tiles run it
   std::vector<Tile3> table_tiles;    // whole-row tiles of the served regions (k_stencil_table)
   std::vector<Tile3> other_tiles;    // the level's 2.5D tiles of the regions not served
   DBuf d_table_tiles, d_other_tiles;
@@ -425,8 +425,9 @@ void make_tiles(Level& L, int depth);
 void make_split(Level& L, const std::vector<int>& served, bool elem);
 // Whether the rows of every region not served fit an element tile.
 bool elem_fits(const Level& L, const std::vector<int>& served);
-// Whether every served region's rows fit a table tile.
-bool split_fits(const Level& L, const std::vector<int>& served);
+// Clears the flags of the regions whose rows do not fit a table tile (extents along x from 340 on);
+// returns how many stay set.
+int table_tile_regions(const Level& L, std::vector<int>& served);
 // The same for a 3-dof level all of whose regions are served (k_stencil_table3); false if a region's
 // rows do not fit.
 bool make_split3(Level& L);

@@ -2345,12 +2345,14 @@ static void make_class_table(Level& L, hipStream_t st) {
     if (served == L.nreg && L.split_auto && (L.deep_table || L.n >= kTable3MinNodes)) make_split3(L);
     return;
   }
-  // regions that the tables do not serve: assembled on the fly where the level has its elements
-  const bool elem = L.elem.p && served < L.nreg && elem_fits(L, flags);
-  if (served == 0 && !elem) return;
+  // regions whose rows are too long for a table tile stream like those that the tables do not serve
+  const int tabled = table_tile_regions(L, flags);
+  // those other regions: assembled on the fly where the level has its elements
+  const bool elem = L.elem.p && tabled < L.nreg && elem_fits(L, flags);
+  if (tabled == 0 && !elem) return;
   if (L.use_tiles) {
     make_split(L, flags, elem);
-  } else if (L.split_auto && (served == L.nreg || elem) && L.n >= kTableMinNodes && split_fits(L, flags)) {
+  } else if (L.split_auto && (tabled == L.nreg || elem) && L.n >= kTableMinNodes) {
     make_split(L, flags, elem);
   }  // else node blocks: each block of a served region reads the tables
 }

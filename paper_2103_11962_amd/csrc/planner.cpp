@@ -224,10 +224,13 @@ bool elem_fits(const Level& L, const std::vector<int>& served) {
   return true;
 }
 
-bool split_fits(const Level& L, const std::vector<int>& served) {
-  for (int k = 0; k < L.nreg; ++k)
-    if (served[k] && table_rows(L.regs[k]) < 1) return false;
-  return true;
+int table_tile_regions(const Level& L, std::vector<int>& served) {
+  int n = 0;
+  for (int k = 0; k < L.nreg; ++k) {
+    if (table_rows(L.regs[k]) < 1) served[k] = 0;
+    n += served[k] != 0;
+  }
+  return n;
 }
 
 // Whole-row tiles of region k, at most ty rows and `planes` planes, both shared out evenly.
