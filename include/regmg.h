@@ -384,6 +384,12 @@ rmg_status rmg_level_transfer_tiles(rmg_handle* h, int level, int* restriction_t
  * (rmg_options.region_table); 0 where no table was built and with a low-precision V-cycle.
  * Output may be NULL. */
 rmg_status rmg_level_table_regions(rmg_handle* h, int level, int* nregions);
+/* What the region tables and the kept element coefficients run on `level` (rmg_options.region_table):
+ * table_tiles = the whole-row tiles that take every coupling from a region's class table,
+ * elem_tiles = the tiles that assemble their couplings from the element coefficients (FP64
+ * operations), 0 where the level runs other kernels; regions_lo = the regions whose couplings the
+ * low-precision V-cycle takes from its own class tables (0 without them).  Any output may be NULL. */
+rmg_status rmg_level_split(rmg_handle* h, int level, int* table_tiles, int* elem_tiles, int* regions_lo);
 /* Copy region `region`'s stencil on `level` to host memory in the layout of
  * rmg_set_region_stencil (npts 27 in 3D, 9 in 2D, all levels). */
 rmg_status rmg_get_level_stencil(rmg_handle* h, int level, int region, double* host_out);

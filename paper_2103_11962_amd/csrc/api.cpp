@@ -775,22 +775,40 @@ rmg_status rmg_level_transfer_tiles(rmg_handle* h, int level, int* restriction_t
   API_END
 }
 
+// Regions with their flag set in `ok` (device); on scalar 2.5D tiles those that table tiles run.
+static int table_regions(rmg_handle* h, const Level& L, const DBuf& ok) {
+  if (!ok.p) return 0;
+  std::vector<int> flags(L.nreg);
+  if (L.use_tiles && L.ndof == 1) {
+    if (!L.use_split) return 0;
+    flags = L.table_served;
+  } else {
+    RMG_HIP(hipStreamSynchronize(h->stream));
+    RMG_HIP(hipMemcpy(flags.data(), ok.p, sizeof(int) * L.nreg, hipMemcpyDeviceToHost));
+  }
+  int count = 0;
+  for (int f : flags) count += f != 0;
+  return count;
+}
+
 rmg_status rmg_level_table_regions(rmg_handle* h, int level, int* nregions) {
   API_BEGIN
   use_device(h);
   Level& L = level_of(h, level);
-  const DBuf& ok = L.class_table_ok;
-  int count = 0;
-  if (ok.p && h->opt.precision == RMG_PREC_FP64) {
-    std::vector<int> flags(L.nreg);
-    RMG_HIP(hipStreamSynchronize(h->stream));
-    RMG_HIP(hipMemcpy(flags.data(), ok.p, sizeof(int) * L.nreg, hipMemcpyDeviceToHost));
-    // on 2.5D tiles, those that table tiles run
-    if (L.use_tiles && L.use_split) flags = L.table_served;
-    else if (L.use_tiles && L.ndof == 1) flags.clear();
-    for (int f : flags) count += f != 0;
-  }
+  const int count = h->opt.precision == RMG_PREC_FP64 ? table_regions(h, L, L.class_table_ok) : 0;
   if (nregions) *nregions = count;
+  API_END
+}
+
+rmg_status rmg_level_split(rmg_handle* h, int level, int* table_tiles, int* elem_tiles, int* regions_lo) {
+  API_BEGIN
+  use_device(h);
+  Level& L = level_of(h, level);
+  if (table_tiles) *table_tiles = L.use_split ? (int)L.table_tiles.size() : 0;
+  if (elem_tiles) *elem_tiles = L.use_split ? (int)L.elem_tiles.size() : 0;
+  // (scalar 2.5D tiles of BF16 storage stream)
+  const bool stream = L.use_tiles && L.ndof == 1 && L.ct_lo == kCoefBF16;
+  if (regions_lo) *regions_lo = stream ? 0 : table_regions(h, L, L.class_table_lo_ok);
   API_END
 }
 

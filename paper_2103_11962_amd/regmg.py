@@ -41,7 +41,7 @@ SYMBOLS = (
     "rmg_mlp_set_loss", "rmg_set_region_kinds", "rmg_hybrid_level_info", "rmg_hybrid_aggregates",
     "rmg_hybrid_composite_ids", "rmg_hybrid_matrix", "rmg_amg_levels", "rmg_amg_level_info", "rmg_amg_matrix",
     "rmg_level_table_regions", "rmg_level_tiles", "rmg_level_transfer_tiles", "rmg_kernel_launches", "rmg_convergence_factor_noalloc",
-    "rmg_level_precision",
+    "rmg_level_precision", "rmg_level_split",
 )
 SMOOTHER_CHEBYSHEV, SMOOTHER_JACOBI, SMOOTHER_GS, SMOOTHER_GS_FB, SMOOTHER_SYMGS = 0, 1, 2, 3, 4
 TIMED_CHEB, TIMED_CG_MATVEC = 0, 1
@@ -196,6 +196,7 @@ def load():
                                     ctypes.POINTER(ctypes.c_double)]),
         "rmg_set_composite_csr": (I, [H, I, ctypes.c_int64, P, P, P, I]),
         "rmg_level_table_regions": (I, [H, I, ctypes.POINTER(I)]),
+        "rmg_level_split": (I, [H, I, ctypes.POINTER(I), ctypes.POINTER(I), ctypes.POINTER(I)]),
         "rmg_level_tiles": (I, [H, I, ctypes.POINTER(I), ctypes.POINTER(I), ctypes.POINTER(I)]),
         "rmg_level_transfer_tiles": (I, [H, I, ctypes.POINTER(I), ctypes.POINTER(I)]),
         "rmg_kernel_launches": (I, [ctypes.POINTER(ctypes.c_int64)]),
@@ -480,6 +481,11 @@ class Handle:
         n = ctypes.c_int()
         _check(load().rmg_level_table_regions(self._h, level, ctypes.byref(n)))
         return n.value
+
+    def level_split(self, level):
+        t, e, lo = ctypes.c_int(), ctypes.c_int(), ctypes.c_int()
+        _check(load().rmg_level_split(self._h, level, ctypes.byref(t), ctypes.byref(e), ctypes.byref(lo)))
+        return {"table_tiles": t.value, "elem_tiles": e.value, "regions_lo": lo.value}
 
     def level_stencil(self, level, region, npts, nnodes):
         out = np.zeros(npts * nnodes)
