@@ -262,6 +262,7 @@ static void begin_operator_change(rmg_handle* h, Level& L) {
   L.class_table_ok.release();
   L.class_table_lo.release();
   L.class_table_lo_ok.release();
+  L.class_dinv_lo.release();
   L.elem.release();
   clear_split(L);
 }

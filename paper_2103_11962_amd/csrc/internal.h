@@ -266,6 +266,7 @@ struct Level {
   // The same couplings as the low-precision copy stores them, in FP32 (ndof x ndof blocks), and the
   // regions all of whose nodes have them; empty without class_table or a low-precision copy.
   DBuf class_table_lo, class_table_lo_ok;
+  DBuf class_dinv_lo;  // FP32 copies of scalar levels: the classes' FP64 D~^-1 rounded, float [nreg][kClasses]
   // With the tables: the served regions run whole-row tiles that take every coupling from the
   // tables (k_stencil_table), the other regions the level's streaming 2.5D tiles.  Built with the
   // tables (make_split), refreshed when the tiles change.

@@ -2357,6 +2357,11 @@ static void make_class_table(Level& L, hipStream_t st) {
   }  // else node blocks: each block of a served region reads the tables
 }
 
+__global__ void k_class_dinv(int64_t n, const double* __restrict__ table, float* __restrict__ dinv) {
+  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (i < n) dinv[i] = (float)(1.0 / table[i * kClassPts + 13]);
+}
+
 // The tables in the low-precision copy's values.  Its couplings are the FP64 ones rounded one by one,
 // so the FP32 copy is served where the FP64 operator is; the centre blocks beside BF16 storage carry
 // a row-sum correction, and the check clears regions where those differ within a class.
@@ -2380,6 +2385,13 @@ static void make_class_table_lo(Level& L, hipStream_t st) {
     const int64_t ne = (int64_t)kClasses * kClassPts * L.ndof * L.ndof * L.nreg;
     launch_f64_to_f32(ne, L.class_table.as<double>(), tab, st);
     RMG_HIP(hipMemcpyAsync(ok, L.class_table_ok.p, sizeof(int) * L.nreg, hipMemcpyDeviceToDevice, st));
+    if (L.ndof == 1) {
+      const int64_t nd = (int64_t)kClasses * L.nreg;
+      L.class_dinv_lo.alloc(sizeof(float) * nd);
+      RMG_LAUNCH(k_class_dinv, dim3(cdiv(nd, kBlock)), dim3(kBlock), 0, st, nd, L.class_table.as<double>(),
+                 L.class_dinv_lo.as<float>());
+      LAUNCH_CHECK();
+    }
   }
 }
 
@@ -2408,6 +2420,7 @@ bool launch_make_sym(Level& L, bool lowp, hipStream_t st, bool table) {
   out.release();
   L.class_table_lo.release();
   L.class_table_lo_ok.release();
+  L.class_dinv_lo.release();
   if (!lowp) {
     L.class_table.release();
     L.class_table_ok.release();

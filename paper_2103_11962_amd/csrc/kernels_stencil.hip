@@ -49,7 +49,7 @@ __device__ __forceinline__ double finish_block3_value(const OpP<V>& p, int64_t n
 // new correction `dd`.  Returns the dof's contribution to the fused reduction, if any.
 // OWN: the dof belongs to one region, whose centre coefficient `centre` is then the composite
 // diagonal: the Chebyshev steps take 1 / centre (the same correctly rounded quotient as the stored
-// D~^-1) instead of reading it.
+// D~^-1) instead of reading it (kOwnCentre), or are given D~^-1 itself in its place (kOwnDinv).
 // The Chebyshev steps keep no direction vector: the previous correction d_(k-1) = u_(k-1) - u_(k-2)
 // is the difference of the step's input and the iterate before it, which the output buffer holds
 // until the step overwrites it (the cycle's two buffers alternate), so a step reads u_(k-2) in
@@ -57,7 +57,9 @@ __device__ __forceinline__ double finish_block3_value(const OpP<V>& p, int64_t n
 // and reads nothing for it: its previous correction is u_(k-1) itself.  `dold` is the previous
 // correction (shared dofs of a Cheb step: the stencil kernel leaves it in p.d for the interface
 // kernel).
-template <StencilOp OP, bool DOT, class V, bool OWN = false>
+constexpr int kOwnCentre = 1, kOwnDinv = 2;
+
+template <StencilOp OP, bool DOT, class V, int OWN = 0>
 __device__ __forceinline__ double finish_value(const OpP<V>& p, int64_t i, V z, int m, V xself, V centre, V dold,
                                                V& out, V& dd) {
   if constexpr (OP == StencilOp::Matvec) {
@@ -73,7 +75,7 @@ __device__ __forceinline__ double finish_value(const OpP<V>& p, int64_t i, V z, 
   } else if constexpr (OP == StencilOp::Cheb || OP == StencilOp::ChebFirst) {
     const V bi = p.b[i];
     const V r = bi - z;
-    const V di = OWN ? (V)1 / centre : p.dinv[i];
+    const V di = OWN == kOwnCentre ? (V)1 / centre : (OWN == kOwnDinv ? centre : p.dinv[i]);
     dd = p.c2 * (di * r);
     dd = fma(p.c1, dold, dd);  // one rounding in every kernel
     out = xself + dd;
@@ -93,7 +95,7 @@ __device__ __forceinline__ V prev_correction(const OpP<V>& p, V xself, V uprev) 
 }
 
 // The same, written to dof i.
-template <StencilOp OP, bool DOT, class V, bool OWN = false>
+template <StencilOp OP, bool DOT, class V, int OWN = 0>
 __device__ __forceinline__ double finish(const OpP<V>& p, int64_t i, V z, int m, V xself, V centre = (V)0) {
   V out, dd = (V)0, dold = (V)0;
   if constexpr (OP == StencilOp::Cheb) dold = prev_correction(p, xself, p.out[i]);
@@ -113,7 +115,7 @@ __device__ __forceinline__ void write_partial(const OpP<V>& p, int64_t i, V z, V
 
 // The same with b_i and u_(k-2) (the output buffer's old value) already in registers (read a
 // plane ahead); the arithmetic is finish_value's.
-template <StencilOp OP, bool DOT, class V, bool OWN = false>
+template <StencilOp OP, bool DOT, class V, int OWN = 0>
 __device__ __forceinline__ double finish_pre(const OpP<V>& p, int64_t i, V z, int m, V xself, V centre, V bi, V uprev) {
   if constexpr (OP == StencilOp::Residual) {
     p.out[i] = bi - z;
@@ -124,7 +126,7 @@ __device__ __forceinline__ double finish_pre(const OpP<V>& p, int64_t i, V z, in
     return 0.0;
   } else if constexpr (OP == StencilOp::Cheb || OP == StencilOp::ChebFirst) {
     const V r = bi - z;
-    const V di = OWN ? (V)1 / centre : p.dinv[i];
+    const V di = OWN == kOwnCentre ? (V)1 / centre : (OWN == kOwnDinv ? centre : p.dinv[i]);
     V dd = p.c2 * (di * r);
     if constexpr (OP == StencilOp::Cheb) dd = fma(p.c1, prev_correction(p, xself, uprev), dd);
     if constexpr (OP == StencilOp::ChebFirst) dd = fma(p.c1, xself, dd);
@@ -592,21 +594,25 @@ __global__ __launch_bounds__(NT) void k_stencil3d(LevelView L, const Tile3* __re
 // tiles share their halo rows through its L2.  Every node sums its 27 products in stencil order with
 // one rounding each, as k_stencil3d does, so the results are those of streaming every coupling bit
 // for bit.
-template <class V, StencilOp OP, bool DOT>
+template <class V, StencilOp OP, bool DOT, bool DINV>
 __global__ __launch_bounds__(kTableThreads) __attribute__((amdgpu_waves_per_eu(sizeof(V) == 4 ? 8 : (DOT ? 5 : 6)))) void k_stencil_table(
-    LevelView L, const Tile3* __restrict__ tiles, const V* __restrict__ table, OpP<V> p, double* __restrict__ partials) {
+    LevelView L, const Tile3* __restrict__ tiles, const V* __restrict__ table, const V* __restrict__ cdinv, OpP<V> p,
+    double* __restrict__ partials) {
   constexpr int NT = kTableThreads;
   constexpr int kPlane = 2 * NT;  // a tile's rows with their halo: two loads per lane (make_split)
   constexpr int kFetch = 2;
   constexpr bool kPreB = OP == StencilOp::Residual || OP == StencilOp::ResidualScaled || OP == StencilOp::Cheb ||
                          OP == StencilOp::ChebFirst;
   constexpr bool kPreD = OP == StencilOp::Cheb;
+  constexpr int kOwn = DINV ? kOwnDinv : kOwnCentre;
   constexpr int kXCols = 20;  // classes of the x-face nodes in a plane: five y classes, four x classes
   __shared__ V pl[2][kPlane];
   __shared__ V xt[5][kClassPts][kXCols];  // the x-face lanes' couplings by z class
+  __shared__ V xd[DINV ? 5 : 1][kXCols];  // and their D~^-1
   const Tile3 T = tiles[xcd_item((int)blockIdx.x, (int)gridDim.x)];
   const RegionGeo R = L.regs[T.region];
   const V* __restrict__ tab = table + (int64_t)T.region * kClasses * kClassPts;
+  const V* __restrict__ dtab = DINV ? cdinv + (int64_t)T.region * kClasses : nullptr;
   const int t = threadIdx.x;
   // lane -> (row, x): inner-x lanes, padded to a wavefront boundary, then x-face lanes
   const int dxw = R.ex - 4, ndl = T.ty * dxw, pad = (ndl + 63) & ~63;
@@ -667,6 +673,7 @@ __global__ __launch_bounds__(kTableThreads) __attribute__((amdgpu_waves_per_eu(s
     const int u = e % kXCols, s2 = e / kXCols % kClassPts, cz = e / (kXCols * kClassPts);
     const int cx = (u & 3) < 2 ? (u & 3) : (u & 3) + 1;
     xt[cz][s2][u] = tab[((cz * 5 + (u >> 2)) * 5 + cx) * kClassPts + s2];
+    if (DINV && s2 == 13) xd[cz][u] = dtab[(cz * 5 + (u >> 2)) * 5 + cx];
   }
   // Running sums: once plane q has been added, a0 is node q - 1's sum, a1 node q's and a2 node
   // q + 1's.  A plane adds its nine values to the three nodes it neighbours in z (as their plane
@@ -691,7 +698,7 @@ __global__ __launch_bounds__(kTableThreads) __attribute__((amdgpu_waves_per_eu(s
       chunk(&xt[czc(q - 1)][18][u], a0);
       chunk(&xt[czc(q)][9][u], a1);
       chunk(&xt[czc(q + 1)][0][u], a2);
-      ctr = xt[czc(q - 1)][13][u];
+      ctr = DINV ? xd[czc(q - 1)][u] : xt[czc(q - 1)][13][u];
     } else {
       // the classes of this wavefront's nodes, one after the other (the mask of lanes left and the
       // leading lane are wavefront-uniform, so every pass reads its class afresh)
@@ -715,7 +722,7 @@ __global__ __launch_bounds__(kTableThreads) __attribute__((amdgpu_waves_per_eu(s
           for (int j = 0; j < 9; ++j) a1 = fma(t1[9 + j], v9[j], a1);
 #pragma unroll
           for (int j = 0; j < 9; ++j) a2 = fma(t2[j], v9[j], a2);
-          ctr = t0[13];
+          ctr = DINV ? dtab[o0 / kClassPts] : t0[13];
         }
         left &= ~__builtin_amdgcn_ballot_w64(mine);
       }
@@ -766,8 +773,8 @@ __global__ __launch_bounds__(kTableThreads) __attribute__((amdgpu_waves_per_eu(s
       const int64_t gi = R.off + (int64_t)zz * sz + (int64_t)y * sy + x;
       const bool edge = x == 0 || x == R.ex - 1 || y == 0 || y == R.ey - 1 || zz == 0 || zz == R.ez - 1;
       if (edge && is_shared(L, R, x, y, zz)) write_partial<OP, V>(p, gi, a0, xprev, cd);  // finished by k_iface
-      else if constexpr (kPreB) contrib += finish_pre<OP, DOT, V, true>(p, gi, a0, 1, xprev, ctr, cb, cd);
-      else contrib += finish<OP, DOT, V, true>(p, gi, a0, 1, xprev, ctr);
+      else if constexpr (kPreB) contrib += finish_pre<OP, DOT, V, kOwn>(p, gi, a0, 1, xprev, ctr, cb, cd);
+      else contrib += finish<OP, DOT, V, kOwn>(p, gi, a0, 1, xprev, ctr);
       shift();
     }
     __syncthreads();
@@ -1246,8 +1253,8 @@ __global__ __launch_bounds__(kTableThreads) __attribute__((amdgpu_waves_per_eu(4
       }
       const bool edge = x == 0 || x == R.ex - 1 || y == 0 || y == R.ey - 1 || zz == 0 || zz == R.ez - 1;
       if (edge && is_shared(L, R, x, y, zz)) write_partial<OP, double>(p, gi, acc, xs, cd);  // finished by k_iface
-      else if constexpr (kPreB) contrib += finish_pre<OP, DOT, double, true>(p, gi, acc, 1, xs, ctr, cb, cd);
-      else contrib += finish<OP, DOT, double, true>(p, gi, acc, 1, xs, ctr);
+      else if constexpr (kPreB) contrib += finish_pre<OP, DOT, double, kOwnCentre>(p, gi, acc, 1, xs, ctr, cb, cd);
+      else contrib += finish<OP, DOT, double, kOwnCentre>(p, gi, acc, 1, xs, ctr);
       shift();
     }
     __syncthreads();
@@ -1402,9 +1409,18 @@ static int64_t run(const Level& L, const StencilArgs& a, hipStream_t st) {
         const int64_t nd = (int64_t)L.table_tiles.size(), no = (int64_t)(elem ? L.elem_tiles : L.other_tiles).size();
         RMG_REQUIRE(L.table_served.size() == (size_t)L.nreg, RMG_ERR_ARG, "internal: class tables without their split");
         if constexpr (kSameType) {
-          if (nd > 0)
-            RMG_LAUNCH((k_stencil_table<V, OP, DOT>), dim3(nd), dim3(kTableThreads), 0, st, v,
-                       L.d_table_tiles.as<Tile3>(), table, p, a.partials);
+          if (nd > 0) {
+            auto tables = [&](auto dinv) {
+              RMG_LAUNCH((k_stencil_table<V, OP, DOT, decltype(dinv)::value>), dim3(nd), dim3(kTableThreads), 0, st, v,
+                         L.d_table_tiles.as<Tile3>(), table, static_cast<const V*>(L.class_dinv_lo.p), p, a.partials);
+            };
+            if constexpr (sizeof(V) == 4 && (OP == StencilOp::Cheb || OP == StencilOp::ChebFirst)) {
+              if (L.use_tiles) tables(std::false_type());
+              else tables(std::true_type());
+            } else {
+              tables(std::false_type());
+            }
+          }
         }
         if constexpr (kSameType && std::is_same<V, double>::value) {
           if (elem)

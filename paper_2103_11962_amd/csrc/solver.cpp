@@ -265,6 +265,7 @@ static void configure_level(rmg_handle* h, Level& L, bool with_b, bool sym) {
     L.class_table_ok.release();
     L.class_table_lo.release();
     L.class_table_lo_ok.release();
+    L.class_dinv_lo.release();
     clear_split(L);
   }
 }
