@@ -263,6 +263,7 @@ static void begin_operator_change(rmg_handle* h, Level& L) {
   L.class_table_lo.release();
   L.class_table_lo_ok.release();
   L.class_dinv_lo.release();
+  L.tabled = L.tabled_lo = 0;
   L.elem.release();
   clear_split(L);
 }

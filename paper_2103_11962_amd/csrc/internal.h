@@ -187,12 +187,21 @@ struct LevelView {
   int ndof;          // unknowns per node (1, or 3 for elasticity)
 };
 
-// Levels of at most this many nodes finish their shared nodes in the node-block kernels themselves: there
-// an interface kernel is a launch and one more chain of dependent loads (4 to 8 us) for a few us of work.
-// Measured with the line at 100,000 and at 600,000 nodes: 8 regions of 82^3 (level 1 of 175,616 nodes)
-// 583 and 577 us a V-cycle, 700 x 720 five-point Gauss-Seidel (504,000 nodes) 10.99 and 10.92 ms a solve.
-// Above the line tiles run most levels, and their shared nodes are many.
+// Node-block levels finish their shared nodes in the stencil kernel itself up to these sizes: there an
+// interface kernel is a launch and one more chain of dependent loads (4 to 8 us), but the copies'
+// products are computed apart from their rows, a cache line a value for every coupling that is streamed.
+// A V-cycle on 2 to 1000 regions with the finest level fused, and with the interface kernel after it:
+// where the class tables serve every region (no couplings streamed) 27 x 28^3 nodes (593,000) 267 and
+// 272 us in FP64, 202 and 221 in FP32, 762 and 819 on 3 dofs; with more copies 729 x 9^3 (531,000 nodes,
+// 257,000 copies) 356 and 346, 216 x 13^3 (475,000, 160,000 copies) 299 and 298; 2D (few couplings and
+// copies) 9 x 240^2 (518,000) 165 and 173 us.
 constexpr int64_t kFuseNodes = 600000;
+constexpr int64_t kFuseCopies = 200000;
+// Couplings streamed in 3D: scalar 8 x 17^3 nodes (39,000) 94 and 105 us in FP64, 82 and 104 in FP32,
+// 27 x 13^3 (59,000) 124 and 110, 104 and 109, 27 x 25^3 (422,000) 332 and 250, 258 and 202; 3 dofs 8 x 10^3
+// (8,000) 157 and 173, 121 and 151, 64 x 7^3 (22,000) 264 and 238, 228 and 212.
+constexpr int64_t kFuseStream = 40000;
+constexpr int64_t kFuseStream3 = 10000;
 
 // Interface copies in blocks, for the node-block kernels that finish the shared nodes themselves (small
 // levels): block k serves copies start[k] .. start[k + 1], whole groups of at most kBlock copies together.
@@ -251,7 +260,7 @@ struct Level {
   DBuf d_gptr;    // int64 [ngroups+1]
   DBuf d_gcopy;   // int32 regional node indices
   DBuf d_gcomp;   // int32 composite node index of each group
-  // levels of at most kFuseNodes nodes: the interface copies in blocks (CopyView), else empty
+  // levels of at most kFuseNodes nodes and kFuseCopies copies: the copies in blocks (CopyView), else empty
   DBuf d_copies, d_copy_start;
   DBuf d_owner;  // with them: int32 per regional node, 1 on a group's first copy
   int ncopyblk = 0;
@@ -267,6 +276,7 @@ struct Level {
   // regions all of whose nodes have them; empty without class_table or a low-precision copy.
   DBuf class_table_lo, class_table_lo_ok;
   DBuf class_dinv_lo;  // FP32 copies of scalar levels: the classes' FP64 D~^-1 rounded, float [nreg][kClasses]
+  int tabled = 0, tabled_lo = 0;  // regions served: FP64 operations, low-precision V-cycle
   // With the tables: the served regions run whole-row tiles that take every coupling from the
   // tables (k_stencil_table), the other regions the level's streaming 2.5D tiles.  Built with the
   // tables (make_split), refreshed when the tiles change.
@@ -335,6 +345,10 @@ struct Level {
   CopyView copies() const { return {d_copies.as<int4>(), d_copy_start.as<int>(), ncopyblk}; }
   // shared nodes finished by the node-block kernels (the unbatched option keeps one launch per region)
   bool fused_groups() const { return n <= kFuseNodes && !per_region; }
+  bool fused_stencil(bool lowp) const {
+    if (per_region || ncopyblk == 0) return false;
+    return dim == 2 || (lowp ? tabled_lo : tabled) == nreg || n <= (ndof == 3 ? kFuseStream3 : kFuseStream);
+  }
 };
 
 }  // namespace rmg

@@ -2336,6 +2336,7 @@ static void make_class_table(Level& L, hipStream_t st) {
   RMG_HIP(hipStreamSynchronize(st));
   int served = 0;
   for (int f : flags) served += f != 0;
+  L.tabled = served;
   clear_split(L);
   if (served == 0) {  // no region served: drop the tables, so the streaming kernel runs
     tab.release();
@@ -2379,12 +2380,16 @@ static void make_class_table_lo(Level& L, hipStream_t st) {
     std::vector<int> flags(L.nreg);
     RMG_HIP(hipMemcpyAsync(flags.data(), ok, sizeof(int) * L.nreg, hipMemcpyDeviceToHost, st));
     RMG_HIP(hipStreamSynchronize(st));
-    for (int k = 0; k < L.nreg; ++k)
+    L.tabled_lo = 0;
+    for (int k = 0; k < L.nreg; ++k) {
+      L.tabled_lo += flags[k] != 0;
       if (!L.table_served.empty() && L.table_served[k] && !flags[k]) L.split_lo = false;
+    }
   } else {
     const int64_t ne = (int64_t)kClasses * kClassPts * L.ndof * L.ndof * L.nreg;
     launch_f64_to_f32(ne, L.class_table.as<double>(), tab, st);
     RMG_HIP(hipMemcpyAsync(ok, L.class_table_ok.p, sizeof(int) * L.nreg, hipMemcpyDeviceToDevice, st));
+    L.tabled_lo = L.tabled;
     if (L.ndof == 1) {
       const int64_t nd = (int64_t)kClasses * L.nreg;
       L.class_dinv_lo.alloc(sizeof(float) * nd);
@@ -2421,7 +2426,9 @@ bool launch_make_sym(Level& L, bool lowp, hipStream_t st, bool table) {
   L.class_table_lo.release();
   L.class_table_lo_ok.release();
   L.class_dinv_lo.release();
+  L.tabled_lo = 0;
   if (!lowp) {
+    L.tabled = 0;
     L.class_table.release();
     L.class_table_ok.release();
     clear_split(L);

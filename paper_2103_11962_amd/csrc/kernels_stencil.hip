@@ -291,8 +291,10 @@ __global__ __launch_bounds__(kBlock) void k_stencil_fused(LevelView L, CopyView 
   __shared__ V part[kBlock * NDOF];
   double contrib = 0.0;
   const int t = threadIdx.x;
-  if ((int)blockIdx.x < nb) {
-    const BlockDesc bd = L.blocks[blockIdx.x];
+  // node blocks: a contiguous run for every XCD, as in k_stencil
+  const int blk = (int)blockIdx.x < nb ? xcd_item((int)blockIdx.x, nb) : (int)blockIdx.x;
+  if (blk < nb) {
+    const BlockDesc bd = L.blocks[blk];
     const RegionGeo R = L.regs[bd.region];
     const int li = bd.start + t;
     if (li < R.n) {
@@ -307,7 +309,7 @@ __global__ __launch_bounds__(kBlock) void k_stencil_fused(LevelView L, CopyView 
       }
     }
   } else {
-    const int first = G.start[blockIdx.x - nb], cnt = G.start[blockIdx.x - nb + 1] - first;
+    const int first = G.start[blk - nb], cnt = G.start[blk - nb + 1] - first;
     int4 ci = make_int4(0, 0, 0, 0);
     int64_t n0 = 0;  // the group's first copy
     V uprev[NDOF];
@@ -360,7 +362,7 @@ __global__ __launch_bounds__(kBlock) void k_stencil_fused(LevelView L, CopyView 
   }
   if constexpr (DOT || OP == StencilOp::CgQ) {
     const double s = block_sum(contrib);
-    if (t == 0) partials[blockIdx.x] = s;
+    if (t == 0) partials[blk] = s;
   }
 }
 
@@ -1280,14 +1282,30 @@ __global__ __launch_bounds__(kTableThreads) __attribute__((amdgpu_waves_per_eu(4
 
 // ----------------------------------------------------------- interface groups
 // ng2: the first ng2 groups have two copies each (their copies start at 2 g, no gptr read).
-template <int NDOF, class V, StencilOp OP, bool DOT>
+// COPIES: the groups lie on the threads of their first copies in the blocks of k_stencil_fused (a sum is
+// then grouped as there).
+template <int NDOF, class V, StencilOp OP, bool DOT, bool COPIES>
 __global__ __launch_bounds__(kBlock) void k_iface(const int64_t* __restrict__ gptr, const int* __restrict__ gcopy,
-                                                  int64_t ng, int64_t ng2, OpP<V> p, double* __restrict__ partials) {
-  const int64_t g = (int64_t)blockIdx.x * kBlock + threadIdx.x;
+                                                  int64_t ng, int64_t ng2, CopyView G, OpP<V> p,
+                                                  double* __restrict__ partials) {
   double contrib = 0.0;
-  if (g < ng) {
-    const bool two = g < ng2;
-    const int64_t a0 = two ? 2 * g : gptr[g], e = two ? a0 + 2 : gptr[g + 1];
+  int64_t a0 = 0, e = 0;  // the group's copies
+  if constexpr (COPIES) {
+    const int first = G.start[blockIdx.x], cnt = G.start[blockIdx.x + 1] - first, t = threadIdx.x;
+    if (t < cnt) {
+      const int4 ci = G.info[first + t];
+      a0 = first + t;
+      e = ci.z == t ? a0 + ci.w : a0;
+    }
+  } else {
+    const int64_t g = (int64_t)blockIdx.x * kBlock + threadIdx.x;
+    if (g < ng) {
+      const bool two = g < ng2;
+      a0 = two ? 2 * g : gptr[g];
+      e = two ? a0 + 2 : gptr[g + 1];
+    }
+  }
+  if (e > a0) {
     const int m = (int)(e - a0);
     bool block = false;
     if constexpr (NDOF == 3 && (OP == StencilOp::Cheb || OP == StencilOp::ChebFirst)) {
@@ -1356,10 +1374,8 @@ static int64_t run(const Level& L, const StencilArgs& a, hipStream_t st) {
   const bool tiled = NPTS == 27 && ((NDOF == 1 && (L.use_tiles || split)) || split3);
   const int ntiles = (int)L.tiles.size();
   const int grid3 = (L.tile_grid > 0 && L.tile_grid < ntiles) ? L.tile_grid : ntiles;
-  // the interface groups in the node blocks' launch; unbatched levels (one launch per region, then the
-  // interface kernel) only where a sum is taken, so that it is grouped as the batched one
   constexpr bool kSums = DOT || OP == StencilOp::CgQ;
-  const bool fused = !tiled && L.n <= kFuseNodes && L.ncopyblk > 0 && (kSums || !L.per_region);
+  const bool fused = !tiled && L.fused_stencil(a.lowp);
   int64_t nparts = grid3;  // partial sums written by the tiled launches
   if constexpr (NDOF == 3 && DOT) {
     if (split3) {
@@ -1437,33 +1453,18 @@ static int64_t run(const Level& L, const StencilArgs& a, hipStream_t st) {
   if (!tiled) {
     const C* symc = static_cast<const C*>(a.lowp ? L.coef_lo_sym.p : L.coef_sym.p);
     if (fused) {
-      // nb node blocks of vk and nc copy blocks
-      auto blocks = [&](const LevelView& vk, int nb, int nc, double* part) {
-        const dim3 g(nb + nc), t(kBlock);
-        if constexpr (NPTS == 27) {
-          if (symc) {
-            RMG_LAUNCH((k_stencil_fused<NPTS, NDOF, V, C, OP, DOT, true>), g, t, 0, st, vk, L.copies(), nb, symc,
-                       centre, p, part, table, table_ok);
-            return;
-          }
-        }
-        RMG_LAUNCH((k_stencil_fused<NPTS, NDOF, V, C, OP, DOT, false>), g, t, 0, st, vk, L.copies(), nb, coef, centre,
-                   p, part, (const V*)nullptr, (const int*)nullptr);
-      };
       const int nb = (int)L.blocks.size();
-      if (L.per_region) {
-        for (int k = 0; k < L.nreg; ++k) {
-          const int b0 = L.region_block[k], n = L.region_block[k + 1] - b0;
-          if (n == 0) continue;
-          LevelView vk = v;
-          vk.blocks = v.blocks + b0;
-          vk.nblocks = n;
-          blocks(vk, n, 0, a.partials ? a.partials + b0 : nullptr);
-        }
-        blocks(v, 0, L.ncopyblk, a.partials ? a.partials + nb : nullptr);
-      } else {
-        blocks(v, nb, L.ncopyblk, a.partials);
+      const dim3 g(nb + L.ncopyblk), t(kBlock);
+      bool sym = false;
+      if constexpr (NPTS == 27) {
+        sym = symc != nullptr;
+        if (sym)
+          RMG_LAUNCH((k_stencil_fused<NPTS, NDOF, V, C, OP, DOT, true>), g, t, 0, st, v, L.copies(), nb, symc, centre, p,
+                     a.partials, table, table_ok);
       }
+      if (!sym)
+        RMG_LAUNCH((k_stencil_fused<NPTS, NDOF, V, C, OP, DOT, false>), g, t, 0, st, v, L.copies(), nb, coef, centre, p,
+                   a.partials, (const V*)nullptr, (const int*)nullptr);
       LAUNCH_CHECK();
       if (a.ev1) RMG_HIP(hipEventRecord(a.ev1, st));
       return kSums ? (int64_t)nb + L.ncopyblk : 0;
@@ -1498,12 +1499,24 @@ static int64_t run(const Level& L, const StencilArgs& a, hipStream_t st) {
   const int64_t nb = tiled ? nparts : (int64_t)L.blocks.size();
   int64_t ngb = 0;
   if (L.ngroups > 0) {
-    ngb = cdiv(L.ngroups, kBlock);
-    RMG_LAUNCH((k_iface<NDOF, V, OP, DOT>), dim3(ngb), dim3(kBlock), 0, st, L.d_gptr.as<int64_t>(),
-                       L.d_gcopy.as<int>(), L.ngroups, L.ngroups2, p, a.partials ? a.partials + nb : nullptr);
+    double* part = a.partials ? a.partials + nb : nullptr;
+    // node blocks of a level with copy blocks, whichever of its operations are fused, batched or not: one
+    // grouping of the sums
+    const bool copies = kSums && !tiled && L.ncopyblk > 0;
+    ngb = copies ? L.ncopyblk : cdiv(L.ngroups, kBlock);
+    auto iface = [&](auto c) {
+      RMG_LAUNCH((k_iface<NDOF, V, OP, DOT, decltype(c)::value>), dim3(ngb), dim3(kBlock), 0, st, L.d_gptr.as<int64_t>(),
+                 L.d_gcopy.as<int>(), L.ngroups, L.ngroups2, L.copies(), p, part);
+    };
+    if constexpr (kSums) {
+      if (copies) iface(std::true_type());
+      else iface(std::false_type());
+    } else {
+      iface(std::false_type());
+    }
     LAUNCH_CHECK();
   }
-  return (DOT || OP == StencilOp::CgQ) ? nb + ngb : 0;
+  return kSums ? nb + ngb : 0;
 }
 
 // FP64: every operation.

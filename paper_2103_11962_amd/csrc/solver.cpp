@@ -266,6 +266,7 @@ static void configure_level(rmg_handle* h, Level& L, bool with_b, bool sym) {
     L.class_table_lo.release();
     L.class_table_lo_ok.release();
     L.class_dinv_lo.release();
+    L.tabled = L.tabled_lo = 0;
     clear_split(L);
   }
 }
