@@ -187,8 +187,10 @@ typedef struct {
   int transfer_rows;  /* geometric restriction and prolongation (Section 3.3): 1 (default) by rows and
                          planes (a block owns whole rows of a region and walks its planes, staging
                          the values it reads in LDS) wherever every region's rows fit a block
-                         (coarse and fine rows of at most 256 nodes); 0 one thread per node.  Both
-                         give the same results bit for bit */
+                         (coarse and fine rows of at most 256 nodes), and the restriction into a coarse
+                         level of at most 200,000 nodes (batched = 1) together with its interface sum in
+                         one launch, one thread per coarse node; 0 one thread per node, the interface sum
+                         after it.  All give the same results bit for bit */
 } rmg_options;
 
 /* Filled by rmg_options_default with the values above. */
@@ -376,9 +378,10 @@ rmg_status rmg_kernel_launches(int64_t* count);
 /* 2.5D tile shape of `level`: the number of tiles, threads per tile block and planes per tile
  * (all 0 where the level runs node-parallel kernels).  Any output may be NULL. */
 rmg_status rmg_level_tiles(rmg_handle* h, int level, int* ntiles, int* threads, int* planes);
-/* Tiles of the transfers between `level` and the next coarser one (rmg_options.transfer_rows): the
- * restriction's and the prolongation's blocks, 0 where they run one thread per node (and on the
- * coarsest level).  Any output may be NULL. */
+/* Tiles of the transfers between `level` and the next coarser one as rmg_options.transfer_rows lays
+ * them out: the restriction's and the prolongation's blocks, 0 where transfers run one thread per node
+ * (and on the coarsest level).  The restriction's tiles wait unused where the coarse level is small
+ * enough for the one-launch restriction.  Any output may be NULL. */
 rmg_status rmg_level_transfer_tiles(rmg_handle* h, int level, int* restriction_tiles, int* prolongation_tiles);
 /* Regions of `level` whose couplings the FP64 V-cycle takes from the region's class table
  * (rmg_options.region_table); 0 where no table was built and with a low-precision V-cycle.

@@ -202,6 +202,11 @@ constexpr int64_t kFuseCopies = 200000;
 // (8,000) 157 and 173, 121 and 151, 64 x 7^3 (22,000) 264 and 238, 228 and 212.
 constexpr int64_t kFuseStream = 40000;
 constexpr int64_t kFuseStream3 = 10000;
+// Coarse levels of at most this many nodes take restriction, interface sum and zero-guess start in one
+// launch (k_restrict_all).  A V-cycle with the line above and below the coarse level: 8 x 28^3 coarse nodes
+// (176,000) 575 us by rows and planes, 569 in one launch, in FP32 537 and 536; 3 dofs 2814 and 2800; 64 x 16^3
+// (262,000) 810 and 841, 772 and 790; 27 x 28^3 (593,000) 1400 and 1445; 2D the same to 1% up to 1.3M nodes.
+constexpr int64_t kFuseRestrict = 200000;
 
 // Interface copies in blocks, for the node-block kernels that finish the shared nodes themselves (small
 // levels): block k serves copies start[k] .. start[k + 1], whole groups of at most kBlock copies together.
@@ -305,6 +310,7 @@ struct Level {
   // fine values (nodes times ndof) a restriction tile stages per plane.
   std::vector<Tile3> rtiles, ptiles;  // a prolongation tile's rows reach at most kProlongStageXY coarse nodes a plane
   DBuf d_rtiles, d_ptiles;
+  bool node_transfers = false;  // rmg_options.transfer_rows = 0
   int64_t rtile_vals = 0;
   DBuf dinv;      // double [n * ndof]: 1 / point diagonal of the composite operator
   DBuf dinv9;     // block_diag (3-dof levels): inverse nodal 3 x 3 blocks of D~, double [n][9] row-major
@@ -344,7 +350,9 @@ struct Level {
   LevelView view() const;
   CopyView copies() const { return {d_copies.as<int4>(), d_copy_start.as<int>(), ncopyblk}; }
   // shared nodes finished by the node-block kernels (the unbatched option keeps one launch per region)
-  bool fused_groups() const { return n <= kFuseNodes && !per_region; }
+  bool fused_restriction() const {  // into this level
+    return n <= kFuseRestrict && !per_region && (ngroups == 0 || ncopyblk > 0);
+  }
   bool fused_stencil(bool lowp) const {
     if (per_region || ncopyblk == 0) return false;
     return dim == 2 || (lowp ? tabled_lo : tabled) == nreg || n <= (ndof == 3 ? kFuseStream3 : kFuseStream);

@@ -831,7 +831,7 @@ static bool restrict_t(const Level& F, const Level& C, const V* r, V* w, hipStre
   // Small coarse levels: restriction, interface sum and zero-guess start in one launch.  Against the
   // rows-and-planes kernel, k_iface_sum and k_cheb_zero: 64 regions of 10^3 coarse nodes 16.3 + 6.9 + 4.8
   // and 26.4 us, 85,000 ragged 17.6 + 5.6 + 3.8 and 23.9 us, 6,000 ragged 14.1 + 5.0 + 2.2 and 12.8 us.
-  if (!pw && C.fused_groups() && (C.ngroups == 0 || C.ncopyblk > 0)) {
+  if (!pw && !F.node_transfers && C.fused_restriction()) {
     const V* dinv = start ? static_cast<const V*>(start->dinv) : nullptr;
     V* u = start ? static_cast<V*>(start->u) : nullptr;
     const V c0 = start ? (V)start->c : (V)0;

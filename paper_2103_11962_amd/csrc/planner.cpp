@@ -344,6 +344,7 @@ void make_transfer_tiles(Level& F, const Level& C, bool rows_and_planes) {
   F.rtiles.clear();
   F.ptiles.clear();
   F.rtile_vals = 0;
+  F.node_transfers = !rows_and_planes;
   auto cpos = [](int c, int e) { return std::min(3 * c, e - 1); };
   // start of the coarse interval of fine node g (the next coarse node for an interval's end node)
   auto lo_of = [](int g, int e, int E) {
