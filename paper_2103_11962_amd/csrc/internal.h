@@ -285,7 +285,9 @@ struct Level {
   // With the tables: the served regions run whole-row tiles that take every coupling from the
   // tables (k_stencil_table), the other regions the level's streaming 2.5D tiles.  Built with the
   // tables (make_split), refreshed when the tiles change.
-  bool split_lo = true;              // the low-precision tables serve the same regions
+  bool lowp_cycle = false;           // the handle's V-cycle runs in low precision
+  bool fill_lo = true;               // the split's tiles are filled enough for FP32 operations
+  bool split_lo = true;              // and run them
   bool use_split = false;            // run the split (an autotuned level may prefer node blocks)
   bool split_auto = false;           // a level without 2.5D tiles may run table tiles when they serve all of it
   // the split also runs the CG product, whose (p, q) sums follow the launch's tiles: not with an FP32
@@ -451,6 +453,8 @@ bool elem_fits(const Level& L, const std::vector<int>& served);
 // Clears the flags of the regions whose rows do not fit a table tile (extents along x from 340 on);
 // returns how many stay set.
 int table_tile_regions(const Level& L, std::vector<int>& served);
+// Share of the lanes that hold a node, of the tiles that make_split would lay out.
+double split_fill(const Level& L, const std::vector<int>& served, bool elem);
 // The same for a 3-dof level all of whose regions are served (k_stencil_table3); false if a region's
 // rows do not fit.
 bool make_split3(Level& L);

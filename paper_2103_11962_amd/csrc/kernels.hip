@@ -2311,11 +2311,26 @@ static void class_table_launch(const Level& L, const C* sym, const float* centre
   LAUNCH_CHECK();
 }
 
-// Scalar levels below the 2.5D tiles' size take table tiles instead of node blocks from this many
-// nodes on.  A Chebyshev step on node blocks and on table tiles: 8 regions of 28^3 (176k nodes) 12 us
-// each, 12 ragged regions of 1.9M nodes 50 and 24 us, 8 regions of 82^3 (4.4M) 125 and 40 us; below,
-// a step is a few microseconds of latency either way and the tiles are too few for the chip.
-constexpr int64_t kTableMinNodes = 150000;
+// Scalar levels below the 2.5D tiles' size run table tiles instead of node blocks, and element tiles for the
+// regions of element-wise coefficients, from these many nodes on, where the tiles' lanes are filled to
+// that share (a tile holds at most the plane of a region).  V-cycles with the finest level on node blocks
+// and on tiles, FP64 Laplacian: 8 x 28^3 (176,000 nodes) 135 and 179 us, 8 x 37^3 (405,000) 198 and 198,
+// 27 x 25^3 (422,000) 232 and 223, 8 x 46^3 (779,000) 293 and 225, 8 x 61^3 (1.8M) 527 and 347; by fill, 512 x 12^3
+// (0.28) 474 and 483, 1000 x 10^3 (0.20) 491 and 684, 216 x 13^3 (0.33) 300 and 297, 1331 x 13^3 1155 and 1029.
+// An FP32 cycle, whose node blocks stream at half the bytes: 125 x 20^3 (1.0M) 341 and 348, 8 x 61^3 347 and
+// 316 (and the FP64 product of CG gains as above).  Element tiles: 27 x 25^3 250 and 251, 216 x 13^3 286 and
+// 306, 8 x 43^3 (636,000) 282 and 261, 125 x 20^3 442 and 388.
+constexpr int64_t kTableMinNodes = 400000, kTableMinNodesLo = 1000000, kElemMinNodes = 600000;
+constexpr double kTableMinFill = 0.3;
+// FP32 cycles also leave 2.5D tiles that are not asked for (stencil_kernel) only from this fill on: 2197 x 12^3 nodes (0.28) 1204 us on 2.5D tiles and 1348
+// on table tiles, 2197 x 14^3 (0.38) 1545 and 1563, 2197 x 17^3 (0.56) 2668 and 1996; FP64 2968 and 2211 already
+// at 12^3.
+constexpr double kTableMinFillLo = 0.4;
+// Scalar low-precision node blocks read class tables on levels that finish their shared nodes themselves
+// (216 x 13^3: 227 us a V-cycle, streaming 255) and on rows of this mean length; else they stream: 1000 x 10^3
+// 366 us streaming and 427 from tables, 216 x 18^3 378 and 437, 125 x 25^3 505 and 553, 27 x 46^3 538 and 527,
+// 200 x (200 x 6 x 6) 435 and 403.
+constexpr double kTableMinRowLo = 46;
 
 // 3-dof levels: table tiles from this many nodes on.  On 185k nodes (27 regions of 19^3) a step takes
 // 110 us in tiles, whose few planes do not cover their start-up, and 30 us on node blocks; on 4.5M
@@ -2351,11 +2366,14 @@ static void make_class_table(Level& L, hipStream_t st) {
   // those other regions: assembled on the fly where the level has its elements
   const bool elem = L.elem.p && tabled < L.nreg && elem_fits(L, flags);
   if (tabled == 0 && !elem) return;
-  if (L.use_tiles) {
+  const double fill = split_fill(L, flags, elem);
+  // (the low-precision cycle streams the 2.5D tiles of a level whose split only FP64 products run)
+  L.fill_lo = !L.split_auto || fill >= kTableMinFillLo;
+  const int64_t least = elem ? kElemMinNodes : (L.lowp_cycle ? kTableMinNodesLo : kTableMinNodes);
+  if (L.use_tiles || (L.split_auto && (tabled == L.nreg || elem) && L.n >= least &&
+                      fill >= (L.lowp_cycle && !elem ? kTableMinFillLo : kTableMinFill)))
     make_split(L, flags, elem);
-  } else if (L.split_auto && (tabled == L.nreg || elem) && L.n >= kTableMinNodes) {
-    make_split(L, flags, elem);
-  }  // else node blocks: each block of a served region reads the tables
+  // else node blocks: each block of a served region reads the tables
 }
 
 __global__ void k_class_dinv(int64_t n, const double* __restrict__ table, float* __restrict__ dinv) {
@@ -2367,7 +2385,17 @@ __global__ void k_class_dinv(int64_t n, const double* __restrict__ table, float*
 // so the FP32 copy is served where the FP64 operator is; the centre blocks beside BF16 storage carry
 // a row-sum correction, and the check clears regions where those differ within a class.
 static void make_class_table_lo(Level& L, hipStream_t st) {
-  L.split_lo = true;
+  L.split_lo = L.fill_lo;
+  if (L.ndof == 1) {
+    const bool tiles = L.use_split && L.split_lo && L.ct_lo == kCoefF32 && (L.use_tiles || L.other_tiles.empty());
+    int64_t rows = 0;
+    for (const RegionGeo& R : L.regs) rows += (int64_t)R.ey * R.ez;
+    const bool nodes = !L.use_tiles && (L.ncopyblk > 0 || (double)L.n >= kTableMinRowLo * (double)rows);
+    if (!tiles && !nodes) {
+      L.split_lo = false;
+      return;
+    }
+  }
   L.class_table_lo.alloc(sizeof(float) * kClasses * kClassPts * L.ndof * L.ndof * L.nreg);
   L.class_table_lo_ok.alloc(sizeof(int) * L.nreg);
   float* tab = L.class_table_lo.as<float>();

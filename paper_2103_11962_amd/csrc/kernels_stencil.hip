@@ -1368,7 +1368,7 @@ static int64_t run(const Level& L, const StencilArgs& a, hipStream_t st) {
   // region-table split: the served regions' whole-row tiles, then the other regions' element tiles or
   // 2.5D tiles
   const bool elem = NPTS == 27 && NDOF == 1 && std::is_same<V, double>::value && kSameType && !L.elem_tiles.empty();
-  const bool split = NPTS == 27 && NDOF == 1 && kSameType && L.use_split && (table || elem) &&
+  const bool split = NPTS == 27 && NDOF == 1 && kSameType && L.use_split && (table || elem) && (!a.lowp || L.split_lo) &&
                      (L.use_tiles || elem || L.other_tiles.empty()) && (OP != StencilOp::CgQ || L.split_dot);
   const bool split3 = NPTS == 27 && NDOF == 3 && L.use_split && table && (!a.lowp || L.split_lo);
   const bool tiled = NPTS == 27 && ((NDOF == 1 && (L.use_tiles || split)) || split3);

@@ -233,6 +233,18 @@ int table_tile_regions(const Level& L, std::vector<int>& served) {
   return n;
 }
 
+double split_fill(const Level& L, const std::vector<int>& served, bool elem) {
+  double nodes = 0.0, lanes = 0.0;
+  for (int k = 0; k < L.nreg; ++k) {
+    if (!served[k] && !elem) continue;
+    const RegionGeo& R = L.regs[k];
+    const int ty = served[k] ? table_rows(R) : elem_rows(R);
+    nodes += R.n;
+    lanes += (double)((R.ey + ty - 1) / ty) * R.ez * kTableThreads;
+  }
+  return lanes > 0.0 ? nodes / lanes : 0.0;
+}
+
 // Whole-row tiles of region k, at most ty rows and `planes` planes, both shared out evenly.
 static void add_tiles(const RegionGeo& R, int k, int tymax, int planes, std::vector<Tile3>& out) {
   const int nty = (R.ey + tymax - 1) / tymax;

@@ -254,7 +254,8 @@ static void configure_level(rmg_handle* h, Level& L, bool with_b, bool sym) {
   if (sym) {
     // class tables for the 2.5D tiles and for the levels run by node blocks
     const bool tables = o.region_table != 0 && L.npts == 27 && !L.per_region;
-    L.split_lo = true;
+    L.lowp_cycle = !fp64;
+    L.split_lo = L.fill_lo = true;
     L.split_auto = o.stencil_kernel == 0;
     L.split_dot = fp64 || L.split_auto;
     L.deep_table = o.tile_planes != 0;
