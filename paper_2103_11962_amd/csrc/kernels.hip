@@ -2332,10 +2332,22 @@ constexpr double kTableMinFillLo = 0.4;
 // 200 x (200 x 6 x 6) 435 and 403.
 constexpr double kTableMinRowLo = 46;
 
-// 3-dof levels: table tiles from this many nodes on.  On 185k nodes (27 regions of 19^3) a step takes
-// 110 us in tiles, whose few planes do not cover their start-up, and 30 us on node blocks; on 4.5M
-// nodes 272 and 405 us.
-constexpr int64_t kTable3MinNodes = 400000;
+// 3-dof levels run table tiles from these many nodes on, by the mean of their regions' shorter plane edge
+// min(ex, ey) (harmonic, weighted by nodes): short rows leave lanes idle, and the x-face columns take a
+// wavefront each.  V-cycles with the finest level on node blocks and on tiles, FP64: edge 28, 27 regions
+// (593,000 nodes) 748 and 1206 us, 343 regions (7.5M) 6998 and 8779; 64 x 40^3 (4.1M) 3555 and 4182; 43, 27
+// regions (2.1M) 1849 and 1880; 46 (2.6M) 2258 and 2207; 48 (3.0M) 2541 and 2319; 55, 8 regions (1.3M) 1193 and
+// 1227, 27 (4.5M) 3675 and 2973; 8 x 61^3 (1.8M) 1527 and 1338; 2 x 64^3 (524,000) 600 and 656, 4 x 64^3 (1.0M)
+// 950 and 874; 100^3 821 and 652.  FP32 cycles cross at the same sizes (55: 793 and 756, 2088 and 1689).
+constexpr int64_t kTable3MinNodes = 1500000, kTable3MinNodesLong = 900000;
+constexpr double kTable3MinEdge = 44, kTable3LongEdge = 60;
+
+static bool table3_pays(const Level& L) {
+  double s = 0.0;
+  for (const RegionGeo& R : L.regs) s += (double)R.n / std::min(R.ex, R.ey);
+  const double edge = (double)L.n / s;
+  return edge >= kTable3MinEdge && L.n >= (edge >= kTable3LongEdge ? kTable3MinNodesLong : kTable3MinNodes);
+}
 
 static void make_class_table(Level& L, hipStream_t st) {
   DBuf& tab = L.class_table;
@@ -2358,7 +2370,7 @@ static void make_class_table(Level& L, hipStream_t st) {
     ok.release();
   }
   if (L.ndof == 3) {
-    if (served == L.nreg && L.split_auto && (L.deep_table || L.n >= kTable3MinNodes)) make_split3(L);
+    if (served == L.nreg && L.split_auto && (L.deep_table || table3_pays(L))) make_split3(L);
     return;
   }
   // regions whose rows are too long for a table tile stream like those that the tables do not serve

@@ -76,3 +76,29 @@ def test_fp32_small_planes_stream_on_tiles(hip_device):
         got.append(z)
         h.close()
     assert torch.equal(got[0], got[2])
+
+
+# (extents, options, table tiles): 3-dof levels by size and by the shorter edge of their planes
+CASES3 = [
+    ([[28] * 3] * 3, dict(), False),  # 593,000 nodes, edge 28
+    ([[40] * 3] * 3, dict(), False),  # 1.7M, edge 40
+    ([[50] * 2] * 3, dict(), False),  # 1.0M, edge 50
+    ([[58] * 2] * 3, dict(), True),  # 1.6M, edge 58
+    ([[97], [97], [97]], dict(), True),  # 913,000, edge 97
+    ([[97], [97], [97]], dict(precision=1), True),
+    ([[25, 30], [61, 61], [120, 120]], dict(), False),  # 1.6M, short rows
+    ([[61, 61], [25, 30], [120, 120]], dict(), False),  # 1.6M, short planes
+    ([[10, 7], [9], [12]], dict(tile_planes=21), True),  # asked for
+]
+
+
+@pytest.mark.parametrize("case", range(len(CASES3)))
+def test_table3_rules(hip_device, case):
+    ext, opts, table = CASES3[case]
+    print(f"[rules3] {CASES3[case]}", flush=True)
+    o, e = synth.tensor_layout(ext)
+    w = synth.Workload("rules3", 3, 3, o, e, 63, 4 if len(e) > 2 or ext[0][0] > 50 else 2, 2, "elasticity", h=0.1, seed=case)
+    h = harness.gpu_problem(w, **opts)
+    assert (h.level_split(0)["table_tiles"] > 0) == table
+    assert len(e) == (h.level_split(0)["regions_lo"] if opts.get("precision") else h.level_table_regions(0))
+    h.close()
