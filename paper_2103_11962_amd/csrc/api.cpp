@@ -211,7 +211,7 @@ rmg_status rmg_build_regions(rmg_handle* h, int dim, int ndof, int nreg, const i
   RMG_REQUIRE(ndof == 1 || (ndof == 3 && dim == 3), RMG_ERR_ARG, "ndof must be 1, or 3 with dim 3");
   RMG_REQUIRE(nreg >= 1 && extent && origin, RMG_ERR_ARG, "need nreg >= 1 and extent/origin arrays");
   RMG_REQUIRE(mask < (1u << (2 * dim)), RMG_ERR_ARG, "dirichlet mask has bits beyond 2*dim");
-  h->have_regions = h->have_operator = h->have_hierarchy = false;
+  h->have_regions = h->have_operator = h->have_hierarchy = h->was_setup = false;
   h->recycler.flush();
   hybrid_destroy(h);
   amg_destroy(h);
@@ -274,17 +274,22 @@ rmg_status rmg_set_region_stencil(rmg_handle* h, int region, int npts, const dou
   Level& L = level_of(h, 0);
   RMG_REQUIRE(region >= 0 && region < h->nreg, RMG_ERR_ARG, "region index out of range");
   RMG_REQUIRE(coef != nullptr, RMG_ERR_ARG, "null coefficient pointer");
-  RecycleScope keep(h->recycler, false);
   const bool ok = (h->dim == 3 && npts == 27) || (h->dim == 2 && (npts == 5 || npts == 9));
   RMG_REQUIRE(ok, RMG_ERR_ARG, "npts must be 27 in 3D and 5 or 9 in 2D");
   bool any = false;
   for (bool b : h->region_set) any = any || b;
   RMG_REQUIRE(!any || L.npts == npts, RMG_ERR_ARG, "all regions must use the same stencil size");
-  begin_operator_change(h, L);
-  h->region_set[region] = false;
-  if (!any || L.npts != npts || !L.coef.p) {
-    L.npts = npts;
-    L.coef.alloc(sizeof(double) * coef_elems(L.n, L.ncoef()));
+  const bool fresh = !any || L.npts != npts || !L.coef.p;
+  {
+    RecycleScope keep(h->recycler, false);
+    begin_operator_change(h, L);
+    h->region_set[region] = false;
+    if (fresh) {
+      L.npts = npts;
+      L.coef.alloc(sizeof(double) * coef_elems(L.n, L.ncoef()));
+    }
+  }
+  if (fresh) {
     RMG_HIP(hipMemsetAsync(L.coef.p, 0, sizeof(double) * coef_elems(L.n, L.ncoef()), h->stream));
   }
   const RegionGeo& R = L.regs[region];
@@ -341,10 +346,13 @@ static void check_composite_split(rmg_handle* h, int npts) {
 
 // Region matrices from a device composite stencil [npts][ncomp].
 static void split_into_regions(rmg_handle* h, Level& L, int npts, const double* src) {
-  begin_operator_change(h, L);
-  h->region_set.assign(h->nreg, false);
-  L.npts = npts;
-  L.coef.alloc(sizeof(double) * coef_elems(L.n, npts));
+  {
+    RecycleScope keep(h->recycler, false);
+    begin_operator_change(h, L);
+    h->region_set.assign(h->nreg, false);
+    L.npts = npts;
+    L.coef.alloc(sizeof(double) * coef_elems(L.n, npts));
+  }
   DBuf flag;
   flag.alloc(sizeof(int));
   RMG_HIP(hipMemsetAsync(flag.p, 0, sizeof(int), h->stream));
@@ -364,7 +372,6 @@ rmg_status rmg_set_composite_stencil(rmg_handle* h, int npts, const double* coef
   Level& L = level_of(h, 0);
   RMG_REQUIRE(coef != nullptr, RMG_ERR_ARG, "null coefficient pointer");
   check_composite_split(h, npts);
-  RecycleScope keep(h->recycler, false);
   DBuf tmp;
   const double* src = coef;
   if (!on_device) {
@@ -383,7 +390,6 @@ rmg_status rmg_set_composite_csr(rmg_handle* h, int npts, int64_t nnz, const int
   Level& L = level_of(h, 0);
   RMG_REQUIRE(rowptr && (nnz == 0 || (colind && values)) && nnz >= 0, RMG_ERR_ARG, "null CSR array or nnz < 0");
   check_composite_split(h, npts);
-  RecycleScope keep(h->recycler, false);
   const int64_t n = L.ncomp;
   // row pointers are checked on the host before any kernel reads through them
   std::vector<int64_t> rp(n + 1);
@@ -414,7 +420,10 @@ rmg_status rmg_set_composite_csr(rmg_handle* h, int npts, int64_t nnz, const int
     }
   }
   // the conversion reads the level's stencil size: from here on level 0 changes
-  begin_operator_change(h, L);
+  {
+    RecycleScope keep(h->recycler, false);
+    begin_operator_change(h, L);
+  }
   h->region_set.assign(h->nreg, false);
   L.npts = npts;
   comp.alloc(sizeof(double) * (size_t)npts * n);
@@ -498,6 +507,14 @@ rmg_status rmg_assemble_q1(rmg_handle* h, int pde, double hsize, const double* e
   API_END
 }
 
+// Whether two setups of one handle take buffers of the same sizes (but for what the operator decides).
+static bool same_buffers(const rmg_options& a, const rmg_options& b) {
+  return a.nlevels == b.nlevels && a.precision == b.precision && a.smoother == b.smoother &&
+         a.symmetric == b.symmetric && a.batched == b.batched && a.hybrid == b.hybrid && a.coarse_amg == b.coarse_amg &&
+         a.amg_coarse_size == b.amg_coarse_size && a.region_table == b.region_table && a.block_diag == b.block_diag &&
+         a.galerkin_generic == b.galerkin_generic;
+}
+
 rmg_status rmg_setup_hierarchy(rmg_handle* h, const rmg_options* opt) {
   API_BEGIN
   use_device(h);
@@ -550,17 +567,21 @@ rmg_status rmg_setup_hierarchy(rmg_handle* h, const rmg_options* opt) {
               "the AMG coarse solver belongs to the geometric region hierarchy (not the hybrid one)");
   RMG_REQUIRE(!opt->coarse_amg || h->ndof == 1 || (h->ndof == 3 && h->dim == 3), RMG_ERR_ARG,
               "the AMG coarse solver handles scalar problems and 3D elasticity");
+  const bool again = h->was_setup && same_buffers(h->opt, *opt);
+  h->was_setup = false;
   h->opt = *opt;
   h->autotune_cache = opt->autotune_cache ? std::string(opt->autotune_cache) : std::string();
   h->opt.autotune_cache = nullptr;  // the caller's string is borrowed for this call only
   h->have_hierarchy = false;
   h->drop_graphs();
   const auto t0 = std::chrono::steady_clock::now();
-  RecycleScope keep(h->recycler, true);
+  // a repeat of the last setup needs the same buffers again; one of other sizes gives the old ones back first
+  if (!again) h->recycler.flush();
+  RecycleScope keep(h->recycler, true, again);
   setup_hierarchy(h);
   RMG_HIP(hipStreamSynchronize(h->stream));
   h->setup_ms = std::chrono::duration<double, std::milli>(std::chrono::steady_clock::now() - t0).count();
-  h->have_hierarchy = true;
+  h->have_hierarchy = h->was_setup = true;
   API_END
 }
 

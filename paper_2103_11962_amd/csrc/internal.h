@@ -45,10 +45,10 @@ DevAlloc& current_allocator();
 // Large device buffers that a handle's rebuild of its operator or hierarchy released, kept for the
 // rest of that rebuild: a repeated assembly and setup needs the same sizes again, and giving 12 GB
 // back and asking for them anew costs more than the setup where the driver has to wipe them (a step
-// of assembly, setup and solve on 64 regions of 82^3 took 84 ms or up to 457 ms).  Filled only inside
-// the entry points that set an operator or the hierarchy, emptied at the end of the setup, before a
-// new set of regions, when an allocation fails and with the handle; what it holds between an
-// assembly and its setup, the handle held before the assembly.
+// of assembly, setup and solve on 64 regions of 82^3 took 84 ms or up to 457 ms).  Filled only where
+// an operator's or a hierarchy's own buffers change, emptied at the end of the setup, before a setup
+// with other options than the last, before a new set of regions, when an allocation fails and with the
+// handle; what it holds between an assembly and its setup, the handle held before the assembly.
 struct Recycler {
   struct Entry {
     void* p;
@@ -77,11 +77,12 @@ struct AllocatorScope {
     current_recycler() = saved_recycler;
   }
 };
-// Opens a handle's recycler for the rest of an entry point; flush: and empties it at the end.
+// Opens a handle's recycler for a block (open: unless told otherwise); flush: and empties it at its end.
+// Staging buffers that a call frees for good are declared outside it.
 struct RecycleScope {
   Recycler& r;
   bool flush;
-  RecycleScope(Recycler& r_, bool flush_) : r(r_), flush(flush_) { r.open = true; }
+  RecycleScope(Recycler& r_, bool flush_, bool open = true) : r(r_), flush(flush_) { r.open = open; }
   ~RecycleScope() {
     r.open = false;
     if (flush) r.flush();
@@ -384,12 +385,14 @@ struct Amg;     // amg.cpp
 }
 
 struct rmg_handle {
+  rmg::Recycler recycler;  // (before the buffers below: destroyed after them)
   int device = 0;
   hipStream_t stream = nullptr;
   int dim = 0, ndof = 1, nreg = 0;
   unsigned mask = 0;
   std::vector<int32_t> extent, origin;  // finest level, [nreg][3] (2D padded)
   bool have_regions = false, have_operator = false, have_hierarchy = false;
+  bool was_setup = false;  // the last setup for these regions succeeded (its operator may have changed since)
   std::vector<bool> region_set;
   rmg_options opt{};
   std::vector<rmg::Level*> levels;
@@ -424,7 +427,6 @@ struct rmg_handle {
   rmg::Hybrid* hy = nullptr;
   rmg::Amg* amg = nullptr;  // AMG coarse solver below the region hierarchy (coarse_amg = 1)
   rmg::DevAlloc alloc;     // device memory provider (empty: hipMalloc)
-  rmg::Recycler recycler;
   double setup_ms = 0.0;   // wall time of the last rmg_setup_hierarchy
   ~rmg_handle();
 };
