@@ -94,8 +94,9 @@ typedef struct {
                          stencil_kernel */
   int use_graph;      /* 1: rmg_solve captures the two halves of a CG iteration (around the
                          host convergence check) as HIP graphs once and replays them */
-  const char* autotune_cache; /* text file of autotuner choices keyed by level shape and
-                         precision; read before tuning, appended after (NULL: no file) */
+  const char* autotune_cache; /* text file of autotuner choices keyed by level shape, precision
+                         and what the region tables serve; read before tuning, appended after
+                         (NULL: no file) */
   int smoother;       /* 0 (default): Chebyshev of degree cheb_degree (Section 3.4, Algorithm 2);
                          1: damped Jacobi, cheb_degree sweeps of u += jacobi_omega D~^-1 r
                          (Section 3.4, the smoother of Table 1);

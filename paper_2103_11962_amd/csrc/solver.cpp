@@ -136,9 +136,16 @@ struct TuneChoice {
   int grid;   // persistent grid size
 };
 
+// What a choice was timed on: the level's shape (all extents), the precision, and which kernels the tiles and
+// the node blocks are there (regions on class tables, element tiles).
 static std::string tune_key(const Level& L, int level, int precision) {
+  uint64_t shape = 1469598103934665603ull;  // FNV-1a
+  for (const RegionGeo& R : L.regs)
+    for (int e : {R.ex, R.ey, R.ez}) shape = (shape ^ (uint64_t)(uint32_t)e) * 1099511628211ull;
   std::string k = "n" + std::to_string(L.n) + "_r" + std::to_string(L.nreg) + "_l" + std::to_string(level) + "_p" +
-                  std::to_string(precision);
+                  std::to_string(precision) + "_e" + std::to_string(shape) + "_t" + std::to_string(L.tabled) + "." +
+                  std::to_string(L.tabled_lo) + "." + std::to_string(L.table_tiles.size()) + "_x" +
+                  std::to_string(L.elem_tiles.size());
   for (int i = 0; i < std::min(L.nreg, 4); ++i)
     k += "_" + std::to_string(L.regs[i].ex) + "x" + std::to_string(L.regs[i].ey) + "x" + std::to_string(L.regs[i].ez);
   return k;
@@ -175,6 +182,10 @@ static void autotune_level(rmg_handle* h, Level& L, int level, bool lowp) {
     }
   }
   std::vector<TuneChoice> cands = {{0, 21, 0}, {1, 11, 0}, {1, 21, 0}, {1, 41, 0}, {2, 21, 256}, {2, 21, 512}, {2, 21, 1024}};
+  // table and element tiles have a depth of their own: where they cover the level, one candidate
+  const bool covered = !L.table_served.empty() && (lowp ? L.split_lo && L.class_table_lo.p && L.ct_lo == kCoefF32 && L.other_tiles.empty()
+                                                        : L.other_tiles.empty() || !L.elem_tiles.empty());
+  if (covered) cands = {{0, L.tile_depth, 0}, {1, L.tile_depth, 0}};
   const size_t vb = (lowp ? sizeof(float) : sizeof(double)) * (size_t)L.ndofs();
   void* vec[5] = {lowp ? L.u32.p : L.u.p, lowp ? L.u232.p : L.u2.p, lowp ? L.d32.p : L.d.p,
                   lowp ? L.r32.p : L.r.p, lowp ? L.b32.p : L.b.p};
