@@ -365,7 +365,12 @@ static int build_levels(rmg_handle* h, bool stored) {
       launch_make_lowp(L, (l == 0 && o.precision == RMG_PREC_FP32_BF16) ? kCoefBF16 : kCoefF32, st);
       if (o.symmetric) launch_make_sym(L, true, st, false);
     }
-    if (o.autotune && !L.per_region && L.dim == 3 && L.ndof == 1 && L.npts == 27) autotune_level(h, L, l, lowp);
+    if (o.autotune && !L.per_region && L.dim == 3 && L.ndof == 1 && L.npts == 27) {
+      autotune_level(h, L, l, lowp);
+      // (shallower tiles: more partial sums)
+      const size_t need = sizeof(double) * (size_t)partial_capacity(L);
+      if (l == 0 && need > h->partials.bytes) h->partials.alloc(need);
+    }
   }
   if (lowp) h->cg_z32.alloc(sizeof(float) * (size_t)L0->ndofs());
   RMG_HIP(hipStreamSynchronize(st));

@@ -1,9 +1,10 @@
 """Autotuner choices belong to the kernels they were timed on: a choice written without class tables is not read for
 a level that they serve, nor one of other regions; levels that table tiles cover have no choice of depth
-or grid.
+or grid; a choice of shallower tiles than the default has room for its partial sums.
 """
 import re
 
+import numpy as np
 import pytest
 
 import synth
@@ -38,3 +39,28 @@ def test_covered_levels_have_two_candidates(hip_device, tmp_path, precision):
         h = harness.gpu_problem(w, stencil_kernel=2, tile_planes=41, precision=precision, autotune=1)
         assert re.search(r"mode [01] depth 41 grid 0 ", h.tune_report()), h.tune_report()
         h.close()
+
+
+def test_shallow_tiles_have_room(hip_device, tmp_path):
+    """256 columns of 2 x 2 x 12 nodes: one node block a region, two tiles of eleven planes at most."""
+    import torch
+
+    cache = tmp_path / "tune.txt"
+    print("[autotune] shallow tiles", flush=True)
+    o, e = synth.tensor_layout([[2] * 16, [2] * 16, [12]])
+    w = synth.Workload("shallow", 3, 1, o, e, 48, 2, 2, "laplace", h=0.1)
+    b = harness.to_dev(synth.rhs(w))
+    got = []
+    for opts in (dict(autotune=1, autotune_cache=str(cache)), dict(autotune=1, autotune_cache=str(cache)), dict()):
+        h = harness.gpu_problem(w, **opts)
+        if got:
+            assert ("cached mode 1 depth 11" in h.tune_report()) == bool(opts)
+        x = torch.zeros_like(b)
+        out = h.solve(b, x, rtol=1e-8, maxit=300)
+        got.append((x.cpu().numpy(), out["iterations"]))
+        h.close()
+        if len(got) == 1:  # the same level, told to take eleven planes a tile
+            cache.write_text(re.sub(r" \d+ \d+ \d+$", " 1 11 0", cache.read_text(), flags=re.M))
+    for x, it in got[:2]:
+        assert it == got[2][1]
+        harness.assert_close(x, got[2][0], 1e-10)
