@@ -252,8 +252,9 @@ __global__ __launch_bounds__(B == 16 ? 256 : (B == 8 ? 512 : 1024)) void k_gs_sw
   double* dd = delta + R.off;
   const double* cw =
       cs + ((BACKWARD ? nrec : 0) + rec0[blockIdx.x] + (int64_t)min(w, nw - 1) * ts) * NV * 64 + lane;
-  // staged element i of this lane: row i RPI + srow, column scol of the chunk.  Lanes without a node
-  // (no couplings, D~^-1 0) may read any residual of the region, and take 0.
+  // staged element i of this lane: row i RPI + srow, column scol of the chunk.  Lanes without a node take a
+  // residual of 0 by a load out of the region's range, whatever (Inf, NaN) the residuals beside them hold:
+  // D~^-1 = 0 alone would make it NaN, which the shifts carry into the rows above.
   const int srow = lane / B, scol = lane % B;
   const int y0 = 64 * w + srow, x0 = scol - G::WY * srow, l0 = y0 * R.ex + x0;
   const int di = RPI * (R.ex - G::WY);
@@ -263,11 +264,14 @@ __global__ __launch_bounds__(B == 16 ? 256 : (B == 8 ? 512 : 1024)) void k_gs_sw
 #pragma unroll
     for (int k = 0; k < NV; ++k) cf[j][k] = p[k * 64];
   };
+  const auto buf = __builtin_amdgcn_make_buffer_rsrc(const_cast<double*>(rr), 0, R.n * 8, 0x00020000);
   auto load_r = [&](int c) {
 #pragma unroll
     for (int i = 0; i < B; ++i) {
-      const int li = min(max(l0 + c * B + i * di, 0), R.n - 1);
-      rp[i] = rr[BACKWARD ? R.n - 1 - li : li];
+      const int li = l0 + c * B + i * di;
+      const bool in = (unsigned)(x0 + c * B - i * RPI * G::WY) < (unsigned)R.ex;
+      const int at = in ? 8 * (BACKWARD ? R.n - 1 - li : li) : -256;
+      rp[i] = __builtin_bit_cast(double, __builtin_amdgcn_raw_buffer_load_b64(buf, at, 0, 0));
     }
   };
 #pragma unroll
@@ -350,7 +354,7 @@ static bool gs2d_ok(const Level& L) {
   if (L.dim != 2 || L.ndof != 1 || L.nreg > 65535) return false;
   int64_t lanes = 0;
   for (const RegionGeo& R : L.regs) {
-    if (R.ey > 1024) return false;
+    if (R.ey > 1024 || (int64_t)(R.ey + 64) * R.ex >= (int64_t)1 << 28) return false;  // (byte offsets in 32 bits)
     lanes += (int64_t)((R.ey + 63) / 64) * Gs2d<NPTS>::steps(R.ex, R.ey) * 64;
   }
   return lanes <= 8 * L.n || lanes * 2 * Gs2d<NPTS>::NV * (int64_t)sizeof(double) <= (int64_t)256 << 20;
