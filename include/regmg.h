@@ -166,7 +166,9 @@ typedef struct {
                          levels where that is faster than streaming) instead of being
                          streamed from memory.  The regions of an RMG_PDE_DIFFUSION finest level
                          that no table serves assemble their couplings on the fly in FP64 (levels
-                         of 2.5D tiles or at least 600,000 nodes).  Results are bit for bit those
+                         of 2.5D tiles or at least 600,000 nodes), from the coefficients kept by
+                         rmg_assemble_q1 until a setup with region_table = 0, symmetric = 0 or
+                         batched = 0.  Results are bit for bit those
                          of 0, which always streams the couplings */
   int tile_planes;    /* planes per 2.5D tile (non-zero also runs the table tiles of 3-dof levels of
                          any size): 0 (default) chooses (41 on FP64 levels that keep at

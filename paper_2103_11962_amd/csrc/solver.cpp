@@ -265,6 +265,7 @@ static void configure_level(rmg_handle* h, Level& L, bool with_b, bool sym) {
   if (sym) {
     // class tables for the 2.5D tiles and for the levels run by node blocks
     const bool tables = o.region_table != 0 && L.npts == 27 && !L.per_region;
+    if (!tables) L.elem.release();  // (8 B an element that only the tables' levels use)
     L.lowp_cycle = !fp64;
     L.split_lo = L.fill_lo = true;
     L.split_auto = o.stencil_kernel == 0;
@@ -272,6 +273,7 @@ static void configure_level(rmg_handle* h, Level& L, bool with_b, bool sym) {
     L.deep_table = o.tile_planes != 0;
     launch_make_sym(L, false, h->stream, tables);
   } else {
+    L.elem.release();
     L.coef_sym.release();
     L.class_table.release();
     L.class_table_ok.release();

@@ -129,3 +129,28 @@ def test_setups_of_other_and_of_same_options(hip_device):
     assert c.large <= 2 * 4, c.large
     h.close()
     assert c.live == c0.live == 0
+
+
+@pytest.mark.parametrize("opts", [dict(region_table=0), dict(symmetric=0), dict(batched=0)])
+def test_element_coefficients_only_where_used(hip_device, opts):
+    """A setup that always streams gives the kept element coefficients back: beside the Laplacian's, the
+    diffusion operator's handle then holds the network's FP32 features only."""
+    import torch
+
+    from paper_2103_11962_amd import regmg
+
+    o, e = synth.tensor_layout([[46, 43], [40], [43]])
+    cells = [int(v) for v in (o + e).max(axis=0) - 1]
+    elements = int(np.prod(cells))
+    ec = torch.ones(elements, dtype=torch.float64, device="cuda:0")
+    held = []
+    for pde, coef in ((regmg.PDE_LAPLACE, None), (regmg.PDE_DIFFUSION, ec)):
+        c = Counter()
+        h = regmg.Handle(0, allocator=c.provider)
+        h.build_regions(3, 1, e, o, 63)
+        h.assemble_q1(pde, 0.1, elem_coef=coef)
+        h.setup_hierarchy(nlevels=3, cheb_degree=2, **opts)
+        held.append(c.live)
+        h.close()
+        assert c.live == 0
+    assert held[1] - held[0] == 4 * elements
