@@ -177,38 +177,80 @@ __device__ __forceinline__ void node_product(const C* __restrict__ coef, const f
              : nullptr;
 #pragma unroll
   for (int a = 0; a < NDOF; ++a) acc[a] = (V)0;
-  // Scalar: a coupling that leaves the box loads from the node itself and its sum is not taken, so
-  // every load is unconditional and many are in flight.
-  auto sum = [&](auto coupling) __attribute__((always_inline)) {
+  if constexpr (NDOF == 3) {
+    // A block is nine loads already: one coupling block at a time, all 27 in flight would spill.  The empty
+    // asm keeps the compiler from moving the two branches' last load and product behind them, where every
+    // block waits for that load alone: a product on 6.1M streamed nodes 1852 us so, 1816 with a loop of
+    // its own for table and stream, 1728 as it is.
 #pragma unroll
     for (int s = 0; s < NPTS; ++s) {
       int dx, dy, dz;
       stencil_offset<NPTS>(s, dx, dy, dz);
       const bool ok = inner || ((unsigned)(x + dx) < (unsigned)R.ex && (unsigned)(y + dy) < (unsigned)R.ey &&
                                 (unsigned)(z + dz) < (unsigned)R.ez);
-      if (NDOF == 3 && !ok) continue;  // (a block is nine loads already; all 27 in flight would spill)
-      const int nb = ok ? li + dx + dy * sy + dz * sz : li;
+      if (ok) {
+        const int nb = li + dx + dy * sy + dz * sz;
+        if constexpr (SYM) {
+          if (kTab && tabbed) {
 #pragma unroll
-      for (int a = 0; a < NDOF; ++a) {
-        V t = acc[a];
+            for (int a = 0; a < NDOF; ++a)
 #pragma unroll
-        for (int b = 0; b < NDOF; ++b) t += coupling(s, a, b, nb) * xr[nb * NDOF + b];
-        acc[a] = ok ? t : acc[a];
+              for (int b = 0; b < NDOF; ++b) acc[a] += tc[(s * NDOF + a) * NDOF + b] * xr[nb * NDOF + b];
+            __asm__ volatile("");
+          } else if (s >= 13) {
+#pragma unroll
+            for (int a = 0; a < NDOF; ++a)
+#pragma unroll
+              for (int b = 0; b < NDOF; ++b) {
+                V c;
+                if (sizeof(C) == 2 && s == 13) c = (V)centre[gi * NB + a * NDOF + b];
+                else c = (V)CoefLoad<C>::get(cf + ((s - 13) * NB + a * NDOF + b) * kTile);
+                acc[a] += c * xr[nb * NDOF + b];
+              }
+          } else {
+            const C* __restrict__ cn = coef + coef_index(R.off + nb, 0, NCOEF);
+#pragma unroll
+            for (int a = 0; a < NDOF; ++a)
+#pragma unroll
+              for (int b = 0; b < NDOF; ++b)
+                acc[a] += (V)CoefLoad<C>::get(cn + ((13 - s) * NB + b * NDOF + a) * kTile) * xr[nb * NDOF + b];
+          }
+        } else {
+#pragma unroll
+          for (int a = 0; a < NDOF; ++a)
+#pragma unroll
+            for (int b = 0; b < NDOF; ++b)
+              acc[a] += (V)coefv<NPTS, NDOF, C>(cf, centre, gi, s, a, b) * xr[nb * NDOF + b];
+        }
       }
     }
-  };
-  if (kTab && tabbed) {
-    sum([&](int s, int a, int b, int) { return tc[(s * NDOF + a) * NDOF + b]; });
-  } else if constexpr (SYM) {
-    sum([&](int s, int a, int b, int nb) -> V {
-      if (s > 13) return (V)CoefLoad<C>::get(cf + ((s - 13) * NB + a * NDOF + b) * kTile);
-      if (s < 13)
-        return (V)CoefLoad<C>::get(coef + coef_index(R.off + nb, 0, NCOEF) + ((13 - s) * NB + b * NDOF + a) * kTile);
-      if (sizeof(C) == 2) return (V)centre[gi * NB + a * NDOF + b];
-      return (V)CoefLoad<C>::get(cf + (a * NDOF + b) * kTile);
-    });
   } else {
-    sum([&](int s, int a, int b, int) { return (V)coefv<NPTS, NDOF, C>(cf, centre, gi, s, a, b); });
+    // a coupling that leaves the box loads from the node itself and its sum is not taken, so every load is
+    // unconditional and many are in flight
+    auto sum = [&](auto coupling) __attribute__((always_inline)) {
+#pragma unroll
+      for (int s = 0; s < NPTS; ++s) {
+        int dx, dy, dz;
+        stencil_offset<NPTS>(s, dx, dy, dz);
+        const bool ok = inner || ((unsigned)(x + dx) < (unsigned)R.ex && (unsigned)(y + dy) < (unsigned)R.ey &&
+                                  (unsigned)(z + dz) < (unsigned)R.ez);
+        const int nb = ok ? li + dx + dy * sy + dz * sz : li;
+        const V t = acc[0] + coupling(s, nb) * xr[nb];
+        acc[0] = ok ? t : acc[0];
+      }
+    };
+    if (kTab && tabbed) {
+      sum([&](int s, int) { return tc[s]; });
+    } else if constexpr (SYM) {
+      sum([&](int s, int nb) -> V {
+        if (s > 13) return (V)CoefLoad<C>::get(cf + (s - 13) * kTile);
+        if (s < 13) return (V)CoefLoad<C>::get(coef + coef_index(R.off + nb, 0, NCOEF) + (13 - s) * kTile);
+        if (sizeof(C) == 2) return (V)centre[gi];
+        return (V)CoefLoad<C>::get(cf);
+      });
+    } else {
+      sum([&](int s, int) { return (V)coefv<NPTS, NDOF, C>(cf, centre, gi, s, 0, 0); });
+    }
   }
 }
 
