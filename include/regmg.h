@@ -194,7 +194,8 @@ typedef struct {
                          planes (a block owns whole rows of a region and walks its planes, staging
                          the values it reads in LDS) wherever every region's rows fit a block
                          (coarse and fine rows of at most 256 nodes), and the restriction into a coarse
-                         level of at most 200,000 nodes (batched = 1) together with its interface sum in
+                         level of at most 200,000 nodes and 50,000 copies of interface nodes
+                         (batched = 1) together with its interface sum in
                          one launch, one thread per coarse node; 0 one thread per node, the interface sum
                          after it.  All give the same results bit for bit */
 } rmg_options;

@@ -207,7 +207,10 @@ constexpr int64_t kFuseStream3 = 10000;
 // launch (k_restrict_all).  A V-cycle with the line above and below the coarse level: 8 x 28^3 coarse nodes
 // (176,000) 575 us by rows and planes, 569 in one launch, in FP32 537 and 536; 3 dofs 2814 and 2800; 64 x 16^3
 // (262,000) 810 and 841, 772 and 790; 27 x 28^3 (593,000) 1400 and 1445; 2D the same to 1% up to 1.3M nodes.
+// With many copies, whose restrictions are computed apart: 512 x 6^3 coarse nodes (110,592, 71,000 copies) 3 dofs
+// 6315 and 6415 us, scalar 608 and 617; 512 x 5^3 (64,000, 46,000 copies) 5475 and 5532, scalar 488 and 472.
 constexpr int64_t kFuseRestrict = 200000;
+constexpr int64_t kFuseRestrictCopies = 50000;
 
 // Interface copies in blocks, for the node-block kernels that finish the shared nodes themselves (small
 // levels): block k serves copies start[k] .. start[k + 1], whole groups of at most kBlock copies together.
@@ -270,6 +273,7 @@ struct Level {
   DBuf d_copies, d_copy_start;
   DBuf d_owner;  // with them: int32 per regional node, 1 on a group's first copy
   int ncopyblk = 0;
+  int64_t ncopies = 0;  // interface copies of the level
   // operator (FP64, wave-tiled, ncoef() values per node: npts blocks of ndof x ndof)
   DBuf coef;
   DBuf coef_sym;     // symmetric scalar 27-point levels: the upper half (kSymPts per node), else empty
@@ -354,7 +358,7 @@ struct Level {
   CopyView copies() const { return {d_copies.as<int4>(), d_copy_start.as<int>(), ncopyblk}; }
   // shared nodes finished by the node-block kernels (the unbatched option keeps one launch per region)
   bool fused_restriction() const {  // into this level
-    return n <= kFuseRestrict && !per_region && (ngroups == 0 || ncopyblk > 0);
+    return n <= kFuseRestrict && ncopies <= kFuseRestrictCopies && !per_region && (ngroups == 0 || ncopyblk > 0);
   }
   bool fused_stencil(bool lowp) const {
     if (per_region || ncopyblk == 0) return false;

@@ -570,6 +570,7 @@ void build_tables(Level& L) {
   L.d_copy_start.release();
   L.d_owner.release();
   L.ncopyblk = 0;
+  L.ncopies = (int64_t)gcopy2.size();
   if (ng > 0 && L.n <= kFuseNodes && (int64_t)gcopy2.size() <= kFuseCopies && most <= kBlock) {
     std::vector<int4> info(gcopy2.size());
     std::vector<int32_t> start(1, 0), owner(L.n, 0);

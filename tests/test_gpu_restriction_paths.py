@@ -44,17 +44,30 @@ def test_restriction_paths_agree(hip_device, name):
             h.close()
 
 
-def test_restriction_line(hip_device):
-    """Into a coarse level above the line the interface sum is a launch of its own."""
+def counts_split(h, nf):
+    """Launches of a restriction without its interface sum: fill, scaling product, one."""
     import torch
 
     from paper_2103_11962_amd import regmg
 
-    for r, fused in ((3, True), (4, False)):
-        o, e = synth.tensor_layout([[46] * r] * 3)
+    v = torch.zeros(nf, dtype=torch.float64, device="cuda:0")
+    before = regmg.kernel_launches()
+    h.regional_matvec(0, v, torch.empty_like(v))
+    return 2 + regmg.kernel_launches() - before
+
+
+def test_restriction_line(hip_device):
+    """Into a coarse level above either line the interface sum is a launch of its own."""
+    import torch
+
+    from paper_2103_11962_amd import regmg
+
+    # (regions a side, extent): few copies, too many nodes, too many copies
+    for r, ex, fused in ((3, 46, True), (4, 46, False), (7, 15, True), (8, 15, False)):
+        o, e = synth.tensor_layout([[ex] * r] * 3)
         h = harness.gpu_problem(synth.Workload("line", 3, 1, o, e, 63, 3, 1, "laplace", h=0.1))
         nf, nc = h.level_info(0)["n_regional"], h.level_info(1)["n_regional"]
-        assert (nc <= 200000) == fused
+        assert (nc <= 200000) == (ex != 46 or r == 3)
         x = torch.zeros(nf, dtype=torch.float64, device="cuda:0")
         y = torch.empty(nc, dtype=torch.float64, device="cuda:0")
         counts = []
@@ -62,6 +75,7 @@ def test_restriction_line(hip_device):
             before = regmg.kernel_launches()
             h.restrict(0, x, y)
             counts.append(regmg.kernel_launches() - before)
-        # fill, scaling product with its interface kernel, restriction
-        assert counts == [4 if fused else 5] * 2
+        # fill, scaling product (with its interface kernel on levels of many copies), restriction
+        assert counts[0] == counts[1]
+        assert counts[0] - counts_split(h, nf) == (0 if fused else 1), counts
         h.close()
