@@ -225,8 +225,9 @@ __device__ __forceinline__ void node_product(const C* __restrict__ coef, const f
       }
     }
   } else {
-    // a coupling that leaves the box loads from the node itself and its sum is not taken, so every load is
-    // unconditional and many are in flight
+    // A coupling that leaves the box loads from the node itself and its sum is not taken, so every load is
+    // unconditional and many are in flight.  (The loops over one dof keep the compiler from making branches
+    // of these selections: without them a step of a small level took half as long again.)
     auto sum = [&](auto coupling) __attribute__((always_inline)) {
 #pragma unroll
       for (int s = 0; s < NPTS; ++s) {
@@ -235,21 +236,27 @@ __device__ __forceinline__ void node_product(const C* __restrict__ coef, const f
         const bool ok = inner || ((unsigned)(x + dx) < (unsigned)R.ex && (unsigned)(y + dy) < (unsigned)R.ey &&
                                   (unsigned)(z + dz) < (unsigned)R.ez);
         const int nb = ok ? li + dx + dy * sy + dz * sz : li;
-        const V t = acc[0] + coupling(s, nb) * xr[nb];
-        acc[0] = ok ? t : acc[0];
+#pragma unroll
+        for (int a = 0; a < NDOF; ++a) {
+          V t = acc[a];
+#pragma unroll
+          for (int b = 0; b < NDOF; ++b) t += coupling(s, a, b, nb) * xr[nb * NDOF + b];
+          acc[a] = ok ? t : acc[a];
+        }
       }
     };
     if (kTab && tabbed) {
-      sum([&](int s, int) { return tc[s]; });
+      sum([&](int s, int a, int b, int) { return tc[(s * NDOF + a) * NDOF + b]; });
     } else if constexpr (SYM) {
-      sum([&](int s, int nb) -> V {
-        if (s > 13) return (V)CoefLoad<C>::get(cf + (s - 13) * kTile);
-        if (s < 13) return (V)CoefLoad<C>::get(coef + coef_index(R.off + nb, 0, NCOEF) + (13 - s) * kTile);
-        if (sizeof(C) == 2) return (V)centre[gi];
-        return (V)CoefLoad<C>::get(cf);
+      sum([&](int s, int a, int b, int nb) -> V {
+        if (s > 13) return (V)CoefLoad<C>::get(cf + ((s - 13) * NB + a * NDOF + b) * kTile);
+        if (s < 13)
+          return (V)CoefLoad<C>::get(coef + coef_index(R.off + nb, 0, NCOEF) + ((13 - s) * NB + b * NDOF + a) * kTile);
+        if (sizeof(C) == 2) return (V)centre[gi * NB + a * NDOF + b];
+        return (V)CoefLoad<C>::get(cf + (a * NDOF + b) * kTile);
       });
     } else {
-      sum([&](int s, int) { return (V)coefv<NPTS, NDOF, C>(cf, centre, gi, s, 0, 0); });
+      sum([&](int s, int a, int b, int) { return (V)coefv<NPTS, NDOF, C>(cf, centre, gi, s, a, b); });
     }
   }
 }
