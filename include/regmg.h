@@ -158,15 +158,15 @@ typedef struct {
                          operator is the same everywhere inside, as the structured regions of the
                          Q1 Laplacian, the per-region diffusion and elasticity problems give), the
                          region's couplings come from its 125 x 27 class table (whole-row tiles on
-                         scalar levels of 2.5D tiles or, all regions served, of at least 400,000
-                         nodes (1,000,000 with a low-precision V-cycle) whose planes fill the tiles,
-                         and on 3-dof levels of at least 900,000 to 1,500,000 nodes with rows of
-                         at least 44, each node's class row on
+                         scalar levels of 2.5D tiles or, all regions served, of at least 300,000
+                         to 400,000 nodes (1,100,000 with a low-precision V-cycle) whose planes
+                         fill the tiles, and on 3-dof levels of at least 900,000 to 1,500,000 nodes
+                         with rows of at least 44, each node's class row on
                          node blocks; the low-precision V-cycle has a table of its own values, on scalar
                          levels where that is faster than streaming) instead of being
                          streamed from memory.  The regions of an RMG_PDE_DIFFUSION finest level
                          that no table serves assemble their couplings on the fly in FP64 (levels
-                         of 2.5D tiles or at least 600,000 nodes), from the coefficients kept by
+                         of 2.5D tiles or at least 330,000 to 600,000 nodes), from the coefficients kept by
                          rmg_assemble_q1 until a setup with region_table = 0, symmetric = 0 or
                          batched = 0.  Results are bit for bit those
                          of 0, which always streams the couplings */

@@ -9,7 +9,7 @@ from tests import harness
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("ext", [[[102], [101], [103]], [[62, 55], [60, 57], [60, 62]]])
+@pytest.mark.parametrize("ext", [[[110], [104], [103]], [[62, 55], [60, 57], [60, 62]]])
 @pytest.mark.parametrize("degree", [1, 3])
 def test_fp32_table_tiles_equal_node_blocks(hip_device, ext, degree):
     import torch

@@ -15,11 +15,16 @@ CASES = [
     (2, 36, "laplace", dict(), False, False, 0),  # 373,000 nodes
     (3, 25, "laplace", dict(), True, False, 0),  # 422,000
     (10, 8, "laplace", dict(), False, False, 0),  # planes of 64 nodes
+    (1, 66, "laplace", dict(), False, False, 0),  # 287,000
+    (1, 70, "laplace", dict(), True, False, 0),  # 343,000, long rows
     (2, 37, "laplace", dict(precision=1), False, False, 8),
     (3, 31, "laplace", dict(precision=1), False, False, 0),  # 804,000: streams
+    (1, 100, "laplace", dict(precision=1), False, False, 1),  # 1.0M: class rows on node blocks
     (3, 46, "laplace", dict(precision=1), True, False, 27),
     (8, 12, "laplace", dict(precision=1), False, False, 0),
     (3, 25, "diffusion", dict(), False, False, 0),
+    (2, 34, "diffusion", dict(), False, False, 0),  # 314,000
+    (2, 35, "diffusion", dict(), False, True, 0),  # 343,000, edge 35
     (3, 31, "diffusion", dict(), False, True, 0),
     (3, 31, "diffusion", dict(precision=1), False, True, 0),
 ]
