@@ -228,17 +228,16 @@ def variant_mixed(dev):
         peff = prec if prec != 3 else (2 if pl[0]["coef_type"] == 2 else 1)
         h.profile(True)
         ms, res, x = _timed_solves(h, b)
-        # equal FP64 blocks round to equal ones, so the low-precision tables serve the regions the
-        # FP64 ones do (level_table_regions counts those of an FP64 V-cycle)
-        if prec == 0:
-            served = h.level_table_regions(0) / len(w.extents)
+        # regions whose couplings the V-cycle takes from class tables
+        tabled = h.level_table_regions(0) if prec == 0 else h.level_split(0)["regions_lo"]
+        served = tabled / len(w.extents)
         entry = {"setup_ms": setup_ms, "solve_ms": ms, "iterations": res["iterations"],
                  "true_relres": res["true_relres"],
                  "cheb_gbs": _cheb_gbs(h, "block3", peff, rows, stored=False),
                  "cheb_bytes_per_node": _cheb_bytes(h, "block3", peff, stored=False),
                  "cheb_gbs_at_stored_bytes": _cheb_gbs(h, "block3", peff, rows, served=served),
                  "cheb_stored_bytes_per_node": _cheb_bytes(h, "block3", peff, served=served),
-                 "table_regions": h.level_table_regions(0)}
+                 "table_regions": tabled}
         if prec == 3:
             entry["levels"] = [{"coef_type": p["coef_type"], "rho_fp32": p["rho_fp32"], "rho_bf16": p["rho_bf16"]}
                                for p in pl]
@@ -265,13 +264,13 @@ def variant_batched(dev):
     w = synth.workload("c4")
     b = _to_dev(synth.rhs(w), dev)
     out = {}
-    served = 1.0  # the Laplacian's couplings are one set per class in every region
     cache = os.path.join(tempfile.gettempdir(), "regmg_bench_tune.txt")
     for name, opts in (("region_by_region", dict(precision=1, batched=0)),
                        ("batched", dict(precision=1, autotune=1, autotune_cache=cache, use_graph=1))):
         h = _handle(w, dev)
         setup_ms = _setup(h, w, **opts)
         rows = h.level_info(0)["n_regional"]
+        served = h.level_split(0)["regions_lo"] / len(w.extents)
         h.profile(True)
         ms, res, _ = _timed_solves(h, b)
         out[name] = {"setup_ms": setup_ms, "solve_ms": ms, "iterations": res["iterations"],
