@@ -158,7 +158,8 @@ __device__ __forceinline__ auto coefv(const C* __restrict__ cf, const float* __r
 // regions whose flag in table_ok is set: a node's 27 couplings (3 x 3 blocks on 3-dof levels) are
 // its class's (the values the half stencil applies, bit for bit), read from the small table
 // instead of from its own and its neighbours' records.
-template <int NPTS, int NDOF, class V, class C, bool SYM>
+// FUSED: the form for the small levels of k_stencil_fused.
+template <int NPTS, int NDOF, class V, class C, bool SYM, bool FUSED>
 __device__ __forceinline__ void node_product(const C* __restrict__ coef, const float* __restrict__ centre,
                                              const V* __restrict__ xv, const V* __restrict__ table,
                                              const int* __restrict__ table_ok, int region, const RegionGeo& R, int li,
@@ -177,11 +178,12 @@ __device__ __forceinline__ void node_product(const C* __restrict__ coef, const f
              : nullptr;
 #pragma unroll
   for (int a = 0; a < NDOF; ++a) acc[a] = (V)0;
-  if constexpr (NDOF == 3) {
+  if constexpr (NDOF == 3 && !FUSED) {
     // A block is nine loads already: one coupling block at a time, all 27 in flight would spill.  The empty
     // asm keeps the compiler from moving the two branches' last load and product behind them, where every
     // block waits for that load alone: a product on 6.1M streamed nodes 1852 us so, 1816 with a loop of
-    // its own for table and stream, 1728 as it is.
+    // its own for table and stream, 1728 as it is.  (Small levels, bound by latency, are 3 to 5% faster
+    // with a loop for each: below.)
 #pragma unroll
     for (int s = 0; s < NPTS; ++s) {
       int dx, dy, dz;
@@ -225,7 +227,7 @@ __device__ __forceinline__ void node_product(const C* __restrict__ coef, const f
       }
     }
   } else {
-    // A coupling that leaves the box loads from the node itself and its sum is not taken, so every load is
+    // Scalar: a coupling that leaves the box loads from the node itself and its sum is not taken, so every load is
     // unconditional and many are in flight.  (The loops over one dof keep the compiler from making branches
     // of these selections: without them a step of a small level took half as long again.)
     auto sum = [&](auto coupling) __attribute__((always_inline)) {
@@ -235,6 +237,7 @@ __device__ __forceinline__ void node_product(const C* __restrict__ coef, const f
         stencil_offset<NPTS>(s, dx, dy, dz);
         const bool ok = inner || ((unsigned)(x + dx) < (unsigned)R.ex && (unsigned)(y + dy) < (unsigned)R.ey &&
                                   (unsigned)(z + dz) < (unsigned)R.ez);
+        if (NDOF == 3 && !ok) continue;
         const int nb = ok ? li + dx + dy * sy + dz * sz : li;
 #pragma unroll
         for (int a = 0; a < NDOF; ++a) {
@@ -309,7 +312,7 @@ __global__ __launch_bounds__(kBlock) void k_stencil(LevelView L, const C* __rest
     const V* __restrict__ xs = p.x + gi * NDOF;
     const bool inner = inner_node<NPTS>(R, x, y, z);
     V acc[NDOF];
-    node_product<NPTS, NDOF, V, C, SYM>(coef, centre, p.x, table, table_ok, bd.region, R, li, x, y, z, inner, acc);
+    node_product<NPTS, NDOF, V, C, SYM, false>(coef, centre, p.x, table, table_ok, bd.region, R, li, x, y, z, inner, acc);
     if (!inner && is_shared(L, R, x, y, z)) {
 #pragma unroll
       for (int a = 0; a < NDOF; ++a)  // summed over copies by k_iface
@@ -353,7 +356,7 @@ __global__ __launch_bounds__(kBlock) void k_stencil_fused(LevelView L, CopyView 
       if (inner || !is_shared(L, R, x, y, z)) {
         const int64_t gi = R.off + li;
         V acc[NDOF];
-        node_product<NPTS, NDOF, V, C, SYM>(coef, centre, p.x, table, table_ok, bd.region, R, li, x, y, z, inner, acc);
+        node_product<NPTS, NDOF, V, C, SYM, true>(coef, centre, p.x, table, table_ok, bd.region, R, li, x, y, z, inner, acc);
         contrib = finish_node<NDOF, OP, DOT, V>(p, gi, acc, p.x + gi * NDOF);
       }
     }
@@ -372,7 +375,7 @@ __global__ __launch_bounds__(kBlock) void k_stencil_fused(LevelView L, CopyView 
       int x, y, z;
       decompose(R, li, x, y, z);
       V acc[NDOF];
-      node_product<NPTS, NDOF, V, C, SYM>(coef, centre, p.x, table, table_ok, ci.y, R, li, x, y, z, false, acc);
+      node_product<NPTS, NDOF, V, C, SYM, true>(coef, centre, p.x, table, table_ok, ci.y, R, li, x, y, z, false, acc);
 #pragma unroll
       for (int a = 0; a < NDOF; ++a) {
         part[t * NDOF + a] = acc[a];
@@ -858,8 +861,9 @@ __global__ __launch_bounds__(kTableThreads) __attribute__((amdgpu_waves_per_eu(s
 // almost all of one class.  Planes of three-vectors pass through two LDS slots as there, and each plane
 // read adds its products to the running sums of the three nodes it neighbours in z; every node's
 // sums are k_stencil's, product for product, so the results are bit for bit those of node blocks.
-// 27 regions of 55^3 (4.5M nodes): CG product 405 us on node blocks, 272 here, the last smoothing step
-// with its inner product 487 and 446, an FP32 Chebyshev step 171 (streaming BF16 blocks 478).  A step is
+// 27 regions of 55^3 (4.5M nodes): CG product 405 us on node blocks, 272 here, a Chebyshev step 490 and
+// 364 (its inner product is a pass of its own, 22 us: in the step it spilled 30 registers and took 446
+// in all), an FP32 Chebyshev step 177 (streaming BF16 blocks 478).  A step is
 // bound by the latency between planes: 128 to 168 VGPRs leave twelve wavefronts a CU, whose 31 scalar
 // loads and one plane's memory latency a step the 243 products (1,000 cycles) only half cover.  Taking
 // the x-face columns' classes one after the other by scalar loads instead of from LDS cost 440 us (their
