@@ -159,9 +159,9 @@ typedef struct {
                          Q1 Laplacian, the per-region diffusion and elasticity problems give), the
                          region's couplings come from its 125 x 27 class table (whole-row tiles on
                          scalar levels of 2.5D tiles or, all regions served, of at least 300,000
-                         to 400,000 nodes (1,100,000 with a low-precision V-cycle) whose planes
-                         fill the tiles, and on 3-dof levels of at least 900,000 to 1,500,000 nodes
-                         with rows of at least 44, each node's class row on
+                         to 400,000 nodes (800,000 to 1,100,000 with a low-precision V-cycle)
+                         whose planes fill the tiles, and on 3-dof levels of at least 750,000 to
+                         1,500,000 nodes with rows of at least 44, each node's class row on
                          node blocks; the low-precision V-cycle has a table of its own values, on scalar
                          levels where that is faster than streaming) instead of being
                          streamed from memory.  The regions of an RMG_PDE_DIFFUSION finest level
@@ -194,8 +194,8 @@ typedef struct {
                          planes (a block owns whole rows of a region and walks its planes, staging
                          the values it reads in LDS) wherever every region's rows fit a block
                          (coarse and fine rows of at most 256 nodes), and the restriction into a coarse
-                         level of at most 200,000 nodes and 50,000 copies of interface nodes
-                         (batched = 1) together with its interface sum in
+                         level of at most 200,000 nodes (3 dofs: and 45,000 copies of interface
+                         nodes; batched = 1) together with its interface sum in
                          one launch, one thread per coarse node; 0 one thread per node, the interface sum
                          after it.  All give the same results bit for bit */
 } rmg_options;

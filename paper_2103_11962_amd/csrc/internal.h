@@ -199,18 +199,19 @@ struct LevelView {
 constexpr int64_t kFuseNodes = 600000;
 constexpr int64_t kFuseCopies = 200000;
 // Couplings streamed in 3D: scalar 8 x 17^3 nodes (39,000) 94 and 105 us in FP64, 82 and 104 in FP32,
-// 27 x 13^3 (59,000) 124 and 110, 104 and 109, 27 x 25^3 (422,000) 332 and 250, 258 and 202; 3 dofs 8 x 10^3
+// 27 x 13^3 (59,000) 124 and 110, 104 and 109, 8 x 25^3 (125,000) 194 and 160, 140 and 133; 3 dofs 8 x 10^3
 // (8,000) 157 and 173, 121 and 151, 64 x 7^3 (22,000) 264 and 238, 228 and 212.
-constexpr int64_t kFuseStream = 40000;
+constexpr int64_t kFuseStream = 40000, kFuseStreamLo = 85000;
 constexpr int64_t kFuseStream3 = 10000;
 // Coarse levels of at most this many nodes take restriction, interface sum and zero-guess start in one
 // launch (k_restrict_all).  A V-cycle with the line above and below the coarse level: 8 x 28^3 coarse nodes
 // (176,000) 575 us by rows and planes, 569 in one launch, in FP32 537 and 536; 3 dofs 2814 and 2800; 64 x 16^3
 // (262,000) 810 and 841, 772 and 790; 27 x 28^3 (593,000) 1400 and 1445; 2D the same to 1% up to 1.3M nodes.
-// With many copies, whose restrictions are computed apart: 512 x 6^3 coarse nodes (110,592, 71,000 copies) 3 dofs
-// 6315 and 6415 us, scalar 608 and 617; 512 x 5^3 (64,000, 46,000 copies) 5475 and 5532, scalar 488 and 472.
+// On 3 dofs with many copies, whose restrictions are computed apart: 512 x 6^3 coarse nodes (110,592, 71,000 copies)
+// 2707 and 2749 us, 512 x 5^3 (64,000, 46,000) 1728 and 1739, 216 x 6^3 (46,656, 29,000) 1233 and 1218; scalar
+// levels gain at all of these and at 2197 x 4^3 (140,608, 119,000) 1549 and 1528.
 constexpr int64_t kFuseRestrict = 200000;
-constexpr int64_t kFuseRestrictCopies = 50000;
+constexpr int64_t kFuseRestrictCopies3 = 45000;
 
 // Interface copies in blocks, for the node-block kernels that finish the shared nodes themselves (small
 // levels): block k serves copies start[k] .. start[k + 1], whole groups of at most kBlock copies together.
@@ -358,11 +359,12 @@ struct Level {
   CopyView copies() const { return {d_copies.as<int4>(), d_copy_start.as<int>(), ncopyblk}; }
   // shared nodes finished by the node-block kernels (the unbatched option keeps one launch per region)
   bool fused_restriction() const {  // into this level
-    return n <= kFuseRestrict && ncopies <= kFuseRestrictCopies && !per_region && (ngroups == 0 || ncopyblk > 0);
+    return n <= kFuseRestrict && (ndof == 1 || ncopies <= kFuseRestrictCopies3) && !per_region &&
+           (ngroups == 0 || ncopyblk > 0);
   }
   bool fused_stencil(bool lowp) const {
     if (per_region || ncopyblk == 0) return false;
-    return dim == 2 || (lowp ? tabled_lo : tabled) == nreg || n <= (ndof == 3 ? kFuseStream3 : kFuseStream);
+    return dim == 2 || (lowp ? tabled_lo : tabled) == nreg || n <= (ndof == 3 ? kFuseStream3 : (lowp ? kFuseStreamLo : kFuseStream));
   }
 };
 

@@ -21,7 +21,7 @@ CASES = [
     (3, 2, 10, "elasticity", dict(region_table=0), 1),
     (3, 3, 10, "elasticity", dict(region_table=0), 2),
     (3, 3, 10, "elasticity", dict(), 1),
-    (1, 3, 13, "laplace", dict(precision=1), 1),
+    (1, 3, 13, "laplace", dict(precision=1), 1),  # (launches of the FP64 product)
     (1, 2, 20, "laplace", dict(precision=2), 1),
 ]
 

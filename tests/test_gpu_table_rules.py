@@ -18,7 +18,8 @@ CASES = [
     (1, 66, "laplace", dict(), False, False, 0),  # 287,000
     (1, 70, "laplace", dict(), True, False, 0),  # 343,000, long rows
     (2, 37, "laplace", dict(precision=1), False, False, 8),
-    (3, 31, "laplace", dict(precision=1), False, False, 0),  # 804,000: streams
+    (3, 30, "laplace", dict(precision=1), False, False, 0),  # 729,000: streams
+    (3, 31, "laplace", dict(precision=1), True, False, 27),  # 804,000
     (1, 100, "laplace", dict(precision=1), False, False, 1),  # 1.0M: class rows on node blocks
     (3, 46, "laplace", dict(precision=1), True, False, 27),
     (8, 12, "laplace", dict(precision=1), False, False, 0),
@@ -88,6 +89,8 @@ CASES3 = [
     ([[28] * 3] * 3, dict(), False),  # 593,000 nodes, edge 28
     ([[40] * 3] * 3, dict(), False),  # 1.7M, edge 40
     ([[50] * 2] * 3, dict(), False),  # 1.0M, edge 50
+    ([[46] * 2] * 3, dict(precision=1), True),  # 779,000, edge 46, FP32
+    ([[44] * 2] * 3, dict(precision=1), False),  # 681,000
     ([[58] * 2] * 3, dict(), True),  # 1.6M, edge 58
     ([[97], [97], [97]], dict(), True),  # 913,000, edge 97
     ([[97], [97], [97]], dict(precision=1), True),
