@@ -2422,7 +2422,8 @@ static void make_class_table_lo(Level& L, hipStream_t st) {
     const bool tiles = L.use_split && L.split_lo && L.ct_lo == kCoefF32 && (L.use_tiles || L.other_tiles.empty());
     int64_t rows = 0;
     for (const RegionGeo& R : L.regs) rows += (int64_t)R.ey * R.ez;
-    const bool nodes = !L.use_tiles && (L.ncopyblk > 0 || (double)L.n >= kTableMinRowLo * (double)rows);
+    const bool small = L.ncopyblk > 0 || (L.ngroups == 0 && L.n <= kFuseNodes);  // (one region: as fused)
+    const bool nodes = !L.use_tiles && (small || (double)L.n >= kTableMinRowLo * (double)rows);
     if (!tiles && !nodes) {
       L.split_lo = false;
       return;

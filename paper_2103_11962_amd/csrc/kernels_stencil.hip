@@ -343,8 +343,7 @@ __global__ __launch_bounds__(kBlock) void k_stencil_fused(LevelView L, CopyView 
   __shared__ V part[kBlock * NDOF];
   double contrib = 0.0;
   const int t = threadIdx.x;
-  // node blocks: a contiguous run for every XCD, as in k_stencil
-  const int blk = (int)blockIdx.x < nb ? xcd_item((int)blockIdx.x, nb) : (int)blockIdx.x;
+  const int blk = (int)blockIdx.x;
   if (blk < nb) {
     const BlockDesc bd = L.blocks[blk];
     const RegionGeo R = L.regs[bd.region];
