@@ -2318,9 +2318,9 @@ static void class_table_launch(const Level& L, const C* sym, const float* centre
 // 27 x 25^3 (422,000) 232 and 223, 8 x 46^3 (779,000) 293 and 225, 8 x 61^3 (1.8M) 527 and 347; by fill, 512 x 12^3
 // (0.28) 474 and 483, 1000 x 10^3 (0.20) 491 and 684, 216 x 13^3 (0.33) 300 and 297, 1331 x 13^3 1155 and 1029.
 // Long rows cross earlier (edge: mean_edge): 64^3 122 and 127 us, 68^3 (314,000) 140 and 129, 2 x 55^3 (333,000) 201
-// and 191.  An FP32 cycle, whose node blocks stream at half the bytes: 125 x 20^3 (1.0M) 341 and
-// 348, 27 x 31^3 (804,000) 246 and 239, 8 x 53^3 (1.2M) 260 and 245, and CG's FP64 product gains as above (27 x 31^3,
-// eight iterations: 2691 and 2540 us); few large regions later: 100^3 176 and 190, 2 x 82^3 (1.1M) 234 and 233.
+// and 191.  An FP32 cycle, whose node blocks stream at half the bytes: 125 x 20^3 (1.0M) 341 and 348, 27 x 31^3
+// (804,000) 246 and 239, 8 x 53^3 (1.2M) 260 and 245, and CG's FP64 product gains as above (27 x 31^3, eight
+// iterations: 2691 and 2540 us); few large regions later: 100^3 176 and 190, 2 x 82^3 (1.1M) 234 and 233.
 // Element tiles: 27 x 25^3 250 and 251, 216 x 13^3 286 and 306, 8 x 43^3 (636,000) 282 and 261,
 // 125 x 20^3 442 and 388; of edge 34 on 8 x 33^3 (287,000) 209 and 209, 2 x 55^3 236 and 228, 8 x 37^3 240 and 220.
 constexpr int64_t kTableMinNodes = 400000, kTableMinNodesLong = 300000;
@@ -2328,12 +2328,12 @@ constexpr int64_t kTableMinNodesLo = 800000, kTableMinNodesLoLong = 1100000;
 constexpr int64_t kElemMinNodes = 600000, kElemMinNodesLong = 330000;
 constexpr double kTableLongEdge = 55, kTableLongEdgeLo = 70, kElemLongEdge = 34;
 constexpr double kTableMinFill = 0.3;
-// FP32 cycles also leave 2.5D tiles that are not asked for (stencil_kernel) only from this fill on: 2197 x 12^3 nodes (0.28) 1204 us on 2.5D tiles and 1348
-// on table tiles, 2197 x 14^3 (0.38) 1545 and 1563, 2197 x 17^3 (0.56) 2668 and 1996; FP64 2968 and 2211 already
-// at 12^3.
+// FP32 cycles also leave 2.5D tiles that are not asked for (stencil_kernel) only from this fill on: 2197 x
+// 12^3 nodes (0.28) 1204 us on 2.5D tiles and 1348 on table tiles, 2197 x 14^3 (0.38) 1545 and 1563, 2197 x 17^3
+// (0.56) 2668 and 1996; FP64 2968 and 2211 already at 12^3.
 constexpr double kTableMinFillLo = 0.4;
-// Scalar low-precision node blocks read class tables on levels that finish their shared nodes themselves
-// (216 x 13^3: 227 us a V-cycle, streaming 255) and on rows of this mean length; else they stream: 1000 x 10^3
+// Scalar low-precision node blocks read class tables on levels that finish their shared nodes themselves or
+// have none (216 x 13^3: 227 us a V-cycle, streaming 255) and on rows of this mean length; else they stream: 1000 x 10^3
 // 366 us streaming and 427 from tables, 216 x 18^3 378 and 437, 125 x 25^3 505 and 553, 27 x 46^3 538 and 527,
 // 200 x (200 x 6 x 6) 435 and 403.
 constexpr double kTableMinRowLo = 46;
@@ -2344,8 +2344,8 @@ constexpr double kTableMinRowLo = 46;
 // (593,000 nodes) 748 and 1206 us, 343 regions (7.5M) 6998 and 8779; 64 x 40^3 (4.1M) 3555 and 4182; 43, 27
 // regions (2.1M) 1849 and 1880; 46 (2.6M) 2258 and 2207; 48 (3.0M) 2541 and 2319; 55, 8 regions (1.3M) 1193 and
 // 1227, 27 (4.5M) 3675 and 2973; 8 x 61^3 (1.8M) 1527 and 1338; 2 x 64^3 (524,000) 600 and 656, 4 x 64^3 (1.0M)
-// 950 and 874; 100^3 821 and 652.  FP32 cycles cross earlier: 8 x 46^3 (779,000) 595
-// and 561, 8 x 55^3 793 and 756 (eight iterations of CG 6067 and 5813 us, 27 x 40^3 1047 and 1089 a cycle).
+// 950 and 874; 100^3 821 and 652.  FP32 cycles cross earlier: 8 x 46^3 (779,000) 595 and 561, with eight
+// iterations of CG around them 6067 and 5813; 8 x 55^3 793 and 756; but 27 x 40^3 1047 and 1089.
 constexpr int64_t kTable3MinNodes = 1500000, kTable3MinNodesLong = 900000, kTable3MinNodesLo = 750000;
 constexpr double kTable3MinEdge = 44, kTable3LongEdge = 60;
 
