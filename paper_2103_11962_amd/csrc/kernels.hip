@@ -2344,8 +2344,8 @@ constexpr double kTableMinRowLo = 46;
 // (593,000 nodes) 748 and 1206 us, 343 regions (7.5M) 6998 and 8779; 64 x 40^3 (4.1M) 3555 and 4182; 43, 27
 // regions (2.1M) 1849 and 1880; 46 (2.6M) 2258 and 2207; 48 (3.0M) 2541 and 2319; 55, 8 regions (1.3M) 1193 and
 // 1227, 27 (4.5M) 3675 and 2973; 8 x 61^3 (1.8M) 1527 and 1338; 2 x 64^3 (524,000) 600 and 656, 4 x 64^3 (1.0M)
-// 950 and 874; 100^3 821 and 652.  FP32 cycles cross earlier: 8 x 46^3 (779,000) 595 and 561, with eight
-// iterations of CG around them 6067 and 5813; 8 x 55^3 793 and 756; but 27 x 40^3 1047 and 1089.
+// 950 and 874; 100^3 821 and 652.  FP32 cycles cross earlier: 8 x 46^3 (779,000) 595 and 561, 8 x 55^3 793
+// and 756 (in a CG solve of eight iterations 6067 and 5813); but 27 x 40^3 1047 and 1089.
 constexpr int64_t kTable3MinNodes = 1500000, kTable3MinNodesLong = 900000, kTable3MinNodesLo = 750000;
 constexpr double kTable3MinEdge = 44, kTable3LongEdge = 60;
 
